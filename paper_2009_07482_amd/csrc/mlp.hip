@@ -3,13 +3,14 @@
 // trained on op times the runtime records.
 //
 // Training step on a batch of B samples (row indices into the uploaded sample set):
-//   mlp_fwd     z1 = W1 xn + b1, h1 = relu(z1), z2 = W2 h1 + b2, h2 = relu(z2), y = W3 h2 + b3,
-//               with xn the z-scored features; z1, z2 and y are kept per sample.
-//   mlp_delta   dy = 2 (y - t) / B, dz2 = dy W3 * [z2 > 0], dz1 = (W2^T dz2) * [z1 > 0]
-//   mlp_update  one thread per parameter sums its gradient over the batch in sample order
-//               (deterministic), then applies Adam with bias-corrected moments.
-// The network is ~9.9 kFLOP per sample forward, so every kernel is latency-bound: plain FP32
-// vector FMAs with the weights staged in LDS, not matrix cores.
+//   mlp_pass    z1 = W1 xn + b1, h1 = relu(z1), z2 = W2 h1 + b2, h2 = relu(z2), y = W3 h2 + b3,
+//               with xn the z-scored features, then dy = 2 (y - t) / B, dz2 = dy W3 * [z2 > 0],
+//               dz1 = (W2^T dz2) * [z1 > 0]; h1, h2, y and the deltas are kept per sample.
+//   mlp_update  sums every parameter's gradient over the batch in sample order (deterministic),
+//               then applies Adam with bias-corrected moments.
+// The network is ~9.9 kFLOP per sample forward and every step depends on the one before, so both
+// kernels are bound by latency (plain FP32 vector FMAs, not matrix cores): each sum is one chain
+// of dependent FMAs in a fixed order, and what can be shortened is the memory latency around it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -31,127 +32,237 @@ namespace psc {
 
 namespace {
 
-constexpr int kSPB = 64;  // samples per block in mlp_fwd / mlp_delta (one per lane)
-constexpr int kUPW = kMlpH / 4;  // hidden units per wave
+constexpr int kSPW = 2;          // samples a wavefront of mlp_pass carries at a time
+constexpr int kPassBlocks = 512;  // blocks of a full grid (two per CU); larger sets loop
+constexpr int kChunk = 256;      // samples of a gradient chunk staged in LDS by mlp_update
+constexpr int kAhead = 32;       // samples of a gradient chain read from LDS ahead of their sums
 
-// Block: 256 threads = 4 waves; lane l handles sample blockIdx.x * 64 + l, wave w handles hidden
-// units [16w, 16w + 16).  Weight reads are wave-uniform (LDS broadcast).
-__global__ __launch_bounds__(256) void mlp_fwd(const float *__restrict__ P, const float *__restrict__ norm,
-                                               const float *__restrict__ X, const int32_t *__restrict__ idx,
-                                               int32_t n, float *__restrict__ Z1, float *__restrict__ Z2,
-                                               float *__restrict__ Y) {
-  __shared__ float w[kMlpP];
-  __shared__ float h1[kSPB][kMlpH + 1];
-  __shared__ float red[4][kSPB];
-  for (int i = threadIdx.x; i < kMlpP; i += 256) w[i] = P[i];
+// Forward and (BACK) back-propagation of kSPW samples per wavefront.  Lane j owns hidden unit j of
+// both layers: it holds row j of W1 and of W2 and (BACK) column j of W2 in registers, so a layer is
+// one chain of FMAs per lane whose other operand is a broadcast LDS read, and a batch of 256 runs
+// on 32 blocks.  Every sum keeps one order: z1 over the features, z2 and dz1 over the units, y as
+// four chains of 16 units added pairwise.  The outputs are written for mlp_update: H1, H2 after
+// ReLU (both are > 0 exactly where their pre-activations are), the deltas, Y and DY.
+// Measured at 256 samples: see mlp_update.
+template <bool BACK>
+__global__ __launch_bounds__(256) void mlp_pass(const float *__restrict__ P, const float *__restrict__ norm,
+                                                const float *__restrict__ X, const float *__restrict__ T,
+                                                const int32_t *__restrict__ idx, int32_t n, float scale,
+                                                float *__restrict__ H1, float *__restrict__ H2,
+                                                float *__restrict__ Y, float *__restrict__ DZ1,
+                                                float *__restrict__ DZ2, float *__restrict__ DY) {
+  __shared__ __attribute__((aligned(16))) float lds[4][kSPW][kMlpH];  // one region per wavefront
+  // W2 goes through LDS: its rows, read by lane straight from memory, would touch 64 cache lines
+  // per load.  Pitch 68: 16-byte row reads of 16 lanes and column reads cover distinct banks.
+  constexpr int kPitch = kMlpH + 4;
+  __shared__ __attribute__((aligned(16))) float w2[kMlpH * kPitch];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t s = int64_t(blockIdx.x) * kSPB + lane;
-  const bool ok = s < n;
-  float x[kMlpF];
-  if (ok) {
-    const int64_t r = idx ? idx[s] : s;
+  static_assert(kMlpW2 % 4 == 0 && kMlpF % 4 == 0 && kMlpW3 % 4 == 0, "16-byte parameter loads");
+  const float4 *P4 = reinterpret_cast<const float4 *>(P);
 #pragma unroll
-    for (int f = 0; f < kMlpF; ++f) x[f] = (X[r * kMlpF + f] - norm[f]) * norm[kMlpF + f];
-  } else {
+  for (int j = 0; j < kMlpH * kMlpH / 4 / 256; ++j) {
+    const int u = threadIdx.x + 256 * j;
+    *reinterpret_cast<float4 *>(&w2[u / (kMlpH / 4) * kPitch + u % (kMlpH / 4) * 4]) = P4[kMlpW2 / 4 + u];
+  }
+  float w1[kMlpF], row[kMlpH], col[BACK ? kMlpH : 1];
 #pragma unroll
-    for (int f = 0; f < kMlpF; ++f) x[f] = 0.0f;
+  for (int f = 0; f < kMlpF; f += 4) {
+    const float4 v = P4[(kMlpW1 + lane * kMlpF + f) / 4];
+    w1[f] = v.x, w1[f + 1] = v.y, w1[f + 2] = v.z, w1[f + 3] = v.w;
   }
-  __syncthreads();
-#pragma unroll 4
-  for (int u = 0; u < kUPW; ++u) {
-    const int j = wv * kUPW + u;
-    float z = w[kMlpB1 + j];
+  const float b1 = P[kMlpB1 + lane], b2 = P[kMlpB2 + lane], w3 = P[kMlpW3 + lane], b3 = P[kMlpB3];
+  // the output layer's chains: lane 4 q + c sums units [16 c, 16 c + 16) of sample q
+  const int q = (lane >> 2) % kSPW, c = lane & 3;
+  float w3c[kMlpH / 4];
 #pragma unroll
-    for (int f = 0; f < kMlpF; ++f) z = fmaf(w[kMlpW1 + j * kMlpF + f], x[f], z);
-    if (ok) Z1[s * kMlpH + j] = z;
-    h1[lane][j] = fmaxf(z, 0.0f);
+  for (int u = 0; u < kMlpH / 4; u += 4) {
+    const float4 v = P4[(kMlpW3 + c * (kMlpH / 4) + u) / 4];
+    w3c[u] = v.x, w3c[u + 1] = v.y, w3c[u + 2] = v.z, w3c[u + 3] = v.w;
   }
   __syncthreads();
-  float acc = 0.0f;
-  for (int u = 0; u < kUPW; ++u) {
-    const int j = wv * kUPW + u;
-    float z = w[kMlpB2 + j];
-#pragma unroll 16
-    for (int i = 0; i < kMlpH; ++i) z = fmaf(w[kMlpW2 + j * kMlpH + i], h1[lane][i], z);
-    if (ok) Z2[s * kMlpH + j] = z;
-    acc = fmaf(w[kMlpW3 + j], fmaxf(z, 0.0f), acc);
+#pragma unroll
+  for (int i = 0; i < kMlpH; i += 4) {
+    const float4 v = *reinterpret_cast<const float4 *>(&w2[lane * kPitch + i]);
+    row[i] = v.x, row[i + 1] = v.y, row[i + 2] = v.z, row[i + 3] = v.w;
   }
-  red[wv][lane] = acc;
-  __syncthreads();
-  if (wv == 0 && ok) Y[s] = w[kMlpB3] + ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]));
-}
-
-// Same block layout as mlp_fwd.  scale = 2 / B (the derivative of the batch-mean squared error).
-__global__ __launch_bounds__(256) void mlp_delta(const float *__restrict__ P, const float *__restrict__ T,
-                                                 const int32_t *__restrict__ idx, int32_t n, float scale,
-                                                 const float *__restrict__ Z1, const float *__restrict__ Z2,
-                                                 const float *__restrict__ Y, float *__restrict__ DZ1,
-                                                 float *__restrict__ DZ2, float *__restrict__ DY) {
-  __shared__ float w2[kMlpH * kMlpH];
-  __shared__ float w3[kMlpH];
-  __shared__ float d2[kSPB][kMlpH + 1];
-  for (int i = threadIdx.x; i < kMlpH * kMlpH; i += 256) w2[i] = P[kMlpW2 + i];
-  if (threadIdx.x < kMlpH) w3[threadIdx.x] = P[kMlpW3 + threadIdx.x];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t s = int64_t(blockIdx.x) * kSPB + lane;
-  const bool ok = s < n;
-  const float dy = ok ? scale * (Y[s] - T[idx ? idx[s] : s]) : 0.0f;
-  __syncthreads();
-  for (int u = 0; u < kUPW; ++u) {
-    const int j = wv * kUPW + u;
-    const float d = ok && Z2[s * kMlpH + j] > 0.0f ? dy * w3[j] : 0.0f;
-    if (ok) DZ2[s * kMlpH + j] = d;
-    d2[lane][j] = d;
+  if constexpr (BACK) {
+#pragma unroll
+    for (int i = 0; i < kMlpH; ++i) col[i] = w2[i * kPitch + lane];
   }
-  __syncthreads();
-  for (int u = 0; u < kUPW; ++u) {
-    const int i = wv * kUPW + u;
+  float(*buf)[kMlpH] = lds[wv];
+  // a wavefront reads only what it wrote itself, and its LDS operations take effect in program
+  // order; the fences keep the compiler to that order
+  auto order = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  const int64_t step = int64_t(gridDim.x) * 4 * kSPW;
+  for (int64_t s0 = (int64_t(blockIdx.x) * 4 + wv) * kSPW; s0 < n; s0 += step) {
+    int64_t s[kSPW], r[kSPW];
+    float z1[kSPW], z2[kSPW];
+#pragma unroll
+    for (int k = 0; k < kSPW; ++k) {
+      s[k] = s0 + k < n ? s0 + k : s0;  // a missing sample repeats the first and is not stored
+      r[k] = idx ? idx[s[k]] : s[k];
+      float z = b1;
+#pragma unroll
+      for (int f = 0; f < kMlpF; ++f) z = fmaf(w1[f], (X[r[k] * kMlpF + f] - norm[f]) * norm[kMlpF + f], z);
+      z1[k] = fmaxf(z, 0.0f);
+      buf[k][lane] = z1[k];
+      z2[k] = b2;
+    }
+    order();
+#pragma unroll
+    for (int i = 0; i < kMlpH; i += 4)
+#pragma unroll
+      for (int k = 0; k < kSPW; ++k) {
+        const float4 h = *reinterpret_cast<const float4 *>(&buf[k][i]);
+        z2[k] = fmaf(row[i + 3], h.w, fmaf(row[i + 2], h.z, fmaf(row[i + 1], h.y, fmaf(row[i], h.x, z2[k]))));
+      }
+    order();
+#pragma unroll
+    for (int k = 0; k < kSPW; ++k) {
+      z2[k] = fmaxf(z2[k], 0.0f);
+      buf[k][lane] = z2[k];
+    }
+    order();
     float acc = 0.0f;
-#pragma unroll 16
-    for (int j = 0; j < kMlpH; ++j) acc = fmaf(w2[j * kMlpH + i], d2[lane][j], acc);
-    if (ok) DZ1[s * kMlpH + i] = Z1[s * kMlpH + i] > 0.0f ? acc : 0.0f;
+#pragma unroll
+    for (int u = 0; u < kMlpH / 4; u += 4) {
+      const float4 h = *reinterpret_cast<const float4 *>(&buf[q][c * (kMlpH / 4) + u]);
+      acc = fmaf(w3c[u + 3], h.w, fmaf(w3c[u + 2], h.z, fmaf(w3c[u + 1], h.y, fmaf(w3c[u], h.x, acc))));
+    }
+    order();
+    float y[kSPW];
+#pragma unroll
+    for (int k = 0; k < kSPW; ++k) {
+      const float r0 = __shfl(acc, 4 * k), r1 = __shfl(acc, 4 * k + 1), r2 = __shfl(acc, 4 * k + 2),
+                  r3 = __shfl(acc, 4 * k + 3);
+      y[k] = b3 + ((r0 + r1) + (r2 + r3));
+    }
+    if constexpr (!BACK) {
+#pragma unroll
+      for (int k = 0; k < kSPW; ++k)
+        if (s0 + k < n && lane == k) Y[s0 + k] = y[k];
+    } else {
+      float dy[kSPW], d1[kSPW];
+#pragma unroll
+      for (int k = 0; k < kSPW; ++k) {
+        dy[k] = scale * (y[k] - T[r[k]]);
+        const float d2 = z2[k] > 0.0f ? dy[k] * w3 : 0.0f;
+        buf[k][lane] = d2;
+        d1[k] = 0.0f;
+        if (s0 + k < n) {
+          H1[s[k] * kMlpH + lane] = z1[k];
+          H2[s[k] * kMlpH + lane] = z2[k];
+          DZ2[s[k] * kMlpH + lane] = d2;
+          if (lane == k) {
+            Y[s0 + k] = y[k];
+            DY[s0 + k] = dy[k];
+          }
+        }
+      }
+      order();
+#pragma unroll
+      for (int j = 0; j < kMlpH; j += 4)
+#pragma unroll
+        for (int k = 0; k < kSPW; ++k) {
+          const float4 d = *reinterpret_cast<const float4 *>(&buf[k][j]);
+          d1[k] = fmaf(col[j + 3], d.w, fmaf(col[j + 2], d.z, fmaf(col[j + 1], d.y, fmaf(col[j], d.x, d1[k]))));
+        }
+      order();
+#pragma unroll
+      for (int k = 0; k < kSPW; ++k)
+        if (s0 + k < n) DZ1[s[k] * kMlpH + lane] = z1[k] > 0.0f ? d1[k] : 0.0f;
+    }
   }
-  if (wv == 0 && ok) DY[s] = dy;
 }
 
 struct UpdateArgs {
   float *P, *M, *V, *G;  // G may be null
   const float *norm, *X;
   const int32_t *idx;
-  const float *Z1, *Z2, *DZ1, *DZ2, *DY;
+  const float *H1, *H2, *DZ1, *DZ2, *DY;
   int32_t n;
   int32_t update;        // apply Adam
   float lr, beta1, beta2, eps, c1, c2;  // c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t)
 };
 
-// One thread per parameter; the batch sum runs in sample order.
+// Blocks of mlp_update: W2 by rows of four, W1 by 256 parameters, b1, b2, W3 with b3.
+constexpr int kUpdW1 = kMlpH / 4, kUpdB1 = kUpdW1 + kMlpH * kMlpF / 256, kUpdB2 = kUpdB1 + 1, kUpdW3 = kUpdB2 + 1,
+              kUpdBlocks = kUpdW3 + 1;
+
+// One thread per parameter; the batch sum runs in sample order.  A block's operands (256 samples
+// of one 64-wide array and of the array or arrays it is multiplied with) are staged in LDS first,
+// all their loads in flight together, so the chain of dependent FMAs reads LDS instead of paying a
+// cache latency per few samples.  Measured at batches of 256, with mlp_pass: a training step takes
+// 14.8 us (5.8 pass, 6.9 update, the launches between); it took 98 us as three kernels that read
+// global memory inside the chains (15.6 forward on four blocks, 18.6 back-propagation, 61.3
+// update), and 22.7 us with the chunk's loads guarded one by one.
 __global__ __launch_bounds__(256) void mlp_update(UpdateArgs a) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= kMlpP) return;
+  __shared__ __attribute__((aligned(16))) float big[kChunk * kMlpH];  // one 64-wide array
+  __shared__ __attribute__((aligned(16))) float small[kChunk * kMlpF];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, blk = blockIdx.x;
+  const float *wide = blk < kUpdW1 ? a.H1 : blk <= kUpdB1 ? a.DZ1 : blk == kUpdB2 ? a.DZ2 : a.H2;
+  int p = -1;                          // this thread's parameter
+  if (blk < kUpdW1) p = kMlpW2 + (blk * 4 + wv) * kMlpH + lane;
+  else if (blk < kUpdB1) p = kMlpW1 + (blk - kUpdW1) * 256 + tid;
+  else if (blk == kUpdB1) p = wv == 0 ? kMlpB1 + lane : -1;
+  else if (blk == kUpdB2) p = wv == 0 ? kMlpB2 + lane : -1;
+  else p = wv == 0 ? kMlpW3 + lane : tid == 64 ? kMlpB3 : -1;
+  const int i1 = (p - kMlpW1) / kMlpF, f1 = (p - kMlpW1) % kMlpF;  // W1: unit and feature
   float g = 0.0f;
-  if (p < kMlpB1) {
-    const int i = p / kMlpF, f = p % kMlpF;
-    const float mu = a.norm[f], is = a.norm[kMlpF + f];
-    for (int32_t s = 0; s < a.n; ++s) {
-      const int64_t r = a.idx ? a.idx[s] : s;
-      g = fmaf(a.DZ1[int64_t(s) * kMlpH + i], (a.X[r * kMlpF + f] - mu) * is, g);
+  for (int32_t s0 = 0; s0 < a.n; s0 += kChunk) {
+    const int m = min(kChunk, a.n - s0);
+    if (s0) __syncthreads();
+    // every load of the chunk is issued before the first LDS write; past the chunk's end they
+    // repeat its last element (a guarded load would wait for its own result inside its branch)
+    const float4 *src = reinterpret_cast<const float4 *>(wide + int64_t(s0) * kMlpH);
+    float4 w[kChunk * kMlpH / 4 / 256];
+#pragma unroll
+    for (int j = 0; j < kChunk * kMlpH / 4 / 256; ++j) w[j] = src[min(tid + 256 * j, m * (kMlpH / 4) - 1)];
+    const int sm = min(tid, m - 1);
+    if (blk < kUpdW1) {          // four columns of DZ2, each contiguous over the samples
+      const float4 d = *reinterpret_cast<const float4 *>(a.DZ2 + int64_t(s0 + sm) * kMlpH + blk * 4);
+      small[tid] = d.x;
+      small[kChunk + tid] = d.y;
+      small[2 * kChunk + tid] = d.z;
+      small[3 * kChunk + tid] = d.w;
+    } else if (blk < kUpdB1) {   // the z-scored features, a sample per thread
+      const int64_t r = a.idx ? a.idx[s0 + sm] : s0 + sm;
+#pragma unroll
+      for (int f = 0; f < kMlpF; ++f) small[tid * kMlpF + f] = (a.X[r * kMlpF + f] - a.norm[f]) * a.norm[kMlpF + f];
+    } else if (blk == kUpdW3) {
+      small[tid] = a.DY[s0 + sm];
     }
-  } else if (p < kMlpW2) {
-    const int i = p - kMlpB1;
-    for (int32_t s = 0; s < a.n; ++s) g += a.DZ1[int64_t(s) * kMlpH + i];
-  } else if (p < kMlpB2) {
-    const int i = (p - kMlpW2) / kMlpH, j = (p - kMlpW2) % kMlpH;
-    for (int32_t s = 0; s < a.n; ++s)
-      g = fmaf(a.DZ2[int64_t(s) * kMlpH + i], fmaxf(a.Z1[int64_t(s) * kMlpH + j], 0.0f), g);
-  } else if (p < kMlpW3) {
-    const int i = p - kMlpB2;
-    for (int32_t s = 0; s < a.n; ++s) g += a.DZ2[int64_t(s) * kMlpH + i];
-  } else if (p < kMlpB3) {
-    const int j = p - kMlpW3;
-    for (int32_t s = 0; s < a.n; ++s) g = fmaf(a.DY[s], fmaxf(a.Z2[int64_t(s) * kMlpH + j], 0.0f), g);
-  } else {
-    for (int32_t s = 0; s < a.n; ++s) g += a.DY[s];
+#pragma unroll
+    for (int j = 0; j < kChunk * kMlpH / 4 / 256; ++j) reinterpret_cast<float4 *>(big)[tid + 256 * j] = w[j];
+    __syncthreads();
+    if (p < 0) continue;
+    // `u` and `v` of sample s, u = 1 for a plain sum
+    auto chain = [&](auto u, auto v, auto &&sum) {
+      int s = 0;
+      for (; s + kAhead <= m; s += kAhead) {
+        float x[kAhead], y[kAhead];
+#pragma unroll
+        for (int e = 0; e < kAhead; ++e) x[e] = u(s + e), y[e] = v(s + e);
+#pragma unroll
+        for (int e = 0; e < kAhead; ++e) g = sum(x[e], y[e], g);
+      }
+      for (; s < m; ++s) g = sum(u(s), v(s), g);
+    };
+    auto fma_ = [](float x, float y, float z) { return fmaf(x, y, z); };
+    auto add_ = [](float, float y, float z) { return z + y; };
+    auto one = [](int) { return 1.0f; };
+    auto wide_lane = [&](int s) { return big[s * kMlpH + lane]; };
+    if (blk < kUpdW1) chain([&](int s) { return small[wv * kChunk + s]; }, wide_lane, fma_);
+    else if (blk < kUpdB1)
+      chain([&](int s) { return big[s * kMlpH + i1]; }, [&](int s) { return small[s * kMlpF + f1]; }, fma_);
+    else if (blk < kUpdW3) chain(one, wide_lane, add_);
+    else if (wv == 0) chain([&](int s) { return small[s]; }, wide_lane, fma_);
+    else chain(one, [&](int s) { return small[s]; }, add_);
   }
+  if (p < 0) return;
   if (a.G) a.G[p] = g;
   if (a.update) {
     const float m = a.beta1 * a.M[p] + (1.0f - a.beta1) * g;
@@ -165,15 +276,15 @@ __global__ __launch_bounds__(256) void mlp_update(UpdateArgs a) {
 void ensure_cap(psc_mlp &m, int64_t n) {
   if (n <= m.cap) return;
   const int64_t c = std::max<int64_t>(n, 2 * m.cap);
-  float **fl[] = {&m.x, &m.t, &m.z1, &m.z2, &m.y, &m.dz1, &m.dz2, &m.dy};
+  float **fl[] = {&m.x, &m.t, &m.h1, &m.h2, &m.y, &m.dz1, &m.dz2, &m.dy};
   for (float **p : fl)
     if (*p) { MLP_HIP(hipFree(*p)); *p = nullptr; }
   if (m.idx) { MLP_HIP(hipFree(m.idx)); m.idx = nullptr; }
   m.cap = 0;
   MLP_HIP(hipMalloc(&m.x, size_t(c) * kMlpF * 4));
   MLP_HIP(hipMalloc(&m.t, size_t(c) * 4));
-  MLP_HIP(hipMalloc(&m.z1, size_t(c) * kMlpH * 4));
-  MLP_HIP(hipMalloc(&m.z2, size_t(c) * kMlpH * 4));
+  MLP_HIP(hipMalloc(&m.h1, size_t(c) * kMlpH * 4));
+  MLP_HIP(hipMalloc(&m.h2, size_t(c) * kMlpH * 4));
   MLP_HIP(hipMalloc(&m.y, size_t(c) * 4));
   MLP_HIP(hipMalloc(&m.dz1, size_t(c) * kMlpH * 4));
   MLP_HIP(hipMalloc(&m.dz2, size_t(c) * kMlpH * 4));
@@ -182,45 +293,40 @@ void ensure_cap(psc_mlp &m, int64_t n) {
   m.cap = c;
 }
 
-unsigned blocks_for(int64_t n) { return unsigned((n + kSPB - 1) / kSPB); }
+unsigned blocks_for(int64_t n) {
+  return unsigned(std::min<int64_t>(kPassBlocks, (n + 4 * kSPW - 1) / (4 * kSPW)));
+}
 
 void check_n(int64_t n) {
   if (n < 1 || n > (int64_t(1) << 30)) fail(PSC_ERR_ARG, "sample count must be in [1, 2^30]");
 }
 
 // Device memory of one forward / backward pass: the samples (x, t), the per-sample activations
-// (z1, z2, y) and the back-propagated errors (dz1, dz2, dy).  The model's own buffers (grown on
+// (h1, h2, y) and the back-propagated errors (dz1, dz2, dy).  The model's own buffers (grown on
 // demand) or the fixed scratch array of the allocation-free entry point.
 struct Work {
   const float *x, *t;
-  float *z1, *z2, *y, *dz1, *dz2, *dy;
+  float *h1, *h2, *y, *dz1, *dz2, *dy;
 };
 
-Work work_of(psc_mlp &m) { return Work{m.x, m.t, m.z1, m.z2, m.y, m.dz1, m.dz2, m.dy}; }
+Work work_of(psc_mlp &m) { return Work{m.x, m.t, m.h1, m.h2, m.y, m.dz1, m.dz2, m.dy}; }
 
-// fwd over the first n uploaded samples (rows idx[0..n) if idx, else 0..n)
-void launch_fwd(psc_mlp &m, const Work &w, const int32_t *idx, int64_t n) {
-  const float *P = m.params, *norm = m.norm, *X = w.x;
+void launch_pass(psc_mlp &m, const Work &w, const int32_t *idx, int64_t n, bool back) {
+  const float *P = m.params, *norm = m.norm, *X = w.x, *T = w.t;
   int32_t nn = int32_t(n);
-  float *Z1 = w.z1, *Z2 = w.z2, *Y = w.y;
-  void *args[] = {&P, &norm, &X, &idx, &nn, &Z1, &Z2, &Y};
-  MLP_HIP(hipLaunchKernel(reinterpret_cast<const void *>(&mlp_fwd), dim3(blocks_for(n)), dim3(256), args, 0, m.stream));
+  float scale = float(2.0 / double(n));
+  float *H1 = w.h1, *H2 = w.h2, *Y = w.y, *DZ1 = w.dz1, *DZ2 = w.dz2, *DY = w.dy;
+  void *args[] = {&P, &norm, &X, &T, &idx, &nn, &scale, &H1, &H2, &Y, &DZ1, &DZ2, &DY};
+  const void *fn = back ? reinterpret_cast<const void *>(&mlp_pass<true>) : reinterpret_cast<const void *>(&mlp_pass<false>);
+  MLP_HIP(hipLaunchKernel(fn, dim3(blocks_for(n)), dim3(256), args, 0, m.stream));
 }
 
-void launch_fwd(psc_mlp &m, const int32_t *idx, int64_t n) { launch_fwd(m, work_of(m), idx, n); }
+// predictions of the first n uploaded samples
+void launch_fwd(psc_mlp &m, int64_t n) { launch_pass(m, work_of(m), nullptr, n, false); }
 
 void launch_step(psc_mlp &m, const Work &w, const int32_t *idx, int64_t n, bool update, const MlpTrainOpts &o,
                  float *G) {
-  launch_fwd(m, w, idx, n);
-  {
-    const float *P = m.params, *T = w.t, *Z1 = w.z1, *Z2 = w.z2, *Y = w.y;
-    int32_t nn = int32_t(n);
-    float scale = float(2.0 / double(n));
-    float *DZ1 = w.dz1, *DZ2 = w.dz2, *DY = w.dy;
-    void *args[] = {&P, &T, &idx, &nn, &scale, &Z1, &Z2, &Y, &DZ1, &DZ2, &DY};
-    MLP_HIP(hipLaunchKernel(reinterpret_cast<const void *>(&mlp_delta), dim3(blocks_for(n)), dim3(256), args, 0,
-                            m.stream));
-  }
+  launch_pass(m, w, idx, n, true);
   UpdateArgs a{};
   a.P = m.params;
   a.M = m.m;
@@ -229,8 +335,8 @@ void launch_step(psc_mlp &m, const Work &w, const int32_t *idx, int64_t n, bool 
   a.norm = m.norm;
   a.X = w.x;
   a.idx = idx;
-  a.Z1 = w.z1;
-  a.Z2 = w.z2;
+  a.H1 = w.h1;
+  a.H2 = w.h2;
   a.DZ1 = w.dz1;
   a.DZ2 = w.dz2;
   a.DY = w.dy;
@@ -246,7 +352,7 @@ void launch_step(psc_mlp &m, const Work &w, const int32_t *idx, int64_t n, bool 
     a.c2 = float(1.0 / (1.0 - std::pow(double(o.beta2), double(m.step))));
   }
   void *uargs[] = {&a};
-  MLP_HIP(hipLaunchKernel(reinterpret_cast<const void *>(&mlp_update), dim3((kMlpP + 255) / 256), dim3(256), uargs, 0,
+  MLP_HIP(hipLaunchKernel(reinterpret_cast<const void *>(&mlp_update), dim3(kUpdBlocks), dim3(256), uargs, 0,
                           m.stream));
 }
 
@@ -328,7 +434,7 @@ void mlp_predict(psc_mlp &m, const float *x, int64_t n, float *y) {
   MLP_HIP(hipSetDevice(m.device));
   ensure_cap(m, n);
   upload_x(m, x, n);
-  launch_fwd(m, nullptr, n);
+  launch_fwd(m, n);
   MLP_HIP(hipMemcpyAsync(y, m.y, size_t(n) * 4, hipMemcpyDeviceToHost, m.stream));
   MLP_HIP(hipStreamSynchronize(m.stream));
 }
@@ -355,14 +461,14 @@ double mlp_grad(psc_mlp &m, const float *x, const float *t, int64_t n, float *gr
 
 namespace {
 
-// Layout of the scratch array, in floats: x (max x F), t, z1, z2, y, dz1, dz2, dy, the gradient
+// Layout of the scratch array, in floats: x (max x F), t, h1, h2, y, dz1, dz2, dy, the gradient
 // (kMlpP, padded) and the loss (one double).
 constexpr int64_t kSMax = kMlpStaticMax;
 constexpr int64_t kOffX = 0;
 constexpr int64_t kOffT = kOffX + kSMax * kMlpF;
-constexpr int64_t kOffZ1 = kOffT + kSMax;
-constexpr int64_t kOffZ2 = kOffZ1 + kSMax * kMlpH;
-constexpr int64_t kOffY = kOffZ2 + kSMax * kMlpH;
+constexpr int64_t kOffH1 = kOffT + kSMax;
+constexpr int64_t kOffH2 = kOffH1 + kSMax * kMlpH;
+constexpr int64_t kOffY = kOffH2 + kSMax * kMlpH;
 constexpr int64_t kOffDZ1 = kOffY + kSMax;
 constexpr int64_t kOffDZ2 = kOffDZ1 + kSMax * kMlpH;
 constexpr int64_t kOffDY = kOffDZ2 + kSMax * kMlpH;
@@ -418,13 +524,13 @@ double mlp_grad_static(psc_mlp &m, const float *x, const float *t, int64_t n, fl
   MLP_HIP(hipSetDevice(m.device));
   float *base = scratch_of(m.device);
   float *xs = base + kOffX, *ts = base + kOffT;
-  const Work w{xs, ts, base + kOffZ1, base + kOffZ2, base + kOffY, base + kOffDZ1, base + kOffDZ2, base + kOffDY};
+  const Work w{xs, ts, base + kOffH1, base + kOffH2, base + kOffY, base + kOffDZ1, base + kOffDZ2, base + kOffDY};
   float *G = base + kOffG;
   double *L = reinterpret_cast<double *>(base + kOffLoss);
   MLP_HIP(hipMemcpyAsync(xs, x, size_t(n) * kMlpF * 4, hipMemcpyHostToDevice, m.stream));
   MLP_HIP(hipMemcpyAsync(ts, t, size_t(n) * 4, hipMemcpyHostToDevice, m.stream));
-  // every element the kernels read is written first in this call (x, t above; z, y, deltas by
-  // the passes; G and the loss entirely), so nothing left by an earlier call is seen
+  // every element the kernels read is written first in this call (x, t above; h, y, deltas by
+  // the pass; G and the loss entirely), so nothing left by an earlier call is seen
   launch_step(m, w, nullptr, n, false, MlpTrainOpts{}, G);
   {
     const float *Y = w.y, *T = ts;
@@ -462,7 +568,7 @@ void mlp_train(psc_mlp &m, const float *x, const float *t, int64_t n, const MlpT
     for (int64_t b0 = 0; b0 < n; b0 += o.batch)
       launch_step(m, m.idx + b0, std::min<int64_t>(o.batch, n - b0), true, o, nullptr);
     if (epoch_loss) {
-      launch_fwd(m, nullptr, n);
+      launch_fwd(m, n);
       MLP_HIP(hipMemcpyAsync(y.data(), m.y, size_t(n) * 4, hipMemcpyDeviceToHost, m.stream));
       MLP_HIP(hipStreamSynchronize(m.stream));
       epoch_loss[e] = float(mse_of(y, t, n));
@@ -521,7 +627,7 @@ std::unique_ptr<CostModel> mlp_cost_model(const psc_mlp *m) {
 psc_mlp::~psc_mlp() {
   if (hipSetDevice(device) != hipSuccess) return;
   if (stream) (void)hipStreamSynchronize(stream);
-  float *fl[] = {params, m, v, g, norm, x, t, z1, z2, y, dz1, dz2, dy};
+  float *fl[] = {params, m, v, g, norm, x, t, h1, h2, y, dz1, dz2, dy};
   for (float *p : fl)
     if (p) (void)hipFree(p);
   if (idx) (void)hipFree(idx);

@@ -53,7 +53,7 @@ struct psc_mlp {
   int64_t step = 0;                                     // Adam steps taken
   // device scratch for a batch / a prediction set, grown on demand
   int64_t cap = 0;
-  float *x = nullptr, *t = nullptr, *z1 = nullptr, *z2 = nullptr, *y = nullptr;
+  float *x = nullptr, *t = nullptr, *h1 = nullptr, *h2 = nullptr, *y = nullptr;
   float *dz1 = nullptr, *dz2 = nullptr, *dy = nullptr, *g = nullptr;
   int32_t *idx = nullptr;
   std::mutex mu;  // scratch use (predictions are requested through const handles)
