@@ -53,34 +53,34 @@ std::vector<std::array<int, 6>> tile_cache_entries() {
 // ---------------------------------------------------------------------------------------------
 // Standalone kernels: one tile function call per 256-thread block.
 // ---------------------------------------------------------------------------------------------
-template <int BM, int BN, int BK, int WM, int WN, bool VEC, bool OUT_BF16>
+template <int BM, int BN, int BK, int WM, int WN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_f32_smem<BM, BN, BK>()];
-  gemm_f32_tile<BM, BN, BK, WM, WN, VEC, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  gemm_f32_tile<BM, BN, BK, WM, WN, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
 }
 
-template <int BM, int BN, int BK, int WM, int WN, bool VEC, bool OUT_BF16>
+template <int BM, int BN, int BK, int WM, int WN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_bf16_smem<BM, BN, BK>()];
-  gemm_bf16_tile<BM, BN, BK, WM, WN, VEC, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  gemm_bf16_tile<BM, BN, BK, WM, WN, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
 }
 
-template <int TM, int TN, bool VEC, bool OUT_BF16>
+template <int TM, int TN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_f32_splitk_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_f32_splitk_smem<TM, TN>()];
-  gemm_f32_splitk_tile<TM, TN, VEC, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  gemm_f32_splitk_tile<TM, TN, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
 }
 
-template <int TM, int TN, bool VEC, bool OUT_BF16>
+template <int TM, int TN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_bf16_splitk_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_bf16_splitk_smem<TM, TN>()];
-  gemm_bf16_splitk_tile<TM, TN, VEC, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  gemm_bf16_splitk_tile<TM, TN, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
 }
 
-template <int TM, int TN, int D, bool VEC, bool OUT_BF16>
+template <int TM, int TN, int D, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_bf16_deep_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_bf16_deep_smem<TM, TN, D>()];
-  gemm_bf16_deep_tile<TM, TN, D, VEC, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  gemm_bf16_deep_tile<TM, TN, D, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
 }
 
 template <bool OUT_BF16>
@@ -96,28 +96,22 @@ __global__ __launch_bounds__(128 * WN) void gemm_bf16_w4_kernel(GemmArgs p) {
   gemm_bf16_w4_tile<WN, OUT_BF16>(p, group_tile(xcd_tile(blockIdx.x, gridDim.x), gridDim.x / p.tiles_n, p.tiles_n, 4), smem);
 }
 
-template <int FN, bool VEC, bool OUT_BF16>
+template <int FN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_direct_smem<FN, false>()];
-  gemm_direct_tile<FN, false, VEC, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  gemm_direct_tile<FN, false, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
 }
 
-template <int FN, bool VEC, bool OUT_BF16>
+template <int FN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_bf16_direct_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_direct_smem<FN, true>()];
-  gemm_direct_tile<FN, true, VEC, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  gemm_direct_tile<FN, true, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
 }
 
-template <int NV, bool VEC, bool IN_BF16, bool OUT_BF16, bool NT = false, int CW = 4>
+template <int NV, bool IN_BF16, bool OUT_BF16, bool NT = false, int CW = 4>
 __global__ __launch_bounds__(256) void softmax_kernel(SoftmaxArgs p) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row < p.R) softmax_row<NV, VEC, IN_BF16, OUT_BF16, NT, CW>(p, row);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_kernel(TransArgs p) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[64 * 65 * sizeof(T)];
-  transpose_tile<T>(p, blockIdx.x, smem);
+  if (row < p.R) softmax_row<NV, IN_BF16, OUT_BF16, NT, CW>(p, row);
 }
 
 template <typename T, bool NT>
@@ -130,11 +124,6 @@ template <typename T, int TR, int TC, bool NT>
 __global__ __launch_bounds__(256) void transpose_rc_kernel(TransArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[transpose_rc_smem<TR, TC, T>()];
   transpose_rc_tile<T, TR, TC, NT>(p, blockIdx.x, smem);
-}
-
-template <bool IN_BF16, bool OUT_BF16>
-__global__ __launch_bounds__(256) void add_kernel(AddArgs p) {
-  add_block<IN_BF16, OUT_BF16>(p, blockIdx.x);
 }
 
 template <bool IN_BF16, bool OUT_BF16, bool NT = false>
@@ -180,11 +169,10 @@ constexpr TileCfg kTiles[] = {{0, 0, false},     {128, 128, false}, {64, 64, fal
                               {256, 256, false}, {256, 256, false}};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
-#define PSC_VO(KERNEL, ...)                                                                     \
-  (vec ? (obf ? (const void *)&KERNEL<__VA_ARGS__, true, true> : (const void *)&KERNEL<__VA_ARGS__, true, false>) \
-       : (obf ? (const void *)&KERNEL<__VA_ARGS__, false, true> : (const void *)&KERNEL<__VA_ARGS__, false, false>))
+#define PSC_VO(KERNEL, ...) \
+  (obf ? (const void *)&KERNEL<__VA_ARGS__, true> : (const void *)&KERNEL<__VA_ARGS__, false>)
 
-const void *gemm_fn(int ab_dtype, int tile, bool vec, bool obf) {
+const void *gemm_fn(int ab_dtype, int tile, bool obf) {
   if (ab_dtype == 0) {
     switch (tile) {
       case 1: return PSC_VO(gemm_f32_kernel, 128, 128, 16, 64, 64);
@@ -314,10 +302,7 @@ bool make_gemm(Launch &L, GemmArgs a, int ab_dtype, int c_dtype, int tile) {
   a.tiles_n = (a.N + bn - 1) / bn;
   const int tiles_m = (a.M + bm - 1) / bm;
   const bool obf = c_dtype == 1;
-  const bool vec = ab_dtype == 0
-                       ? (aligned16(a.A) && aligned16(a.B) && a.lda % 4 == 0 && a.ldb % 4 == 0)
-                       : (aligned16(a.A) && aligned16(a.B) && a.lda % 8 == 0 && a.ldb % 8 == 0);
-  const void *fn = gemm_fn(ab_dtype, tile, vec, obf);
+  const void *fn = gemm_fn(ab_dtype, tile, obf);
   if (!fn) return false;
   L.func = fn;
   L.grid = dim3(unsigned(int64_t(tiles_m) * a.tiles_n), 1, 1);
@@ -331,38 +316,26 @@ bool make_gemm(Launch &L, GemmArgs a, int ab_dtype, int c_dtype, int tile) {
 
 bool make_softmax(Launch &L, SoftmaxArgs a, int in_dtype, int out_dtype) {
   const bool ib = in_dtype == 1, ob = out_dtype == 1;
-  const int in_align = ib ? 8 : 16, out_align = ob ? 8 : 16;
-  const bool vec = (reinterpret_cast<uintptr_t>(a.X) % in_align == 0) &&
-                   (reinterpret_cast<uintptr_t>(a.Y) % out_align == 0) && a.ldx % 4 == 0 && a.ldy % 4 == 0;
   int nv = 0;
   if (a.C <= 256) nv = 1;
   else if (a.C <= 512) nv = 2;
   else if (a.C <= 1024) nv = 4;
   else if (a.C <= 2048) nv = 8;
-  const bool nt = vec && nv > 0 && int64_t(a.R) * a.C * (ob ? 2 : 4) >= kStreamBytes;
-  // bf16 input in 16-byte chunks of eight where both operands allow it
-  const bool w16 = vec && ib && nv >= 2 && aligned16(a.X) && aligned16(a.Y) && a.ldx % 8 == 0 && a.ldy % 8 == 0;
-#define PSC_SMB(NV, NT, W)                                                                          \
-  (w16 ? (ob ? (const void *)&softmax_kernel<NV, true, true, true, NT, W> : (const void *)&softmax_kernel<NV, true, true, false, NT, W>) \
-       : (ob ? (const void *)&softmax_kernel<NV, true, true, true, NT> : (const void *)&softmax_kernel<NV, true, true, false, NT>))
-#define PSC_SM4(NV, NT, W)                                                                          \
-  (ib ? PSC_SMB(NV, NT, W)                                                                          \
-      : (ob ? (const void *)&softmax_kernel<NV, true, false, true, NT> : (const void *)&softmax_kernel<NV, true, false, false, NT>))
-#define PSC_SMS(NV)                                                                                 \
-  (ib ? (ob ? (const void *)&softmax_kernel<NV, false, true, true> : (const void *)&softmax_kernel<NV, false, true, false>) \
-      : (ob ? (const void *)&softmax_kernel<NV, false, false, true> : (const void *)&softmax_kernel<NV, false, false, false>))
-#define PSC_SM(NV, W) (vec ? (nt ? PSC_SM4(NV, true, W) : PSC_SM4(NV, false, W)) : PSC_SMS(NV))
+  const bool nt = nv > 0 && int64_t(a.R) * a.C * (ob ? 2 : 4) >= kStreamBytes;
+// (NV register quads per lane, streaming hint, chunk width of bf16 input)
+#define PSC_SMS(NV, NT, W)                                                                          \
+  (ib ? (ob ? (const void *)&softmax_kernel<NV, true, true, NT, W> : (const void *)&softmax_kernel<NV, true, false, NT, W>) \
+      : (ob ? (const void *)&softmax_kernel<NV, false, true, NT> : (const void *)&softmax_kernel<NV, false, false, NT>))
+#define PSC_SM(NV, W) (nt ? PSC_SMS(NV, true, W) : PSC_SMS(NV, false, W))
   switch (nv) {
     case 1: L.func = PSC_SM(1, 4); break;   // (no eight-wide chunks for rows of at most 256)
     case 2: L.func = PSC_SM(2, 8); break;
     case 4: L.func = PSC_SM(4, 8); break;
     case 8: L.func = PSC_SM(8, 8); break;
-    default: L.func = PSC_SMS(0); break;
+    default: L.func = PSC_SMS(0, false, 4); break;
   }
 #undef PSC_SM
 #undef PSC_SMS
-#undef PSC_SM4
-#undef PSC_SMB
   L.grid = dim3(unsigned((a.R + 3) / 4), 1, 1);
   L.block = dim3(256, 1, 1);
   L.shmem = 0;
@@ -373,24 +346,18 @@ bool make_softmax(Launch &L, SoftmaxArgs a, int in_dtype, int out_dtype) {
 
 #define PSC_TRC(T, TR, TC) (nt ? (const void *)&transpose_rc_kernel<T, TR, TC, true> : (const void *)&transpose_rc_kernel<T, TR, TC, false>)
 
-// tile: 1 64 x 64, 2 64 x 128, 3 128 x 64, 4 64 x 256 (rows x columns of the input); the
-// rectangular tiles need aligned operands (else 64 x 64).  Automatic (0): 64 x 256 for streaming
+// tile: 1 64 x 64, 2 64 x 128, 3 128 x 64, 4 64 x 256 (rows x columns of the input).  Automatic (0): 64 x 256 for streaming
 // sizes, 64 x 64 otherwise.  Measured on a 16384^2 transpose with streaming hints (HBM fraction,
 // FP32 / BF16): 64 x 256 70.2-70.5% / 71.2-72.1%; 128 x 256 (BF16) 71.2%; 64 x 128 66.9% / 67.9%;
 // 64 x 64 65.4% / 67.1%; 128 x 128 66.3% / 68.2%; 32 x 256 68.7-68.9% / 52.5%; 64 x 512 (BF16)
 // 68.3%; without the hints every shape 1.5-4 points lower.
 bool make_transpose(Launch &L, TransArgs a, int dtype, int tile) {
-  const int64_t v = dtype == 1 ? 8 : 4;  // elements per 16-byte vector
-  const bool vec = aligned16(a.A) && aligned16(a.B) && a.lda % v == 0 && a.ldb % v == 0;
   const bool nt = int64_t(a.R) * a.C * (dtype == 1 ? 2 : 4) >= kStreamBytes;
   if (tile < 1 || tile > 4) tile = nt ? 4 : 1;
-  if (!vec) tile = 1;
   int tr = 64, tcl = 64;
-  if (tile == 1 && vec)
+  if (tile == 1)
     L.func = dtype == 1 ? (nt ? (const void *)&transpose_vec_kernel<uint16_t, true> : (const void *)&transpose_vec_kernel<uint16_t, false>)
                         : (nt ? (const void *)&transpose_vec_kernel<float, true> : (const void *)&transpose_vec_kernel<float, false>);
-  else if (tile == 1)
-    L.func = dtype == 1 ? (const void *)&transpose_kernel<uint16_t> : (const void *)&transpose_kernel<float>;
   else if (tile == 2)
     L.func = dtype == 1 ? PSC_TRC(uint16_t, 64, 128) : PSC_TRC(float, 64, 128), tcl = 128;
   else if (tile == 4)
@@ -408,18 +375,10 @@ bool make_transpose(Launch &L, TransArgs a, int dtype, int tile) {
 
 bool make_add(Launch &L, AddArgs a, int in_dtype, int out_dtype) {
   const bool ib = in_dtype == 1, ob = out_dtype == 1;
-  const bool vec = aligned16(a.A) && aligned16(a.B) && aligned16(a.Cp) && a.lda % 8 == 0 && a.ldb % 8 == 0 &&
-                   a.ldc % 8 == 0;
-  if (vec) {
-    // plain loads and stores: streaming hints measured slower for the two-input add
-    L.func = ib ? (ob ? (const void *)&add_vec_kernel<true, true> : (const void *)&add_vec_kernel<true, false>)
-                : (ob ? (const void *)&add_vec_kernel<false, true> : (const void *)&add_vec_kernel<false, false>);
-    L.grid = dim3(unsigned(int64_t((a.C + 2047) / 2048) * a.R), 1, 1);
-  } else {
-    L.func = ib ? (ob ? (const void *)&add_kernel<true, true> : (const void *)&add_kernel<true, false>)
-                : (ob ? (const void *)&add_kernel<false, true> : (const void *)&add_kernel<false, false>);
-    L.grid = dim3(unsigned(int64_t((a.C + 255) / 256) * a.R), 1, 1);
-  }
+  // plain loads and stores: streaming hints measured slower for the two-input add
+  L.func = ib ? (ob ? (const void *)&add_vec_kernel<true, true> : (const void *)&add_vec_kernel<true, false>)
+              : (ob ? (const void *)&add_vec_kernel<false, true> : (const void *)&add_vec_kernel<false, false>);
+  L.grid = dim3(unsigned(int64_t((a.C + 2047) / 2048) * a.R), 1, 1);
   L.block = dim3(256, 1, 1);
   L.shmem = 0;
   L.empty = a.R == 0 || a.C == 0;

@@ -32,28 +32,21 @@ namespace {
 
 constexpr uint64_t kExit = ~uint64_t(0);
 
-template <int NV, bool VEC, bool IN_BF16, bool OUT_BF16>
+template <int NV, bool IN_BF16, bool OUT_BF16>
 __device__ __forceinline__ void softmax_task(const SoftmaxArgs &p, int tile) {
   const int wave = threadIdx.x >> 6;
 #pragma unroll 1
   for (int j = 0; j < 4; ++j) {
     const int row = tile * 16 + j * 4 + wave;
-    if (row < p.R) softmax_row<NV, VEC, IN_BF16, OUT_BF16>(p, row);
+    if (row < p.R) softmax_row<NV, IN_BF16, OUT_BF16>(p, row);
   }
 }
 
 template <bool IN_BF16, bool OUT_BF16>
 __device__ __forceinline__ void add_task(const AddArgs &p, int tile) {
+  const int nbx = (p.C + 2047) / 2048;  // column chunks of a row
 #pragma unroll 1
-  for (int rr = 0; rr < 8; ++rr) {
-    const int r = tile * 8 + rr;
-    if (r >= p.R) break;
-    for (int c = threadIdx.x; c < p.C; c += 256) {
-      const float a = load_elem<IN_BF16>(p.A, int64_t(r) * p.lda + c);
-      const float b = load_elem<IN_BF16>(p.B, int64_t(r) * p.ldb + c);
-      store_elem<OUT_BF16>(p.Cp, int64_t(r) * p.ldc + c, a + b);
-    }
-  }
+  for (int j = 0; j < 8 * nbx; ++j) add_block_vec<IN_BF16, OUT_BF16>(p, tile * 8 * nbx + j);
 }
 
 // Copies rows [tile rpt, (tile + 1) rpt) of a host copy, the region taken as units of 16 bytes
@@ -138,70 +131,46 @@ __device__ __forceinline__ bool run_task(const ExecNode *ndp, int tile, unsigned
   const ExecNode &nd = *ndp;
   const int v = __builtin_amdgcn_readfirstlane(nd.variant);
   switch (v) {
-    PSC_TASK(110, gemm_f32_tile<64, 64, 16, 32, 32, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(111, gemm_f32_tile<64, 64, 16, 32, 32, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(114, gemm_f32_tile<32, 32, 32, 16, 16, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(115, gemm_f32_tile<32, 32, 32, 16, 16, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(138, gemm_f32_splitk_tile<32, 32, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(139, gemm_f32_splitk_tile<32, 32, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(142, gemm_f32_splitk_tile<16, 32, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(143, gemm_f32_splitk_tile<16, 32, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(148, gemm_f32_splitk_tile<16, 16, false, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(149, gemm_f32_splitk_tile<16, 16, false, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(150, gemm_f32_splitk_tile<16, 16, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(151, gemm_f32_splitk_tile<16, 16, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(152, gemm_direct_tile<1, false, false, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(153, gemm_direct_tile<1, false, false, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(154, gemm_direct_tile<1, false, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(155, gemm_direct_tile<1, false, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(158, gemm_direct_tile<2, false, true, false, 8>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(159, gemm_direct_tile<2, false, true, true, 8>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(162, gemm_direct_tile<4, false, true, false, 8>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(163, gemm_direct_tile<4, false, true, true, 8>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(210, gemm_bf16_tile<64, 64, 64, 32, 32, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(211, gemm_bf16_tile<64, 64, 64, 32, 32, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(266, gemm_bf16_splitk_tile<64, 64, true, false, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(267, gemm_bf16_splitk_tile<64, 64, true, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(214, gemm_bf16_tile<32, 32, 64, 16, 16, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(215, gemm_bf16_tile<32, 32, 64, 16, 16, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(238, gemm_bf16_splitk_tile<32, 32, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(239, gemm_bf16_splitk_tile<32, 32, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(242, gemm_bf16_splitk_tile<16, 32, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(243, gemm_bf16_splitk_tile<16, 32, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(248, gemm_bf16_splitk_tile<16, 16, false, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(249, gemm_bf16_splitk_tile<16, 16, false, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(250, gemm_bf16_splitk_tile<16, 16, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(252, gemm_direct_tile<1, true, false, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(253, gemm_direct_tile<1, true, false, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(254, gemm_direct_tile<1, true, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(255, gemm_direct_tile<1, true, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(258, gemm_direct_tile<2, true, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(259, gemm_direct_tile<2, true, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(262, gemm_direct_tile<4, true, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(263, gemm_direct_tile<4, true, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(251, gemm_bf16_splitk_tile<16, 16, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(300, softmax_task<0, false, false, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(301, softmax_task<0, false, false, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(302, softmax_task<0, false, true, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(303, softmax_task<0, false, true, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(312, softmax_task<1, true, false, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(313, softmax_task<1, true, false, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(314, softmax_task<1, true, true, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(315, softmax_task<1, true, true, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(320, softmax_task<2, true, false, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(321, softmax_task<2, true, false, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(322, softmax_task<2, true, true, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(323, softmax_task<2, true, true, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(328, softmax_task<4, true, false, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(329, softmax_task<4, true, false, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(330, softmax_task<4, true, true, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(331, softmax_task<4, true, true, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(336, softmax_task<8, true, false, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(337, softmax_task<8, true, false, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(338, softmax_task<8, true, true, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(339, softmax_task<8, true, true, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
-    PSC_TASK(400, transpose_tile<float>(uniform_load<TransArgs>(nd.args), tile, smem));
-    PSC_TASK(401, transpose_tile<uint16_t>(uniform_load<TransArgs>(nd.args), tile, smem));
+    PSC_TASK(110, gemm_f32_tile<64, 64, 16, 32, 32, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(111, gemm_f32_tile<64, 64, 16, 32, 32, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(154, gemm_direct_tile<1, false, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(155, gemm_direct_tile<1, false, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(158, gemm_direct_tile<2, false, false, 8>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(159, gemm_direct_tile<2, false, true, 8>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(162, gemm_direct_tile<4, false, false, 8>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(163, gemm_direct_tile<4, false, true, 8>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(210, gemm_bf16_tile<64, 64, 64, 32, 32, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(211, gemm_bf16_tile<64, 64, 64, 32, 32, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(266, gemm_bf16_splitk_tile<64, 64, false, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(267, gemm_bf16_splitk_tile<64, 64, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(254, gemm_direct_tile<1, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(255, gemm_direct_tile<1, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(258, gemm_direct_tile<2, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(259, gemm_direct_tile<2, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(262, gemm_direct_tile<4, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(263, gemm_direct_tile<4, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(300, softmax_task<0, false, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(301, softmax_task<0, false, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(302, softmax_task<0, true, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(303, softmax_task<0, true, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(312, softmax_task<1, false, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(313, softmax_task<1, false, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(314, softmax_task<1, true, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(315, softmax_task<1, true, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(320, softmax_task<2, false, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(321, softmax_task<2, false, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(322, softmax_task<2, true, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(323, softmax_task<2, true, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(328, softmax_task<4, false, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(329, softmax_task<4, false, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(330, softmax_task<4, true, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(331, softmax_task<4, true, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(336, softmax_task<8, false, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(337, softmax_task<8, false, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(338, softmax_task<8, true, false>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(339, softmax_task<8, true, true>(uniform_load<SoftmaxArgs>(nd.args), tile));
+    PSC_TASK(400, transpose_tile_vec<float>(uniform_load<TransArgs>(nd.args), tile, smem));
+    PSC_TASK(401, transpose_tile_vec<uint16_t>(uniform_load<TransArgs>(nd.args), tile, smem));
     PSC_TASK(420, copy_task(uniform_load<CopyArgs>(nd.args), tile));
     PSC_TASK(410, add_task<false, false>(uniform_load<AddArgs>(nd.args), tile));
     PSC_TASK(411, add_task<false, true>(uniform_load<AddArgs>(nd.args), tile));
@@ -343,10 +312,7 @@ const void *exec_fn(int i) { return instance_fn(i, std::make_integer_sequence<in
 struct PCfg {
   int cfg, bm, bn;
 };
-constexpr PCfg kPersistentGemm[] = {{2, 64, 64},  {3, 32, 32},  {9, 32, 32}, {10, 16, 32}, {16, 64, 64},
-                                    {12, 16, 16}, {13, 16, 16}, {14, 16, 32}, {15, 16, 64}};
-
-bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+constexpr PCfg kPersistentGemm[] = {{2, 64, 64}, {16, 64, 64}, {13, 16, 16}, {14, 16, 32}, {15, 16, 64}};
 
 }  // namespace
 
@@ -357,8 +323,6 @@ ExecNode make_exec_node(int kind, const unsigned char *args, int in_dtype, int o
       GemmArgs g;
       memcpy(&g, args, sizeof(g));
       if (g.M == 0 || g.N == 0) break;
-      const bool vec = in_dtype == 0 ? (aligned16(g.A) && aligned16(g.B) && g.lda % 4 == 0 && g.ldb % 4 == 0)
-                                     : (aligned16(g.A) && aligned16(g.B) && g.lda % 8 == 0 && g.ldb % 8 == 0);
       // The executor's own tile choice: its parallelism comes from kernels running side by side,
       // so a task should carry more work than the standalone kernels' small tiles (made to fill
       // the GPU with one kernel).  `want` is the number of workgroups this kernel can expect:
@@ -376,25 +340,21 @@ ExecNode make_exec_node(int kind, const unsigned char *args, int in_dtype, int o
       // for K = 1024 against four.  (`tile`, the standalone choice, is unused.)
       (void)tile;
       int cfg = -1;
-      if (!vec) {
-        cfg = in_dtype == 0 ? 13 : 12;
-      } else {
-        static constexpr int c0[] = {2, 15, 14, 13};
-        constexpr int nc = sizeof(c0) / sizeof(c0[0]);
-        for (int i = 0; i < nc && cfg < 0; ++i) {
-          int bm = 16, bn = 16;
-          for (const PCfg &c : kPersistentGemm)
-            if (c.cfg == c0[i]) { bm = c.bm; bn = c.bn; }
-          const int64_t tiles = int64_t((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
-          if (tiles >= want || i == nc - 1) cfg = c0[i];
-        }
-        if (cfg == 2 && in_dtype == 1 && g.K >= 256) cfg = 16;
+      static constexpr int c0[] = {2, 15, 14, 13};
+      constexpr int nc = sizeof(c0) / sizeof(c0[0]);
+      for (int i = 0; i < nc && cfg < 0; ++i) {
+        int bm = 16, bn = 16;
+        for (const PCfg &c : kPersistentGemm)
+          if (c.cfg == c0[i]) { bm = c.bm; bn = c.bn; }
+        const int64_t tiles = int64_t((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
+        if (tiles >= want || i == nc - 1) cfg = c0[i];
       }
+      if (cfg == 2 && in_dtype == 1 && g.K >= 256) cfg = 16;
       int bm = 16, bn = 16;
       for (const PCfg &c : kPersistentGemm)
         if (c.cfg == cfg) { bm = c.bm; bn = c.bn; }
       g.tiles_n = (g.N + bn - 1) / bn;
-      n.variant = 100 + in_dtype * 100 + cfg * 4 + (vec ? 2 : 0) + (out_dtype == 1 ? 1 : 0);
+      n.variant = 100 + in_dtype * 100 + cfg * 4 + 2 + (out_dtype == 1 ? 1 : 0);
       n.n_tiles = ((g.M + bm - 1) / bm) * g.tiles_n;
       n.tile_m = bm;
       n.tile_n = bn;
@@ -405,11 +365,7 @@ ExecNode make_exec_node(int kind, const unsigned char *args, int in_dtype, int o
       SoftmaxArgs sa;
       memcpy(&sa, args, sizeof(sa));
       if (sa.R == 0 || sa.C == 0) break;
-      const int ia = in_dtype ? 8 : 16, oa = out_dtype ? 8 : 16;
-      const bool vec = (reinterpret_cast<uintptr_t>(sa.X) % ia == 0) && (reinterpret_cast<uintptr_t>(sa.Y) % oa == 0) &&
-                       sa.ldx % 4 == 0 && sa.ldy % 4 == 0;
-      int code = 0;
-      if (vec) code = sa.C <= 256 ? 1 : sa.C <= 512 ? 2 : sa.C <= 1024 ? 3 : sa.C <= 2048 ? 4 : 0;
+      const int code = sa.C <= 256 ? 1 : sa.C <= 512 ? 2 : sa.C <= 1024 ? 3 : sa.C <= 2048 ? 4 : 0;
       n.variant = 300 + code * 8 + (code ? 4 : 0) + in_dtype * 2 + out_dtype;
       n.n_tiles = (sa.R + 15) / 16;
       n.tile_m = 16;

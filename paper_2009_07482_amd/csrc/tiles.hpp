@@ -23,28 +23,63 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// 16- and 8-byte global loads and stores.  NT: with the non-temporal (streaming) hint, for
-// operands far larger than the last-level cache, which are read or written once and would only
-// evict data still to be used.
-template <bool NT>
+// 16- and 8-byte global loads and stores at any element alignment: gfx950's global memory
+// instructions take addresses of any alignment, so rows whose pitch or start is no multiple of 16
+// bytes (odd matrix sizes, windows) are read with the same wide accesses as aligned ones, at the
+// cost of one more cache line where a wavefront's run of addresses crosses one.  Read element by
+// element, as they were before, a batch of sixteen attention DAGs of odd lengths (BF16, 1,824
+// kernels) took 6.77 ms; it takes 3.70 ms.  NT: with the non-temporal (streaming) hint, for operands far larger than the last-level
+// cache, which are read or written once and would only evict data still to be used.
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+template <bool NT = false>
 __device__ __forceinline__ u32x4 load16(const void *src) {
-  if constexpr (NT) return __builtin_nontemporal_load(static_cast<const u32x4 *>(src));
-  else return *static_cast<const u32x4 *>(src);
+  if constexpr (NT) return __builtin_nontemporal_load(static_cast<const u32x4_any *>(src));
+  else return *static_cast<const u32x4_any *>(src);
 }
-template <bool NT>
+template <bool NT = false>
 __device__ __forceinline__ u32x2 load8(const void *src) {
-  if constexpr (NT) return __builtin_nontemporal_load(static_cast<const u32x2 *>(src));
-  else return *static_cast<const u32x2 *>(src);
+  if constexpr (NT) return __builtin_nontemporal_load(static_cast<const u32x2_any *>(src));
+  else return *static_cast<const u32x2_any *>(src);
 }
-template <bool NT>
+template <bool NT = false>
 __device__ __forceinline__ void store16(void *dst, u32x4 w) {
-  if constexpr (NT) __builtin_nontemporal_store(w, static_cast<u32x4 *>(dst));
-  else *static_cast<u32x4 *>(dst) = w;
+  if constexpr (NT) __builtin_nontemporal_store(w, static_cast<u32x4_any *>(dst));
+  else *static_cast<u32x4_any *>(dst) = w;
 }
-template <bool NT>
+template <bool NT = false>
 __device__ __forceinline__ void store8(void *dst, u32x2 w) {
-  if constexpr (NT) __builtin_nontemporal_store(w, static_cast<u32x2 *>(dst));
-  else *static_cast<u32x2 *>(dst) = w;
+  if constexpr (NT) __builtin_nontemporal_store(w, static_cast<u32x2_any *>(dst));
+  else *static_cast<u32x2_any *>(dst) = w;
+}
+template <typename V>
+__device__ __forceinline__ V load_as(const void *src) {
+  static_assert(sizeof(V) == 16 || sizeof(V) == 8, "a 16- or 8-byte vector");
+  V v;
+  if constexpr (sizeof(V) == 16) {
+    const u32x4 w = load16(src);
+    memcpy(&v, &w, 16);
+  } else {
+    const u32x2 w = load8(src);
+    memcpy(&v, &w, 8);
+  }
+  return v;
+}
+
+// Element e of the result is element e + bits / element size of `v` (bits < 128; zeros past its
+// end): the vector at a column that a load started `bits` earlier.
+template <typename V>
+__device__ __forceinline__ V shift_down(V v, int bits) {
+  static_assert(sizeof(V) == 16, "a 16-byte vector");
+  uint64_t w[2];
+  memcpy(w, &v, 16);
+  const int b = bits & 63;
+  const uint64_t up = (w[1] << 1) << (63 - b);  // w[1] << (64 - b), 0 for b = 0
+  const uint64_t lo = bits >= 64 ? w[1] >> b : (w[0] >> b) | up;
+  w[1] = bits >= 64 ? 0 : w[1] >> b;
+  w[0] = lo;
+  memcpy(&v, w, 16);
+  return v;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -104,13 +139,23 @@ __device__ __forceinline__ int group_tile(int t, int tiles_m, int tiles_n, int G
 //   v_mfma_f32_16x16x4_f32:   A: row l%16, k l/16          B: col l%16, k l/16
 //   v_mfma_f32_16x16x32_bf16: A: row l%16, k 8*(l/16)+e    B: col l%16, k 8*(l/16)+e  (e < 8)
 //   accumulator (both): element r of lane l is row 4*(l/16)+r, col l%16.
+//
+// Unguarded loads.  A K step that lies inside the matrix is loaded without a check per vector:
+// one wavefront-uniform test picks that path, so the loads of a step are issued back to back
+// instead of each behind its own branch.  Rows of A past the last one read the last row instead
+// (their products land in rows that are not stored).  A vector of B that crosses the last column
+// starts at the last place where it fits, and its elements are shifted into place on the way to
+// LDS (`raw`; only in the blocks of the last tile column, the only ones to pay for it).  With a
+// check per vector those blocks set the time of a ragged product: 1777 x 2050 x 1001 FP32, whose
+// last tile column is two wide, took 143 us reading element by element, 128 us with unguarded
+// vectors everywhere else, and takes 92 us.
 // ---------------------------------------------------------------------------------------------
 template <int BM, int BN, int BK>
 constexpr int gemm_f32_smem() {
   return 4 * BK * ((((BM + 63) / 64) * 64 + 16) + (((BN + 63) / 64) * 64 + 16));
 }
 
-template <int BM, int BN, int BK, int WM, int WN, bool VEC, bool OUT_BF16>
+template <int BM, int BN, int BK, int WM, int WN, bool OUT_BF16>
 __device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, int bid, unsigned char *smem) {
   static_assert(64 * (BM / WM) * (BN / WN) == 256, "four wavefronts per block");
   constexpr int NWN = BN / WN, NT = 64 * (BM / WM) * NWN;
@@ -135,13 +180,29 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, int bid, unsign
   const float *B = static_cast<const float *>(p.B);
 
   float4 ra[NA], rb[NB];
+  const bool n_whole = n0 + BN <= p.N;
+  const int bc = n0 + (tid % (BN / 4)) * 4, bs = max(0, min(bc, p.N - 4)), b_bits = min(32 * (bc - bs), 96);
+  bool raw = false;
+  const float *pa[NA], *const pb = B + int64_t(tid / (BN / 4)) * p.ldb + bs;
+#pragma unroll
+  for (int j = 0; j < NA; ++j)
+    pa[j] = A + int64_t(min(m0 + (tid + NT * j) / (BK / 4), p.M - 1)) * p.lda + (tid % (BK / 4)) * 4;
+  static_assert(NT % (BK / 4) == 0 && NT % (BN / 4) == 0, "a thread keeps its column in every unit");
   auto load = [&](int k0) {  // next tile into registers (zero outside the matrices)
+    raw = UA % NT == 0 && UB % NT == 0 && p.N >= 4 && k0 + BK <= p.K;  // see "Unguarded loads" above
+    if (raw) {
+#pragma unroll
+      for (int j = 0; j < NA; ++j) ra[j] = load_as<float4>(pa[j] + k0);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) rb[j] = load_as<float4>(pb + int64_t(k0 + j * (NT / (BN / 4))) * p.ldb);
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
       const int u = tid + NT * j, r = u / (BK / 4), c = (u % (BK / 4)) * 4;
       const int gr = m0 + r, gc = k0 + c;
-      if (u < UA && VEC && gr < p.M && gc + 3 < p.K) {
-        ra[j] = *reinterpret_cast<const float4 *>(A + int64_t(gr) * p.lda + gc);
+      if (u < UA && gr < p.M && gc + 3 < p.K) {
+        ra[j] = load_as<float4>(A + int64_t(gr) * p.lda + gc);
       } else {
         float v[4];
 #pragma unroll
@@ -154,8 +215,8 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, int bid, unsign
     for (int j = 0; j < NB; ++j) {
       const int u = tid + NT * j, r = u / (BN / 4), c = (u % (BN / 4)) * 4;
       const int gr = k0 + r, gc = n0 + c;
-      if (u < UB && VEC && gr < p.K && gc + 3 < p.N) {
-        rb[j] = *reinterpret_cast<const float4 *>(B + int64_t(gr) * p.ldb + gc);
+      if (u < UB && gr < p.K && gc + 3 < p.N) {
+        rb[j] = load_as<float4>(B + int64_t(gr) * p.ldb + gc);
       } else {
         float v[4];
 #pragma unroll
@@ -187,6 +248,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, int bid, unsign
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int u = tid + NT * j, r = u / (BN / 4), c = (u % (BN / 4)) * 4;
+      if (raw && !n_whole) rb[j] = shift_down(rb[j], b_bits);
       if (u < UB) *reinterpret_cast<float4 *>(&Bs[r * SB + c]) = rb[j];
     }
     __syncthreads();
@@ -225,7 +287,7 @@ constexpr int gemm_bf16_smem() {
   return 2 * (BM + BN) * (BK + 8);
 }
 
-template <int BM, int BN, int BK, int WM, int WN, bool VEC, bool OUT_BF16>
+template <int BM, int BN, int BK, int WM, int WN, bool OUT_BF16>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &p, int bid, unsigned char *smem) {
   static_assert(BK % 32 == 0, "BK must be a multiple of the 32-deep matrix-core step");
   static_assert(64 * (BM / WM) * (BN / WN) == 256, "four wavefronts per block");
@@ -245,14 +307,34 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &p, int bid, unsig
   const uint16_t *B = static_cast<const uint16_t *>(p.B);
 
   uint4 ra[NA], rb0[NB], rb1[NB];
+  const bool n_whole = n0 + BN <= p.N;
+  const int bc = n0 + (tid % (BN / 8)) * 8, bs = max(0, min(bc, p.N - 8)), b_bits = min(16 * (bc - bs), 112);
+  bool raw = false;
+  const uint16_t *pa[NA], *const pb = B + int64_t(2 * (tid / (BN / 8))) * p.ldb + bs;
+#pragma unroll
+  for (int j = 0; j < NA; ++j)
+    pa[j] = A + int64_t(min(m0 + (tid + NT * j) / (BK / 8), p.M - 1)) * p.lda + (tid % (BK / 8)) * 8;
+  static_assert(NT % (BK / 8) == 0 && NT % (BN / 8) == 0, "a thread keeps its column in every unit");
   auto load = [&](int k0) {
+    raw = UA % NT == 0 && UB % NT == 0 && p.N >= 8 && k0 + BK <= p.K;  // see "Unguarded loads" above
+    if (raw) {
+#pragma unroll
+      for (int j = 0; j < NA; ++j) ra[j] = load_as<uint4>(pa[j] + k0);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const uint16_t *q = pb + int64_t(k0 + j * (2 * NT / (BN / 8))) * p.ldb;
+        rb0[j] = load_as<uint4>(q);
+        rb1[j] = load_as<uint4>(q + p.ldb);
+      }
+      return;
+    }
     // A: units of 8 consecutive k in one row
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
       const int u = tid + NT * j, r = u / (BK / 8), c = (u % (BK / 8)) * 8;
       const int gr = m0 + r, gc = k0 + c;
-      if (u < UA && VEC && gr < p.M && gc + 7 < p.K) {
-        ra[j] = *reinterpret_cast<const uint4 *>(A + int64_t(gr) * p.lda + gc);
+      if (u < UA && gr < p.M && gc + 7 < p.K) {
+        ra[j] = load_as<uint4>(A + int64_t(gr) * p.lda + gc);
       } else {
         uint16_t v[8];
 #pragma unroll
@@ -265,9 +347,9 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &p, int bid, unsig
     for (int j = 0; j < NB; ++j) {
       const int u = tid + NT * j, kp = u / (BN / 8), c = (u % (BN / 8)) * 8;
       const int gk = k0 + 2 * kp, gc = n0 + c;
-      if (u < UB && VEC && gk + 1 < p.K && gc + 7 < p.N) {
-        rb0[j] = *reinterpret_cast<const uint4 *>(B + int64_t(gk) * p.ldb + gc);
-        rb1[j] = *reinterpret_cast<const uint4 *>(B + int64_t(gk + 1) * p.ldb + gc);
+      if (u < UB && gk + 1 < p.K && gc + 7 < p.N) {
+        rb0[j] = load_as<uint4>(B + int64_t(gk) * p.ldb + gc);
+        rb1[j] = load_as<uint4>(B + int64_t(gk + 1) * p.ldb + gc);
       } else {
         uint16_t lo[8], hi[8];
 #pragma unroll
@@ -297,6 +379,10 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &p, int bid, unsig
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int u = tid + NT * j, kp = u / (BN / 8), c = (u % (BN / 8)) * 8;
+      if (raw && !n_whole) {
+        rb0[j] = shift_down(rb0[j], b_bits);
+        rb1[j] = shift_down(rb1[j], b_bits);
+      }
       if (u < UB) {
         uint16_t lo[8], hi[8];
         memcpy(lo, &rb0[j], 16);
@@ -360,7 +446,7 @@ constexpr int gemm_f32_splitk_smem() {
                   : 4 * TM * TN);
 }
 
-template <int TM, int TN, bool VEC, bool OUT_BF16>
+template <int TM, int TN, bool OUT_BF16>
 __device__ __forceinline__ void gemm_f32_splitk_tile(const GemmArgs &p, int bid, unsigned char *smem_raw) {
   constexpr int BK = 32, FM = TM / 16, FN = TN / 16;
   constexpr int SA = SkPitch<TM>::value, SB = SkPitch<TN>::value;
@@ -377,14 +463,29 @@ __device__ __forceinline__ void gemm_f32_splitk_tile(const GemmArgs &p, int bid,
   const int iters = (nchunks + 3) / 4;
 
   float4 ra[UA], rb[UB];
+  const bool n_whole = n0 + TN <= p.N;
+  const int bc = n0 + (lane % (TN / 4)) * 4, bs = max(0, min(bc, p.N - 4)), b_bits = min(32 * (bc - bs), 96);
+  bool raw = false;
+  const float *pa[UA], *const pb = B + int64_t(lane / (TN / 4)) * p.ldb + bs;
+#pragma unroll
+  for (int j = 0; j < UA; ++j)
+    pa[j] = A + int64_t(min(m0 + (lane + 64 * j) / (BK / 4), p.M - 1)) * p.lda + (lane % (BK / 4)) * 4;
   auto load = [&](int chunk) {
     const int k0 = chunk * BK;
+    raw = p.N >= 4 && k0 + BK <= p.K;  // see "Unguarded loads" above
+    if (raw) {
+#pragma unroll
+      for (int j = 0; j < UA; ++j) ra[j] = load_as<float4>(pa[j] + k0);
+#pragma unroll
+      for (int j = 0; j < UB; ++j) rb[j] = load_as<float4>(pb + int64_t(k0 + j * (64 / (TN / 4))) * p.ldb);
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < UA; ++j) {
       const int u = lane + 64 * j, r = u / (BK / 4), c = (u % (BK / 4)) * 4;
       const int gr = m0 + r, gc = k0 + c;
-      if (VEC && gr < p.M && gc + 3 < p.K) {
-        ra[j] = *reinterpret_cast<const float4 *>(A + int64_t(gr) * p.lda + gc);
+      if (gr < p.M && gc + 3 < p.K) {
+        ra[j] = load_as<float4>(A + int64_t(gr) * p.lda + gc);
       } else {
         float v[4];
 #pragma unroll
@@ -396,8 +497,8 @@ __device__ __forceinline__ void gemm_f32_splitk_tile(const GemmArgs &p, int bid,
     for (int j = 0; j < UB; ++j) {
       const int u = lane + 64 * j, r = u / (TN / 4), c = (u % (TN / 4)) * 4;
       const int gr = k0 + r, gc = n0 + c;
-      if (VEC && gr < p.K && gc + 3 < p.N) {
-        rb[j] = *reinterpret_cast<const float4 *>(B + int64_t(gr) * p.ldb + gc);
+      if (gr < p.K && gc + 3 < p.N) {
+        rb[j] = load_as<float4>(B + int64_t(gr) * p.ldb + gc);
       } else {
         float v[4];
 #pragma unroll
@@ -428,6 +529,7 @@ __device__ __forceinline__ void gemm_f32_splitk_tile(const GemmArgs &p, int bid,
 #pragma unroll
     for (int j = 0; j < UB; ++j) {
       const int u = lane + 64 * j, r = u / (TN / 4), c = (u % (TN / 4)) * 4;
+      if (raw && !n_whole) rb[j] = shift_down(rb[j], b_bits);
       *reinterpret_cast<float4 *>(&Bs[r * SB + c]) = rb[j];
     }
     if (it + 1 < iters) load((it + 1) * 4 + w);
@@ -473,7 +575,7 @@ constexpr int gemm_bf16_splitk_smem() {
 // 64 x 64 tile, whose 64 accumulator registers per lane would otherwise push a two-wavefront-per-
 // SIMD kernel into spills), at the price of the overlap, which matters little when a wavefront
 // has only a few chunks.
-template <int TM, int TN, bool VEC, bool OUT_BF16, bool PREFETCH = true>
+template <int TM, int TN, bool OUT_BF16, bool PREFETCH = true>
 __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid, unsigned char *smem) {
   constexpr int BK = 64, KP = BK + 8, FM = TM / 16, FN = TN / 16;
   constexpr int UA = TM * (BK / 8) / 64;        // uint4 (8 x bf16) loads per lane
@@ -490,14 +592,33 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
   const int iters = (nchunks + 3) / 4;
 
   uint4 ra[UA], rb0[UB], rb1[UB];
+  const bool n_whole = n0 + TN <= p.N;
+  const int bc = n0 + (lane % (TN / 8)) * 8, bs = max(0, min(bc, p.N - 8)), b_bits = min(16 * (bc - bs), 112);
+  bool raw = false;
+  const uint16_t *pa[UA], *const pb = B + int64_t(2 * (lane / (TN / 8))) * p.ldb + bs;
+#pragma unroll
+  for (int j = 0; j < UA; ++j)
+    pa[j] = A + int64_t(min(m0 + (lane + 64 * j) / (BK / 8), p.M - 1)) * p.lda + (lane % (BK / 8)) * 8;
   auto load = [&](int chunk) {
     const int k0 = chunk * BK;
+    raw = p.N >= 8 && k0 + BK <= p.K;  // see "Unguarded loads" above
+    if (raw) {
+#pragma unroll
+      for (int j = 0; j < UA; ++j) ra[j] = load_as<uint4>(pa[j] + k0);
+#pragma unroll
+      for (int j = 0; j < UB; ++j) {
+        const uint16_t *q = pb + int64_t(k0 + j * (2 * 64 / (TN / 8))) * p.ldb;
+        rb0[j] = load_as<uint4>(q);
+        rb1[j] = load_as<uint4>(q + p.ldb);
+      }
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < UA; ++j) {
       const int u = lane + 64 * j, r = u / (BK / 8), c = (u % (BK / 8)) * 8;
       const int gr = m0 + r, gc = k0 + c;
-      if (VEC && gr < p.M && gc + 7 < p.K) {
-        ra[j] = *reinterpret_cast<const uint4 *>(A + int64_t(gr) * p.lda + gc);
+      if (gr < p.M && gc + 7 < p.K) {
+        ra[j] = load_as<uint4>(A + int64_t(gr) * p.lda + gc);
       } else {
         uint16_t v[8];
 #pragma unroll
@@ -509,9 +630,9 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
     for (int j = 0; j < UB; ++j) {
       const int u = lane + 64 * j, kp = u / (TN / 8), c = (u % (TN / 8)) * 8;
       const int gk = k0 + 2 * kp, gc = n0 + c;
-      if (VEC && gk + 1 < p.K && gc + 7 < p.N) {
-        rb0[j] = *reinterpret_cast<const uint4 *>(B + int64_t(gk) * p.ldb + gc);
-        rb1[j] = *reinterpret_cast<const uint4 *>(B + int64_t(gk + 1) * p.ldb + gc);
+      if (gk + 1 < p.K && gc + 7 < p.N) {
+        rb0[j] = load_as<uint4>(B + int64_t(gk) * p.ldb + gc);
+        rb1[j] = load_as<uint4>(B + int64_t(gk + 1) * p.ldb + gc);
       } else {
         uint16_t lo[8], hi[8];
 #pragma unroll
@@ -544,6 +665,10 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
 #pragma unroll
     for (int j = 0; j < UB; ++j) {
       const int u = lane + 64 * j, kp = u / (TN / 8), c = (u % (TN / 8)) * 8;
+      if (raw && !n_whole) {
+        rb0[j] = shift_down(rb0[j], b_bits);
+        rb1[j] = shift_down(rb1[j], b_bits);
+      }
       uint16_t lo[8], hi[8];
       memcpy(lo, &rb0[j], 16);
       memcpy(hi, &rb1[j], 16);
@@ -600,7 +725,7 @@ constexpr int gemm_bf16_deep_smem() {
   return 4 * D * (TM + TN) * 72 * 2 > 4 * TM * TN * 4 ? 4 * D * (TM + TN) * 72 * 2 : 4 * TM * TN * 4;
 }
 
-template <int TM, int TN, int D, bool VEC, bool OUT_BF16>
+template <int TM, int TN, int D, bool OUT_BF16>
 __device__ __forceinline__ void gemm_bf16_deep_tile(const GemmArgs &p, int bid, unsigned char *smem) {
   constexpr int BK = 64, KP = BK + 8, FM = TM / 16, FN = TN / 16;
   constexpr int UA = TM * (BK / 8) / 64;        // uint4 (8 x bf16) A loads per lane per chunk
@@ -635,8 +760,8 @@ __device__ __forceinline__ void gemm_bf16_deep_tile(const GemmArgs &p, int bid, 
       for (int j = 0; j < UA; ++j) {
         const int u = lane + 64 * j, r = u / (BK / 8), c = (u % (BK / 8)) * 8;
         const int gr = m0 + r, gc = k0 + c;
-        if (VEC && live && gr < p.M && gc + 7 < p.K) {
-          ra[d][j] = *reinterpret_cast<const uint4 *>(A + int64_t(gr) * p.lda + gc);
+        if (live && gr < p.M && gc + 7 < p.K) {
+          ra[d][j] = load_as<uint4>(A + int64_t(gr) * p.lda + gc);
         } else {
           uint16_t v[8];
 #pragma unroll
@@ -648,9 +773,9 @@ __device__ __forceinline__ void gemm_bf16_deep_tile(const GemmArgs &p, int bid, 
       for (int j = 0; j < UB; ++j) {
         const int u = lane + 64 * j, kp = u / (TN / 8), c = (u % (TN / 8)) * 8;
         const int gk = k0 + 2 * kp, gc = n0 + c;
-        if (VEC && live && gk + 1 < p.K && gc + 7 < p.N) {
-          rb0[d][j] = *reinterpret_cast<const uint4 *>(B + int64_t(gk) * p.ldb + gc);
-          rb1[d][j] = *reinterpret_cast<const uint4 *>(B + int64_t(gk + 1) * p.ldb + gc);
+        if (live && gk + 1 < p.K && gc + 7 < p.N) {
+          rb0[d][j] = load_as<uint4>(B + int64_t(gk) * p.ldb + gc);
+          rb1[d][j] = load_as<uint4>(B + int64_t(gk + 1) * p.ldb + gc);
         } else {
           uint16_t lo[8], hi[8];
 #pragma unroll
@@ -1054,7 +1179,7 @@ constexpr int gemm_direct_smem() {
 //   BCOL = true: one 4-byte load per (block, row), block j holding columns 16 j .. 16 j + 15 --
 //     faster with the executor's groups of 8 steps (its projection tasks ran ~10% longer with
 //     the vector loads, 128 of them in flight per lane).
-template <int FN, bool BF16, bool VEC, bool OUT_BF16, int G = 8 / FN, bool BCOL = (G > 8 / FN)>
+template <int FN, bool BF16, bool OUT_BF16, int G = 8 / FN, bool BCOL = (G > 8 / FN)>
 __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &p, int bid, unsigned char *smem) {
   static_assert(!BF16 || G == 8 / FN, "the BF16 staging area is sized for G = 8 / FN");
   constexpr int TN = 16 * FN;
@@ -1088,8 +1213,8 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &p, int bid, uns
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const int k = kb + (s0 + g) * STEP + kl;
-      if (VEC && row_ok && k + E <= ke) {
-        ra[g] = *reinterpret_cast<const uint4 *>(arow + k);
+      if (row_ok && k + E <= ke) {
+        ra[g] = load_as<uint4>(arow + k);
       } else if constexpr (BF16) {
         ra[g] = pack8_guarded(reinterpret_cast<const uint16_t *>(arow) + k, [&](int e) { return row_ok && k + e < ke; });
       } else {
@@ -1106,9 +1231,9 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &p, int bid, uns
           const int k0 = ks + 2 * kp;
           const bool uok = unit < 16 * (TN / 8);
           const uint16_t *b0 = reinterpret_cast<const uint16_t *>(B) + int64_t(k0) * p.ldb + c;
-          if (uok && VEC && k0 + 1 < ke && c + 7 < p.N) {
-            rb0[g][u] = *reinterpret_cast<const uint4 *>(b0);
-            rb1[g][u] = *reinterpret_cast<const uint4 *>(b0 + p.ldb);
+          if (uok && k0 + 1 < ke && c + 7 < p.N) {
+            rb0[g][u] = load_as<uint4>(b0);
+            rb1[g][u] = load_as<uint4>(b0 + p.ldb);
           } else {
             rb0[g][u] = pack8_guarded(b0, [&](int e) { return uok && k0 < ke && c + e < p.N; });
             rb1[g][u] = pack8_guarded(b0 + p.ldb, [&](int e) { return uok && k0 + 1 < ke && c + e < p.N; });
@@ -1130,12 +1255,12 @@ __device__ __forceinline__ void gemm_direct_tile(const GemmArgs &p, int bid, uns
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const float *brow = reinterpret_cast<const float *>(B) + int64_t(k + e) * p.ldb + colb;
-          if (VEC && FN > 1 && colb + FN <= p.N && k + e < ke) {
+          if (FN > 1 && colb + FN <= p.N && k + e < ke) {
             if constexpr (FN == 4) {
-              const float4 v = *reinterpret_cast<const float4 *>(brow);
+              const float4 v = load_as<float4>(brow);
               rbf[g][0][e] = v.x; rbf[g][FN > 1 ? 1 : 0][e] = v.y; rbf[g][FN > 2 ? 2 : 0][e] = v.z; rbf[g][FN > 3 ? 3 : 0][e] = v.w;
             } else if constexpr (FN == 2) {
-              const float2 v = *reinterpret_cast<const float2 *>(brow);
+              const float2 v = load_as<float2>(brow);
               rbf[g][0][e] = v.x; rbf[g][FN > 1 ? 1 : 0][e] = v.y;
             }
           } else {
@@ -1225,7 +1350,7 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-template <int NV, bool VEC, bool IN_BF16, bool OUT_BF16, bool NT = false, int CW = 4>
+template <int NV, bool IN_BF16, bool OUT_BF16, bool NT = false, int CW = 4>
 __device__ __forceinline__ void softmax_row(const SoftmaxArgs &p, int row) {
   const int lane = threadIdx.x & 63;
   const int64_t xo = int64_t(row) * p.ldx, yo = int64_t(row) * p.ldy;
@@ -1240,7 +1365,7 @@ __device__ __forceinline__ void softmax_row(const SoftmaxArgs &p, int row) {
 #pragma unroll
     for (int t = 0; t < NC; ++t) {
       const int c = (t * 64 + lane) * CW;
-      if (VEC && c + CW - 1 < p.C) {
+      if (c + CW - 1 < p.C) {
         if constexpr (IN_BF16 && CW == 8) {
           const u32x4 w = load16<NT>(static_cast<const uint16_t *>(p.X) + xo + c);
 #pragma unroll
@@ -1279,7 +1404,7 @@ __device__ __forceinline__ void softmax_row(const SoftmaxArgs &p, int row) {
 #pragma unroll
     for (int t = 0; t < NC; ++t) {
       const int c = (t * 64 + lane) * CW;
-      if (VEC && c + CW - 1 < p.C) {
+      if (c + CW - 1 < p.C) {
 #pragma unroll
         for (int h = 0; h < CW / 4; ++h) {
           const float *q = &v[t][4 * h];
@@ -1322,41 +1447,12 @@ __device__ __forceinline__ void softmax_row(const SoftmaxArgs &p, int row) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Transpose through a padded 64 x 64 LDS tile: coalesced reads along A's rows, coalesced writes
-// along B's rows.  Element size ES bytes (4: f32, 2: bf16); bit-exact.
+// Transpose through a padded 64 x 64 LDS tile: 16-byte global reads along A's rows and 16-byte
+// global writes along B's rows; elements move through the LDS tile one by one.  T: 4 (f32) or 2
+// (bf16) byte elements; bit-exact.  Tiles inside the matrix take an unchecked path with all
+// sixteen-byte loads in flight at once; edge tiles check every vector and fall back to element
+// accesses where one crosses the edge.  NT: streaming loads and stores.
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ void transpose_tile(const TransArgs &p, int bid, unsigned char *smem) {
-  T(*tile)[65] = reinterpret_cast<T(*)[65]>(smem);
-  const int tiles_c = (p.C + 63) / 64;
-  const int tr = bid / tiles_c, tc = bid % tiles_c;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const T *A = static_cast<const T *>(p.A);
-  T *B = static_cast<T *>(p.B);
-  T v[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {  // all sixteen loads in flight before the first LDS write
-    const int r = tr * 64 + ty + 4 * i, c = tc * 64 + tx;
-    v[i] = (r < p.R && c < p.C) ? A[int64_t(r) * p.lda + c] : T(0);
-  }
-#pragma unroll
-  for (int i = 0; i < 16; ++i) tile[ty + 4 * i][tx] = v[i];
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 16; ++i) v[i] = tile[tx][ty + 4 * i];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int orow = tc * 64 + ty + 4 * i, ocol = tr * 64 + tx;
-    if (orow < p.C && ocol < p.R) B[int64_t(orow) * p.ldb + ocol] = v[i];
-  }
-}
-
-// Vector variant for aligned operands (base addresses 16-byte aligned, leading dimensions
-// multiples of V = 16 / sizeof(T)): 16-byte global reads along A's rows and 16-byte global writes
-// along B's rows; elements move through the padded LDS tile one by one.  Tiles inside the matrix
-// take an unchecked path with all sixteen-byte loads in flight at once; edge tiles check every
-// vector and fall back to element accesses where one crosses the edge.  NT: streaming loads and
-// stores.
 template <typename T, bool CHECK, bool NT>
 __device__ __forceinline__ void transpose_vec_load(const TransArgs &p, int tr, int tc, T (*tile)[65]) {
   constexpr int V = 16 / int(sizeof(T)), VPR = 64 / V, RPP = 256 / VPR, PASSES = 64 / RPP;
@@ -1427,7 +1523,7 @@ __device__ __forceinline__ void transpose_tile_vec(const TransArgs &p, int bid, 
   }
 }
 
-// Rectangular tiles for aligned operands: TR rows x TC columns of A per 256-thread block, so a
+// Rectangular tiles: TR rows x TC columns of A per 256-thread block, so a
 // block reads TR runs of TC elements and writes TC runs of TR elements (64 x 128 doubles the
 // contiguous read runs of the 64 x 64 tile, 128 x 64 the write runs).  Tiles inside the matrix go
 // through 16-byte vectors, edge tiles element by element with checks.  Diagonal tile order as
@@ -1487,22 +1583,9 @@ __device__ __forceinline__ void transpose_rc_tile(const TransArgs &p, int bid, u
 }
 
 // ---------------------------------------------------------------------------------------------
-// Element-wise add in FP32: grid (ceil(C/256), R), one element per thread.
+// Element-wise add in FP32, rounded once to the output type: each thread adds 8 consecutive
+// elements per row of a 2048-column chunk; a workgroup covers one chunk of one row.
 // ---------------------------------------------------------------------------------------------
-template <bool IN_BF16, bool OUT_BF16>
-__device__ __forceinline__ void add_block(const AddArgs &p, int bid) {
-  const int nbx = (p.C + 255) / 256;
-  const int c = (bid % nbx) * 256 + threadIdx.x;
-  const int r = bid / nbx;
-  if (c >= p.C || r >= p.R) return;
-  const float a = load_elem<IN_BF16>(p.A, int64_t(r) * p.lda + c);
-  const float b = load_elem<IN_BF16>(p.B, int64_t(r) * p.ldb + c);
-  store_elem<OUT_BF16>(p.Cp, int64_t(r) * p.ldc + c, a + b);
-}
-
-// Vector variant (operands 16-byte aligned, leading dimensions multiples of 8): each thread adds
-// 8 consecutive elements per row of a 2048-column chunk; a workgroup covers one chunk of one row.
-// The FP32 sum of two values is rounded once to the output type, as in add_block.
 template <bool IN_BF16, bool OUT_BF16, bool NT = false>
 __device__ __forceinline__ void add_block_vec(const AddArgs &p, int bid) {
   const int nbx = (p.C + 2047) / 2048;

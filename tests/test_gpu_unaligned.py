@@ -1,0 +1,70 @@
+"""Kernels on operands of no common alignment: odd leading dimensions and windows that start at odd
+rows and columns, at widths around a 16-byte vector and a tile.  Every GEMM tile and dtype, against
+exact results (ternary operands), and softmax, transpose and add."""
+import numpy as np
+import pytest
+
+import paper_2009_07482_amd as psc
+from oracle.bf16 import round_bf16, round_f32
+from gpu_helpers import normwise, oracle_outputs, uniform
+
+pytestmark = pytest.mark.gpu
+
+
+def _window(name, dt, rows, cols, pad):
+    """A root of odd width and the rows x cols window of it at an odd offset."""
+    width = cols + 2 * pad + 1
+    return [{"name": name + "r", "dtype": dt, "rows": rows + pad, "cols": width, "view_of": None, "row_off": 0,
+             "col_off": 0},
+            {"name": name, "dtype": dt, "rows": rows, "cols": cols, "view_of": name + "r", "row_off": pad,
+             "col_off": pad}]
+
+
+def _embed(value, spec, name):
+    b = {x["name"]: x for x in spec["buffers"]}
+    v, r = b[name], b[name + "r"]
+    out = np.full((r["rows"], r["cols"]), 7.0, np.float32)   # what lies around a window must not matter
+    out[v["row_off"]:v["row_off"] + v["rows"], v["col_off"]:v["col_off"] + v["cols"]] = value
+    return out
+
+
+SHAPES = [(5, 1, 3), (33, 7, 9), (70, 9, 65), (64, 65, 64), (130, 66, 127), (257, 129, 200)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("tile", list(range(1, psc.psc_gemm_tile_count())))
+def test_gemm_windows_exact(dt, tile):
+    g = np.random.default_rng(40 + tile)
+    for m, n, k in SHAPES:
+        for pad in (1, 3):
+            print(f"gemm {dt} {m}x{n}x{k} tile {tile} pad {pad}", flush=True)
+            spec = {"buffers": _window("A", dt, m, k, pad) + _window("B", dt, k, n, pad) + _window("C", "f32", m, n, pad),
+                    "kernels": [{"name": "k", "kind": "gemm", "inputs": ["A", "B"], "outputs": ["C"], "alpha": 1.0,
+                                 "tile": tile}], "edges": [], "component": [0]}
+            a = g.integers(-1, 2, (m, k)).astype(np.float32)
+            b = g.integers(-1, 2, (k, n)).astype(np.float32)
+            out, _ = psc.run_spec(spec, {"Ar": _embed(a, spec, "A"), "Br": _embed(b, spec, "B")}, "coarse")
+            np.testing.assert_array_equal(out["C"], a.astype(np.float64) @ b.astype(np.float64))
+
+
+@pytest.mark.parametrize("policy", ["coarse", "device"])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("r,c,pad", [(3, 1, 1), (65, 7, 3), (9, 257, 1), (66, 515, 3), (5, 1001, 1), (4, 2047, 3)])
+def test_elementwise_windows(policy, dt, r, c, pad):
+    print(f"elementwise {dt} {r}x{c} pad {pad} {policy}", flush=True)
+    names = [("A", r, c), ("B", r, c), ("S", r, c), ("P", r, c), ("T", c, r)]
+    spec = {"buffers": [b for n, h, w in names for b in _window(n, dt, h, w, pad)],
+            "kernels": [{"name": "s", "kind": "add", "inputs": ["A", "B"], "outputs": ["S"], "alpha": 1.0, "tile": 0},
+                        {"name": "p", "kind": "softmax", "inputs": ["A"], "outputs": ["P"], "alpha": 1.0, "tile": 0},
+                        {"name": "t", "kind": "transpose", "inputs": ["A"], "outputs": ["T"], "alpha": 1.0, "tile": 0}],
+            "edges": [], "component": [0, 0, 0]}
+    a, b = uniform(51, (r, c), -3, 3), uniform(52, (r, c))
+    inp = {"Ar": _embed(a, spec, "A"), "Br": _embed(b, spec, "B")}
+    out, _ = psc.run_spec(spec, inp, policy)
+    if dt == "bf16":
+        a, b = round_bf16(a), round_bf16(b)
+    s = a.astype(np.float64) + b.astype(np.float64)
+    np.testing.assert_array_equal(out["S"], round_bf16(round_f32(s)) if dt == "bf16" else round_f32(s))
+    np.testing.assert_array_equal(out["T"], np.asarray(a, np.float64).T)
+    # FP32 exponentials and sums (~1e-7 each), and for BF16 output the rare rounding they flip
+    assert normwise(out["P"], oracle_outputs(spec, inp, emulate=True)["P"]) < (1e-5 if dt == "f32" else 1e-3)
