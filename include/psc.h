@@ -113,7 +113,9 @@ typedef enum psc_policy {
  *                     (sel_rr of Sec. IV-B, Algorithm 1) -- the plain heuristic.
  *  PSC_MAP_EFT        list scheduling under the cost model given in the options: kernels by
  *                     descending bottom-level rank (Sec. V, clustering) on predicted durations,
- *                     each on the stream where it can start first (ties: the earliest predicted
+ *                     each on the stream where it can start first (3 us later
+ *                    on any but the stream of the predecessor that finishes last, for the
+ *                    cross-stream wait; ties: the earliest predicted
  *                     finish with the streams then busy, as HEFT's EFT rule; then the lower
  *                     stream); the stream stays busy for that predicted, contended duration.
  *  PSC_MAP_COMPONENT  every kernel of task component c on stream c mod n_streams. */
@@ -168,7 +170,8 @@ typedef struct psc_sched_opts {
                            edge per stream-order or wait precedence -- once (again when the host
                            pointers change) and launches it with hipGraphLaunch */
   int32_t record_ops;   /* 1: psc_run records start/end events around every op (timeline and
-                           cost-model samples); incompatible with use_graph */
+                           cost-model samples), every kernel in a launch of its own (see
+                           psc_run); incompatible with use_graph */
   int32_t device;       /* HIP device ordinal */
   const psc_mlp *cost;  /* learned cost model for PSC_MAP_EFT; NULL = heuristic model */
   int32_t host_threads; /* host threads that enqueue in psc_run (stream s is enqueued by thread
@@ -431,6 +434,13 @@ psc_status psc_sched_prepare(psc_sched *sched);
  * host order (each wait as hipStreamWaitEvent on the producing op's event), joins all streams
  * and waits for the end event.  io[0..n_io) gives host memory for isolated writes / reads by
  * buffer name (see psc_host_io); buffers not listed are not copied.  stats may be NULL.
+ * A PSC_FINE schedule with in-order queues hands kernels of one stream that run the same kernel
+ * function at the same level of the DAG (so none depends on another) to the GPU as one launch over
+ * all their workgroups, placed where the first of them stands: the precedences, the buffers and
+ * the results are those of one launch per kernel, and psc_sched_export keeps describing the plan
+ * kernel by kernel.  GEMMs with an automatic tile take one that suits the launch, among those that
+ * sum in the same order.  Every kernel keeps its own launch under record_ops, mark_components,
+ * use_graph, fault_inject_op and out_of_order, and under every other policy.
  * Errors: PSC_ERR_NAME (io names no isolated write or read), PSC_ERR_ARG (byte count), PSC_ERR_HIP. */
 psc_status psc_run(psc_sched *sched, const psc_host_io *io, int32_t n_io, psc_run_stats *stats);
 
@@ -687,8 +697,9 @@ psc_status psc_autotune_dag(psc_dag *dag, int32_t device, int32_t iters, int32_t
  * by holding more LDS and registers).  For every GEMM shape class of the DAG (operand and output
  * dtype included; kernels with a fixed tile are left alone) this first runs psc_autotune_gemm,
  * then, for the max_classes heaviest classes (isolated time x kernels), heaviest first, schedules
- * the DAG with `policy` and `opts` once per candidate among the class's top_k isolated tiles --
- * the other classes at their current choice -- and times `iters` device-resident runs on seeded
+ * the DAG with `policy` and `opts` once per candidate among the class's top_k isolated tiles (and,
+ * under PSC_FINE, the 64-column tiles 2, 6 and 7, which suit kernels launched together) -- the
+ * other classes at their current choice -- and times `iters` device-resident runs on seeded
  * inputs; the tile with the lowest median makespan goes into the tile cache (lighter classes keep
  * the isolated winner).  *n_changed (may be NULL) = classes whose choice differs from the
  * isolated winner.  The DAG must be schedulable with these options. */
@@ -704,7 +715,8 @@ psc_status psc_autotune_dag_in_schedule(psc_dag *dag, int32_t policy, const psc_
 psc_status psc_autotune_schedule(psc_dag *dag, int32_t policy, const psc_sched_opts *candidates,
                                  int32_t n, int32_t iters, int32_t *best, float *ms_per_run);
 
-/* [GPU after prepare] Tile configuration a prepared schedule uses for GEMM kernel `kernel`. */
+/* [GPU after prepare] Tile configuration a prepared schedule uses for GEMM kernel `kernel` in a
+ * launch of its own (launched with others, an automatic tile may be a larger one; see psc_run). */
 psc_status psc_sched_kernel_tile(const psc_sched *sched, int32_t kernel, int32_t *tile);
 
 /* [GPU after prepare] The device executor a prepared PSC_DEVICE schedule launches: its workgroup

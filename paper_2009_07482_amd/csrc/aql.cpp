@@ -308,6 +308,7 @@ struct AqlSchedule::Impl {
   Agent *ag = nullptr;
   const SchedPlan *plan = nullptr;
   bool record = false;
+  std::shared_ptr<AqlQueues> shared;
   std::vector<hsa_queue_t *> queues;       // per stream; nullptr for streams without kernels
   std::vector<hsa_signal_t> sig;           // per op: its completion
   hsa_signal_t start_sig{}, end_sig{};
@@ -360,9 +361,10 @@ struct AqlSchedule::Impl {
       if (start_sig.handle) hsa_signal_store_screlease(start_sig, 0);
       drained = ended_within(10000);
     }
-    if (!drained) return;
-    for (hsa_queue_t *q : queues)
-      if (q) (void)hsa_queue_destroy(q);
+    if (!drained) {
+      if (shared) shared->abandon();
+      return;
+    }
     for (hsa_signal_t x : sig)
       if (x.handle) (void)hsa_signal_destroy(x);
     for (hsa_signal_t x : qend)
@@ -465,8 +467,53 @@ struct AqlSchedule::Impl {
   }
 };
 
-AqlSchedule::AqlSchedule(int device, const SchedPlan &plan, const std::vector<Launch> &launch,
-                         const std::vector<Launch> &mark_after, const Launch *mark_start, bool record)
+AqlQueues::AqlQueues(int device, const std::vector<const SchedPlan *> &plans, bool record) {
+  Agent &ag = agent_for(device);
+  for (const SchedPlan *plan : plans) {
+    const int32_t T = plan->total_streams;
+    if (queues_.size() < size_t(T)) queues_.resize(T, nullptr);
+  }
+  const int32_t T = int32_t(queues_.size());
+  // a queue for every stream holding a kernel (and stream 0, which holds the marks and the join);
+  // packets per queue per run, an upper bound: start, per op its barriers, dispatch and mark, join
+  std::vector<char> has_kernel(T, 0);
+  has_kernel[0] = 1;
+  std::vector<uint64_t> size_for(T, 0);
+  for (const SchedPlan *plan : plans) {
+    std::vector<uint64_t> need(T, 6);
+    need[0] += uint64_t(T) / 5 + 8;
+    for (const Op &op : plan->ops) {
+      if (op.type == PSC_OP_KERNEL) has_kernel[op.stream] = 1;
+      need[op.stream] += 3 + (op.waits.size() + 1 + 4) / 5;
+    }
+    for (int32_t s = 0; s < T; ++s) size_for[s] = std::max(size_for[s], need[s]);
+  }
+  try {
+    for (int32_t s = 0; s < T; ++s) {
+      if (!has_kernel[s]) continue;
+      uint32_t size = 256;
+      while (size < size_for[s] && size < ag.queue_max) size *= 2;
+      if (size < size_for[s]) fail(PSC_ERR_UNSUPPORTED, "AQL dispatch: a stream holds more packets than a queue");
+      hsa_queue_t *q = nullptr;
+      PSC_HSA(hsa_queue_create(ag.gpu, size, HSA_QUEUE_TYPE_SINGLE, queue_error, nullptr, UINT32_MAX, UINT32_MAX, &q));
+      queues_[s] = q;
+      if (record) PSC_HSA(hsa_amd_profiling_set_profiler_enabled(q, 1));
+    }
+  } catch (...) {
+    for (void *q : queues_)
+      if (q) (void)hsa_queue_destroy(static_cast<hsa_queue_t *>(q));
+    throw;
+  }
+}
+
+AqlQueues::~AqlQueues() {
+  if (abandoned_) return;
+  for (void *q : queues_)
+    if (q) (void)hsa_queue_destroy(static_cast<hsa_queue_t *>(q));
+}
+
+AqlSchedule::AqlSchedule(int device, std::shared_ptr<AqlQueues> queues, const SchedPlan &plan,
+                         const std::vector<Launch> &launch, const std::vector<Launch> &mark_after, const Launch *mark_start, bool record)
     : p_(new Impl) {
   Impl &I = *p_;
   I.device = device;
@@ -477,25 +524,9 @@ AqlSchedule::AqlSchedule(int device, const SchedPlan &plan, const std::vector<La
   Agent &ag = *I.ag;
   const size_t n = plan.ops.size();
   const int32_t T = plan.total_streams;
-  // a queue for every stream holding a kernel (and stream 0, which holds the marks and the join)
-  std::vector<char> has_kernel(T, 0);
-  has_kernel[0] = 1;
-  for (const Op &op : plan.ops)
-    if (op.type == PSC_OP_KERNEL) has_kernel[op.stream] = 1;
-  // packets per queue per run, an upper bound: start, per op its barriers, dispatch and mark, join
-  std::vector<uint64_t> need(T, 6);
-  need[0] += uint64_t(T) / 5 + 8;
-  for (const Op &op : plan.ops) need[op.stream] += 3 + (op.waits.size() + 1 + 4) / 5;
+  I.shared = std::move(queues);
   I.queues.assign(T, nullptr);
-  for (int32_t s = 0; s < T; ++s) {
-    if (!has_kernel[s]) continue;
-    uint32_t size = 256;
-    while (size < need[s] && size < ag.queue_max) size *= 2;
-    if (size < need[s]) fail(PSC_ERR_UNSUPPORTED, "AQL dispatch: a stream holds more packets than a queue");
-    PSC_HSA(hsa_queue_create(ag.gpu, size, HSA_QUEUE_TYPE_SINGLE, queue_error, nullptr, UINT32_MAX, UINT32_MAX,
-                             &I.queues[s]));
-    if (record) PSC_HSA(hsa_amd_profiling_set_profiler_enabled(I.queues[s], 1));
-  }
+  for (int32_t s = 0; s < T; ++s) I.queues[s] = static_cast<hsa_queue_t *>(I.shared->queues_[s]);
   if (record) PSC_HSA(hsa_amd_profiling_async_copy_enable(true));
   I.sig.assign(n, hsa_signal_t{0});
   for (size_t o = 0; o < n; ++o) PSC_HSA(hsa_amd_signal_create(1, 0, nullptr, HSA_AMD_SIGNAL_AMD_GPU_ONLY, &I.sig[o]));
@@ -579,6 +610,8 @@ AqlSchedule::AqlSchedule(int device, const SchedPlan &plan, const std::vector<La
     const bool copy = op.type != PSC_OP_KERNEL;
     std::vector<int32_t> before(op.waits.begin(), op.waits.end());
     if (prev[o] >= 0) before.push_back(prev[o]);
+    // the first kernel of a queue may read what a copy before the run wrote
+    if (!copy && prev[o] < 0) I.acq_sys[o] = 1;
     for (int32_t w : before) {
       if (copy) I.rel_sys[w] = 1;
       if (plan.ops[w].type != PSC_OP_KERNEL) I.acq_sys[o] = 1;

@@ -32,14 +32,31 @@ struct AqlCopy {
   size_t dpitch = 0, spitch = 0, width = 0, height = 0;
 };
 
+// The queues of one schedule's streams, shared by the plans it may run (one run at a time).
+class AqlQueues {
+ public:
+  // plans: every plan that will run on these queues; a queue per stream that holds a kernel in
+  // any of them, large enough for a whole run of each.  record: with the queues' profiler.
+  AqlQueues(int device, const std::vector<const SchedPlan *> &plans, bool record);
+  ~AqlQueues();
+  AqlQueues(const AqlQueues &) = delete;
+  AqlQueues &operator=(const AqlQueues &) = delete;
+  // Leave the queues in place at destruction: work on them never finished.
+  void abandon() { abandoned_ = true; }
+
+ private:
+  friend class AqlSchedule;
+  std::vector<void *> queues_;  // hsa_queue_t per stream; nullptr for streams without kernels
+  bool abandoned_ = false;
+};
+
 class AqlSchedule {
  public:
-  // Resolves every launch in the library's code object on `device`, creates one queue per
-  // stream that holds a kernel, one completion signal per op and the kernel argument records
-  // (device memory, written once).  mark_after[k] (may be empty) is a launch that follows kernel
+  // Resolves every launch in the library's code object on `device`, creates one completion signal
+  // per op and the kernel argument records (device memory, written once).  mark_after[k] (may be empty) is a launch that follows kernel
   // k's op and mark_start (may be NULL) one that precedes every op (component completion marks).
   // record: per-op timestamps from the queues' profiler and the DMA engines.
-  AqlSchedule(int device, const SchedPlan &plan, const std::vector<Launch> &launch,
+  AqlSchedule(int device, std::shared_ptr<AqlQueues> queues, const SchedPlan &plan, const std::vector<Launch> &launch,
               const std::vector<Launch> &mark_after, const Launch *mark_start, bool record);
   ~AqlSchedule();
   AqlSchedule(const AqlSchedule &) = delete;

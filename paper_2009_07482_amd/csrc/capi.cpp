@@ -866,6 +866,10 @@ psc_status psc_autotune_dag_in_schedule(psc_dag *dag, int32_t policy, const psc_
         if (us[t] > 0) order.push_back(t);
       std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return us[x] < us[y]; });
       if (int(order.size()) > top_k) order.resize(top_k);
+      // kernels that share a launch fill the GPU together, with tiles too large for one alone
+      if (policy == PSC_FINE && kv.second > 1)
+        for (int t : {2, 6, 7})
+          if (us[t] > 0 && std::find(order.begin(), order.end(), t) == order.end()) order.push_back(t);
       cls.push_back({kv.first, double(best_us) * kv.second, order});
     }
     std::stable_sort(cls.begin(), cls.end(), [](const Cls &x, const Cls &y) { return x.weight > y.weight; });

@@ -134,6 +134,11 @@ std::unique_ptr<CostModel> mlp_cost_model(const psc_mlp *m);  // mlp.hip
 
 SchedPlan build_plan(const Dag &g, int policy, const psc_sched_opts &o);
 
+// Positions and waits of an in-order plan whose ops (types, streams) are set, from the ops each op
+// depends on (smaller ids): a cross-stream dependency becomes a wait unless stream order or
+// another wait implies it.
+void assign_waits(SchedPlan &plan, const std::vector<std::vector<int32_t>> &deps);
+
 struct Device;  // HIP state, runtime.cpp
 
 }  // namespace psc

@@ -17,13 +17,19 @@ using Clock = std::chrono::steady_clock;
 constexpr auto kIdleSpin = std::chrono::milliseconds(20);  // spin before parking when idle
 }  // namespace
 
-Dispatcher::Dispatcher(const SchedPlan &plan, int32_t n_threads)
-    : plan_(plan), n_threads_(std::max<int32_t>(1, std::min(n_threads, plan.total_streams))) {
-  ops_of_.assign(n_threads_, {});
-  for (size_t o = 0; o < plan_.ops.size(); ++o)
-    ops_of_[plan_.ops[o].stream % n_threads_].push_back(static_cast<int32_t>(o));
-  published_.reset(new std::atomic<uint64_t>[plan_.ops.size() ? plan_.ops.size() : 1]);
-  for (size_t o = 0; o < plan_.ops.size(); ++o) published_[o].store(0, std::memory_order_relaxed);
+Dispatcher::Dispatcher(const std::vector<const SchedPlan *> &plans, int32_t n_threads)
+    : n_threads_(std::max<int32_t>(1, std::min(n_threads, plans[0]->total_streams))) {
+  for (const SchedPlan *plan : plans) {
+    Plan p;
+    p.plan = plan;
+    p.ops_of.assign(n_threads_, {});
+    const size_t n = plan->ops.size();
+    for (size_t o = 0; o < n; ++o) p.ops_of[plan->ops[o].stream % n_threads_].push_back(static_cast<int32_t>(o));
+    p.published.reset(new std::atomic<uint64_t>[n ? n : 1]);
+    for (size_t o = 0; o < n; ++o) p.published[o].store(0, std::memory_order_relaxed);
+    plans_.push_back(std::move(p));
+  }
+  now_ = &plans_[0];
   for (int32_t t = 1; t < n_threads_; ++t) workers_.emplace_back([this, t] { worker_main(t); });
 }
 
@@ -38,12 +44,14 @@ Dispatcher::~Dispatcher() {
 
 void Dispatcher::work(int32_t t) {
   const uint64_t g = gen_.load(std::memory_order_acquire);
+  const SchedPlan &plan = *now_->plan;
+  std::atomic<uint64_t> *published = now_->published.get();
   try {
-    for (int32_t o : ops_of_[t]) {
-      const Op &op = plan_.ops[o];
+    for (int32_t o : now_->ops_of[t]) {
+      const Op &op = plan.ops[o];
       for (int32_t w : op.waits) {
         // the awaited op's record must already be enqueued by its owner
-        while (published_[w].load(std::memory_order_acquire) < g) {
+        while (published[w].load(std::memory_order_acquire) < g) {
           if (abort_.load(std::memory_order_relaxed)) return;
           PSC_PAUSE();
         }
@@ -51,9 +59,9 @@ void Dispatcher::work(int32_t t) {
       }
       backend_->exec(o);
       if (op.recorded) backend_->record(o);
-      published_[o].store(g, std::memory_order_release);
+      published[o].store(g, std::memory_order_release);
     }
-    for (int32_t s = t; s < plan_.total_streams; s += n_threads_) backend_->stream_done(s);
+    for (int32_t s = t; s < plan.total_streams; s += n_threads_) backend_->stream_done(s);
   } catch (const Error &e) {
     std::lock_guard<std::mutex> lk(mu_);
     if (error_status_ == PSC_OK) {
@@ -77,6 +85,7 @@ void Dispatcher::worker_main(int32_t t) {
     // spin briefly for the next run, then park
     const auto t0 = Clock::now();
     while (gen_.load(std::memory_order_acquire) == seen) {
+      if (stop_.load(std::memory_order_relaxed)) return;
       if (Clock::now() - t0 > kIdleSpin) {
         std::unique_lock<std::mutex> lk(mu_);
         cv_.wait(lk, [&] { return stop_ || gen_.load(std::memory_order_acquire) != seen; });
@@ -84,10 +93,6 @@ void Dispatcher::worker_main(int32_t t) {
         break;
       }
       PSC_PAUSE();
-    }
-    {
-      std::lock_guard<std::mutex> lk(mu_);
-      if (stop_) return;
     }
     seen = gen_.load(std::memory_order_acquire);
     work(t);
@@ -98,8 +103,9 @@ void Dispatcher::worker_main(int32_t t) {
   }
 }
 
-void Dispatcher::run(Backend &b) {
+void Dispatcher::run(Backend &b, int32_t plan) {
   backend_ = &b;
+  now_ = &plans_[plan];
   abort_.store(false);
   error_status_ = PSC_OK;
   error_msg_.clear();

@@ -36,31 +36,37 @@ struct Backend {
 
 class Dispatcher {
  public:
-  Dispatcher(const SchedPlan &plan, int32_t n_threads);
+  // plans: the plans the threads may enqueue, one per run (all with the same streams)
+  Dispatcher(const std::vector<const SchedPlan *> &plans, int32_t n_threads);
+  Dispatcher(const SchedPlan &plan, int32_t n_threads)
+      : Dispatcher(std::vector<const SchedPlan *>{&plan}, n_threads) {}
   ~Dispatcher();
   Dispatcher(const Dispatcher &) = delete;
   Dispatcher &operator=(const Dispatcher &) = delete;
 
-  // Enqueues every op through `b`; returns once all threads have finished enqueueing.
-  void run(Backend &b);
+  // Enqueues every op of plans[plan] through `b`; returns once all threads have finished enqueueing.
+  void run(Backend &b, int32_t plan = 0);
   int32_t threads() const { return n_threads_; }
 
  private:
   void work(int32_t t);
   void worker_main(int32_t t);
 
-  const SchedPlan &plan_;
+  struct Plan {
+    const SchedPlan *plan;
+    std::vector<std::vector<int32_t>> ops_of;            // per thread: op ids in host order
+    std::unique_ptr<std::atomic<uint64_t>[]> published;  // per op: run generation it was issued in
+  };
   int32_t n_threads_;
-  std::vector<std::vector<int32_t>> ops_of_;  // per thread: op ids in host order
-  std::vector<int32_t> streams_of_thread_;
-  std::unique_ptr<std::atomic<uint64_t>[]> published_;  // per op: run generation it was issued in
+  std::vector<Plan> plans_;
+  Plan *now_ = nullptr;  // the plan of this run (written before the generation is)
   std::atomic<uint64_t> gen_{0};
   std::atomic<int32_t> finished_{0};
   std::atomic<bool> abort_{false};
   Backend *backend_ = nullptr;
   std::mutex mu_;
   std::condition_variable cv_, done_cv_;
-  bool stop_ = false;
+  std::atomic<bool> stop_{false};
   std::string error_msg_;
   psc_status error_status_ = PSC_OK;
   std::vector<std::thread> workers_;

@@ -51,36 +51,51 @@ std::vector<std::array<int, 6>> tile_cache_entries() {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Standalone kernels: one tile function call per 256-thread block.
+// Standalone kernels: one tile function call per 256-thread block.  A launch of several kernels
+// (group_launch) finds its block's kernel in the table: two scalar loads, one after the other,
+// before the block starts (~1 us, paid once per launch instead of a dispatch per kernel).
 // ---------------------------------------------------------------------------------------------
+template <typename Args>
+__device__ __forceinline__ int member_block(Args &p, int b) {
+  if (!p.map) return b;
+  const uint32_t m = p.map[b];
+  p = p.list[m >> 16];
+  return int(m & 0xffffu);
+}
+
 template <int BM, int BN, int BK, int WM, int WN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_f32_smem<BM, BN, BK>()];
-  gemm_f32_tile<BM, BN, BK, WM, WN, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  const int bid = member_block(p, xcd_tile(blockIdx.x, gridDim.x));
+  gemm_f32_tile<BM, BN, BK, WM, WN, OUT_BF16>(p, bid, smem);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_bf16_smem<BM, BN, BK>()];
-  gemm_bf16_tile<BM, BN, BK, WM, WN, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  const int bid = member_block(p, xcd_tile(blockIdx.x, gridDim.x));
+  gemm_bf16_tile<BM, BN, BK, WM, WN, OUT_BF16>(p, bid, smem);
 }
 
 template <int TM, int TN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_f32_splitk_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_f32_splitk_smem<TM, TN>()];
-  gemm_f32_splitk_tile<TM, TN, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  const int bid = member_block(p, xcd_tile(blockIdx.x, gridDim.x));
+  gemm_f32_splitk_tile<TM, TN, OUT_BF16>(p, bid, smem);
 }
 
 template <int TM, int TN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_bf16_splitk_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_bf16_splitk_smem<TM, TN>()];
-  gemm_bf16_splitk_tile<TM, TN, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  const int bid = member_block(p, xcd_tile(blockIdx.x, gridDim.x));
+  gemm_bf16_splitk_tile<TM, TN, OUT_BF16>(p, bid, smem);
 }
 
 template <int TM, int TN, int D, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_bf16_deep_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_bf16_deep_smem<TM, TN, D>()];
-  gemm_bf16_deep_tile<TM, TN, D, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  const int bid = member_block(p, xcd_tile(blockIdx.x, gridDim.x));
+  gemm_bf16_deep_tile<TM, TN, D, OUT_BF16>(p, bid, smem);
 }
 
 template <bool OUT_BF16>
@@ -99,36 +114,41 @@ __global__ __launch_bounds__(128 * WN) void gemm_bf16_w4_kernel(GemmArgs p) {
 template <int FN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_direct_smem<FN, false>()];
-  gemm_direct_tile<FN, false, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  const int bid = member_block(p, xcd_tile(blockIdx.x, gridDim.x));
+  gemm_direct_tile<FN, false, OUT_BF16>(p, bid, smem);
 }
 
 template <int FN, bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_bf16_direct_kernel(GemmArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[gemm_direct_smem<FN, true>()];
-  gemm_direct_tile<FN, true, OUT_BF16>(p, xcd_tile(blockIdx.x, gridDim.x), smem);
+  const int bid = member_block(p, xcd_tile(blockIdx.x, gridDim.x));
+  gemm_direct_tile<FN, true, OUT_BF16>(p, bid, smem);
 }
 
 template <int NV, bool IN_BF16, bool OUT_BF16, bool NT = false, int CW = 4>
 __global__ __launch_bounds__(256) void softmax_kernel(SoftmaxArgs p) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int row = member_block(p, blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (row < p.R) softmax_row<NV, IN_BF16, OUT_BF16, NT, CW>(p, row);
 }
 
 template <typename T, bool NT>
 __global__ __launch_bounds__(256) void transpose_vec_kernel(TransArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[64 * 65 * sizeof(T)];
-  transpose_tile_vec<T, NT>(p, blockIdx.x, smem);
+  const int bid = member_block(p, blockIdx.x);
+  transpose_tile_vec<T, NT>(p, bid, smem);
 }
 
 template <typename T, int TR, int TC, bool NT>
 __global__ __launch_bounds__(256) void transpose_rc_kernel(TransArgs p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[transpose_rc_smem<TR, TC, T>()];
-  transpose_rc_tile<T, TR, TC, NT>(p, blockIdx.x, smem);
+  const int bid = member_block(p, blockIdx.x);
+  transpose_rc_tile<T, TR, TC, NT>(p, bid, smem);
 }
 
 template <bool IN_BF16, bool OUT_BF16, bool NT = false>
 __global__ __launch_bounds__(256) void add_vec_kernel(AddArgs p) {
-  add_block_vec<IN_BF16, OUT_BF16, NT>(p, blockIdx.x);
+  const int bid = member_block(p, blockIdx.x);
+  add_block_vec<IN_BF16, OUT_BF16, NT>(p, bid);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -274,18 +294,103 @@ void make_fill(Launch &L, void *p, int64_t bytes, int bf16, uint32_t seed) {
   std::memcpy(L.args, &a, sizeof(a));
 }
 
+namespace {
+constexpr int kStaged[] = {1, 4, 5, 2}, kSplit[] = {6, 7, 8, 9, 10, 11, 12};
+
+// A tile at least twice as wide (or high) as the matrix works mostly on padding.
+bool wasteful(int t, int M, int N) { return kTiles[t].bm >= 2 * std::max(M, 16) || kTiles[t].bn >= 2 * std::max(N, 16); }
+}  // namespace
+
 int gemm_auto_tile(int M, int N, int K, int dtype) {
   // BF16 shapes of whole 256 x 256 tiles that fill the chip: the four-wavefront tile with direct
   // global-to-LDS copies (the launch factory still checks alignment).  Otherwise, enough output tiles to fill the chip: the
   // large-tile kernels; else the split-K kernels, which run four wavefronts per tile along K: the
   // largest tile that still yields >= 256 blocks (>= 128 when K is long), else the smallest tile.
   if (dtype == 1 && M % 256 == 0 && N % 256 == 0 && K % 64 == 0 && K > 0 && tiles_of(20, M, N) >= 256) return 20;
-  for (int t : {1, 4, 5, 2})
-    if (tiles_of(t, M, N) >= 256) return t;
+  for (int t : kStaged)
+    if (tiles_of(t, M, N) >= 256 && (!wasteful(t, M, N) || t == 2)) return t;
   const int64_t want = K >= 256 ? 128 : 256;
-  for (int t : {6, 7, 8, 9, 10, 11, 12})
+  for (int t : kSplit)
     if (tiles_of(t, M, N) >= want) return t;
   return 12;
+}
+
+int gemm_sum_order(int tile) {
+  // 1-5 walk K in steps of one matrix-core depth; 6-12 deal 64-deep (FP32: 32-deep) chunks to the
+  // wavefronts in turn and add the four sums in order; the others each have an order of their own
+  return tile >= 1 && tile <= 5 ? 1 : tile >= 6 && tile <= 12 ? 6 : tile;
+}
+
+int gemm_group_tile(const std::vector<GemmArgs> &args, int tile) {
+  // The largest tile of the same order that still yields kGroupBlocks blocks over all kernels.
+  constexpr int64_t kGroupBlocks = 384;
+  auto fits = [&](int t) {
+    int64_t n = 0;
+    bool waste = false;
+    for (const GemmArgs &a : args) {
+      n += tiles_of(t, a.M, a.N);
+      waste = waste || wasteful(t, a.M, a.N);
+    }
+    return n >= kGroupBlocks && !waste;
+  };
+  if (gemm_sum_order(tile) == 1) {
+    for (int t : kStaged)
+      if (fits(t)) return t;
+    return 2;
+  }
+  if (gemm_sum_order(tile) == 6) {
+    for (int t : kSplit)
+      if (fits(t)) return t;
+    return 12;
+  }
+  return tile;
+}
+
+namespace {
+size_t args_size(int kind) {
+  return kind == 0 ? sizeof(GemmArgs) : kind == 1 ? sizeof(TransArgs) : kind == 2 ? sizeof(SoftmaxArgs) : sizeof(AddArgs);
+}
+size_t up16(size_t n) { return (n + 15) & ~size_t(15); }
+
+template <typename Args>
+void point_at(Launch &L, const uint32_t *map, const void *list) {
+  Args a;
+  std::memcpy(&a, L.args, sizeof(a));
+  a.map = map;
+  a.list = static_cast<const Args *>(list);
+  std::memcpy(L.args, &a, sizeof(a));
+}
+}  // namespace
+
+bool groupable(const Launch &L) {
+  return L.kind >= 0 && !L.empty && L.grid.x < 2048 && !(L.kind == 0 && (L.tile == 16 || L.tile >= 20));
+}
+
+size_t group_table_bytes(const std::vector<Launch> &m) {
+  size_t blocks = 0;
+  for (const Launch &L : m) blocks += L.grid.x;
+  return up16(m.size() * args_size(m[0].kind)) + up16(4 * blocks);
+}
+
+Launch group_launch(const std::vector<Launch> &m, void *host_image, void *dev) {
+  const size_t as = args_size(m[0].kind), map_off = up16(m.size() * as);
+  auto *list = static_cast<unsigned char *>(host_image);
+  auto *map = reinterpret_cast<uint32_t *>(list + map_off);
+  size_t b = 0;
+  for (size_t i = 0; i < m.size(); ++i) {
+    std::memcpy(list + i * as, m[i].args, as);
+    for (uint32_t t = 0; t < m[i].grid.x; ++t) map[b++] = uint32_t(i) << 16 | t;
+  }
+  Launch L = m[0];
+  L.grid = dim3(unsigned(b), 1, 1);
+  const auto *dmap = reinterpret_cast<const uint32_t *>(static_cast<const unsigned char *>(dev) + map_off);
+  switch (L.kind) {
+    case 0: point_at<GemmArgs>(L, dmap, dev); break;
+    case 1: point_at<TransArgs>(L, dmap, dev); break;
+    case 2: point_at<SoftmaxArgs>(L, dmap, dev); break;
+    default: point_at<AddArgs>(L, dmap, dev); break;
+  }
+  return L;
 }
 
 bool make_gemm(Launch &L, GemmArgs a, int ab_dtype, int c_dtype, int tile) {
@@ -310,6 +415,7 @@ bool make_gemm(Launch &L, GemmArgs a, int ab_dtype, int c_dtype, int tile) {
   L.shmem = 0;
   L.empty = a.M == 0 || a.N == 0;
   L.tile = tile;
+  L.kind = 0;
   set_args(L, a);
   return true;
 }
@@ -340,6 +446,7 @@ bool make_softmax(Launch &L, SoftmaxArgs a, int in_dtype, int out_dtype) {
   L.block = dim3(256, 1, 1);
   L.shmem = 0;
   L.empty = a.R == 0 || a.C == 0;
+  L.kind = 2;
   set_args(L, a);
   return true;
 }
@@ -369,6 +476,7 @@ bool make_transpose(Launch &L, TransArgs a, int dtype, int tile) {
   L.block = dim3(256, 1, 1);
   L.shmem = 0;
   L.empty = a.R == 0 || a.C == 0;
+  L.kind = 1;
   set_args(L, a);
   return true;
 }
@@ -382,6 +490,7 @@ bool make_add(Launch &L, AddArgs a, int in_dtype, int out_dtype) {
   L.block = dim3(256, 1, 1);
   L.shmem = 0;
   L.empty = a.R == 0 || a.C == 0;
+  L.kind = 3;
   set_args(L, a);
   return true;
 }

@@ -18,6 +18,10 @@ struct GemmArgs {           // C (M x N) = alpha * A (M x K) * B (K x N), row-ma
   float alpha;
   int32_t tiles_n;          // filled by make_gemm
   int32_t pad;
+  // a launch of several kernels (group_launch), here and in the records below: block b of the
+  // grid runs block map[b] % 65536 of kernel map[b] / 65536 of the list; map = nullptr otherwise
+  const uint32_t *map;
+  const GemmArgs *list;
 };
 
 struct SoftmaxArgs {        // Y (R x C) = row-softmax(X)
@@ -25,6 +29,8 @@ struct SoftmaxArgs {        // Y (R x C) = row-softmax(X)
   void *Y;
   int64_t ldx, ldy;
   int32_t R, C;
+  const uint32_t *map;
+  const SoftmaxArgs *list;
 };
 
 struct TransArgs {          // B (C x R) = A (R x C)^T
@@ -32,6 +38,8 @@ struct TransArgs {          // B (C x R) = A (R x C)^T
   void *B;
   int64_t lda, ldb;
   int32_t R, C;
+  const uint32_t *map;
+  const TransArgs *list;
 };
 
 struct AddArgs {            // Cp (R x C) = A + B
@@ -40,6 +48,8 @@ struct AddArgs {            // Cp (R x C) = A + B
   void *Cp;
   int64_t lda, ldb, ldc;
   int32_t R, C;
+  const uint32_t *map;
+  const AddArgs *list;
 };
 
 // A prepared kernel launch: hipLaunchKernel(func, grid, block, {args}, shmem, stream).
@@ -49,6 +59,7 @@ struct Launch {
   unsigned shmem = 0;
   bool empty = false;       // nothing to compute (an empty operand): skip the launch
   int tile = 0;             // GEMM tile configuration used
+  int kind = -1;            // psc_kind of a kernel of the DAG, -1 for marks and fills
   alignas(16) unsigned char args[96];
 };
 
@@ -58,6 +69,20 @@ bool make_softmax(Launch &L, SoftmaxArgs a, int in_dtype, int out_dtype);
 bool make_transpose(Launch &L, TransArgs a, int dtype, int tile = 0);
 bool make_add(Launch &L, AddArgs a, int in_dtype, int out_dtype);
 int gemm_num_tiles();
+
+// Whether a launch may run together with others of the same kernel function: not one that is
+// empty, that fills the GPU several times over by itself, or whose block order needs its grid.
+bool groupable(const Launch &L);
+// Bytes of the table a launch of these kernels needs in device memory (16-byte multiple), its
+// host image, and the launch itself, with the table at `dev` (16-byte aligned).  All members have
+// one kernel function.
+size_t group_table_bytes(const std::vector<Launch> &members);
+Launch group_launch(const std::vector<Launch> &members, void *host_image, void *dev);
+// The tile for a launch of several GEMMs whose tile is automatic: `tile` is what one of them
+// takes alone.  Only tiles that sum K in the same order are considered, so the results do not
+// depend on what a kernel is launched with.  gemm_sum_order: equal for tiles of one order.
+int gemm_group_tile(const std::vector<GemmArgs> &args, int tile);
+int gemm_sum_order(int tile);
 // One-thread kernel that stores the device wall clock (wall_clock64) to *slot.
 void make_mark(Launch &L, uint64_t *slot);
 // Fills bytes / 4 32-bit words at p with values uniform in [-1, 1) from a hash of (index, seed):

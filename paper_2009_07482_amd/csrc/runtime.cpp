@@ -17,12 +17,14 @@
 #include <thread>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <queue>
 #include <string>
 
 #include "aql.hpp"
 #include "core.hpp"
 #include "dispatch.hpp"
+#include "group.hpp"
 #include "kernels.hpp"
 #include "persistent.hpp"
 
@@ -94,12 +96,35 @@ struct ExecCopy {
   int64_t width = 0;  // bytes per row
 };
 
+// One of the plans a schedule runs: its launches (per op.kernel), events and dispatchers.  A
+// PSC_FINE schedule has two when it groups launches, for runs without and with host copies.
+struct Runner {
+  SchedPlan own;                      // a grouped plan
+  const SchedPlan *plan = nullptr;    // &own, or the schedule's plan
+  const std::vector<Launch> *launch = nullptr;
+  std::vector<Launch> own_launch;
+  std::vector<int32_t> op_of;         // per op: the op of the schedule's plan (grouped plans)
+  std::vector<hipEvent_t> op_ev;      // per op that another stream waits for
+  void *table = nullptr;              // device memory: the launch groups' argument lists and maps
+  int32_t disp_plan = 0;              // its index in the dispatcher
+  std::unique_ptr<AqlSchedule> aql;   // PSC_DISPATCH_AQL: signals, argument records
+
+  Runner() = default;
+  Runner(const Runner &) = delete;
+  Runner &operator=(const Runner &) = delete;
+  ~Runner() {
+    aql.reset();                      // (waits for its own run)
+    for (hipEvent_t e : op_ev)
+      if (e) (void)hipEventDestroy(e);
+    if (table) (void)hipFree(table);
+  }
+};
+
 struct Device {
   int device = 0;
   void *arena = nullptr;
   std::vector<char *> base;  // per buffer id (roots only): device storage
   std::vector<hipStream_t> streams;
-  std::vector<hipEvent_t> op_ev;
   std::vector<hipEvent_t> join_ev;
   hipEvent_t start = nullptr, end = nullptr;
   bool in_flight = false;          // a timed-out run may still execute (wait for `end` first)
@@ -116,8 +141,10 @@ struct Device {
   Launch mark_start;
   std::vector<Launch> mark_after;  // per kernel; .func == nullptr unless an END kernel
   bool have_marks = false;
-  std::unique_ptr<Dispatcher> disp;
-  std::unique_ptr<AqlSchedule> aql;  // PSC_DISPATCH_AQL: queues, signals, argument records
+  std::unique_ptr<Runner> plain;     // the schedule's plan as it is, or with launch groups:
+  std::unique_ptr<Runner> grouped[2];  // [1] for runs with host copies, [0] without
+  std::unique_ptr<Dispatcher> disp;  // enqueueing threads, for every plan
+  AqlSchedule *aql_run = nullptr;    // the AQL plan of the last run
   std::unique_ptr<struct DynState> dyn;  // PSC_EAGER / PSC_HEFT: the run-time scheduler's state
   // PSC_DEVICE executor
   void *exec_mem = nullptr;
@@ -134,8 +161,9 @@ struct Device {
 
   ~Device() {
     if (in_flight && end) (void)hipEventSynchronize(end);  // a timed-out run still executing
-    aql.reset();                                           // (waits for its own run the same way)
     disp.reset();
+    plain.reset();                                         // (AQL plans wait for their own runs)
+    for (auto &r : grouped) r.reset();
     if (exec_mem) (void)hipFree(exec_mem);
     if (exec_mem_copy) (void)hipFree(exec_mem_copy);
     if (marks) (void)hipFree(marks);
@@ -143,8 +171,6 @@ struct Device {
     if (h_copy_nodes) (void)hipHostFree(h_copy_nodes);
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
-    for (hipEvent_t e : op_ev)
-      if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : join_ev)
       if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : t0)
@@ -571,6 +597,96 @@ void prepare_executor(const Dag &g, const SchedPlan &plan, int32_t per_cu_cap, D
   }
 }
 
+// Launch groups serve the fine schedules whose kernels need not be told apart: not runs that record
+// every op or mark every component, not the injected faults (an op prefix), graphs or
+// out-of-order queues; and not PSC_COARSE, the baseline of one kernel at a time.
+bool groups_launches(const psc_sched &s) {
+  return s.policy == PSC_FINE && !s.opts.record_ops && !s.opts.mark_components && !s.opts.fault_inject_op &&
+         !s.opts.use_graph && !s.plan.out_of_order;
+}
+
+// A launch stops taking kernels at this many workgroups: eight per CU keep the GPU busy, and what
+// waits for the launch's first kernels does not wait for a longer one.
+constexpr int64_t kGroupMaxBlocks = 2048;
+
+// The grouped plan of a schedule with its launches.  GEMMs whose tile is automatic are grouped by
+// summation order and take the tile that suits the group; everything else by kernel function.
+std::unique_ptr<Runner> make_grouped(const psc_sched &s, const Device &d, bool copies) {
+  const Dag &g = s.dag->g;
+  const size_t nk = g.kers.size();
+  std::vector<int32_t> key(nk, -1);
+  std::vector<int64_t> blocks(nk, 0);
+  std::vector<char> automatic(nk, 0);
+  std::map<std::vector<int64_t>, int32_t> ids;
+  for (size_t k = 0; k < nk; ++k) {
+    const Launch &L = d.launch[k];
+    const Kernel &ker = g.kers[k];
+    blocks[k] = L.grid.x;
+    if (!groupable(L)) continue;
+    std::vector<int64_t> v{L.kind, int64_t(reinterpret_cast<intptr_t>(L.func))};
+    if (ker.kind == PSC_GEMM && ker.tile <= 0) {
+      GemmArgs a;
+      memcpy(&a, L.args, sizeof(a));
+      const int ab = g.bufs[ker.ins[0]].dtype, c = g.bufs[ker.outs[0]].dtype;
+      automatic[k] = tile_cache_get(a.M, a.N, a.K, ab, c) == 0;
+      if (automatic[k]) v = {-1, ab, c, gemm_sum_order(L.tile)};
+    }
+    key[k] = ids.emplace(v, int32_t(ids.size())).first->second;
+  }
+  GroupedPlan gp = group_plan(g, s.plan, key, blocks, kGroupMaxBlocks, copies, s.opts.copy_roots != 0);
+  auto r = std::make_unique<Runner>();
+  std::vector<std::vector<Launch>> members(gp.units.size());
+  size_t bytes = 0;
+  for (size_t u = 0; u < gp.units.size(); ++u) {
+    const std::vector<int32_t> &ks = gp.units[u];
+    for (int32_t k : ks) members[u].push_back(d.launch[k]);
+    if (ks.size() < 2) continue;
+    if (automatic[ks[0]]) {
+      std::vector<GemmArgs> as(ks.size());
+      for (size_t i = 0; i < ks.size(); ++i) memcpy(&as[i], members[u][i].args, sizeof(GemmArgs));
+      const int t = gemm_group_tile(as, members[u][0].tile);
+      const Kernel &ker = g.kers[ks[0]];
+      for (size_t i = 0; i < ks.size(); ++i)
+        if (!make_gemm(members[u][i], as[i], g.bufs[ker.ins[0]].dtype, g.bufs[ker.outs[0]].dtype, t))
+          fail(PSC_ERR_UNSUPPORTED, "no kernel instance for '" + g.kers[ks[i]].name + "'");
+    }
+    bytes += group_table_bytes(members[u]);
+  }
+  std::vector<unsigned char> host(bytes);
+  if (bytes) {
+    hipError_t e = hipMalloc(&r->table, bytes);
+    if (e != hipSuccess) fail(PSC_ERR_OOM, std::string("hipMalloc (launch groups): ") + hipGetErrorString(e));
+  }
+  size_t off = 0;
+  for (const std::vector<Launch> &m : members) {
+    if (m.size() < 2) {
+      r->own_launch.push_back(m[0]);
+      continue;
+    }
+    r->own_launch.push_back(group_launch(m, host.data() + off, static_cast<char *>(r->table) + off));
+    off += group_table_bytes(m);
+  }
+  if (bytes) PSC_HIP(hipMemcpy(r->table, host.data(), bytes, hipMemcpyHostToDevice));
+  r->own = std::move(gp.plan);
+  r->op_of = std::move(gp.op_of);
+  r->plan = &r->own;
+  r->launch = &r->own_launch;
+  return r;
+}
+
+// Events, or AQL signals and records, of a plan.
+void finish_runner(const psc_sched &s, const Device &d, Runner &r, const std::shared_ptr<AqlQueues> &queues) {
+  const SchedPlan &plan = *r.plan;
+  r.op_ev.assign(plan.ops.size(), nullptr);
+  if (!queues)
+    for (size_t i = 0; i < plan.ops.size(); ++i)
+      if (plan.ops[i].recorded || (plan.dynamic && plan.ops[i].type == PSC_OP_H2D))
+        PSC_HIP(hipEventCreateWithFlags(&r.op_ev[i], hipEventDisableTiming));
+  if (queues)
+    r.aql = std::make_unique<AqlSchedule>(d.device, queues, plan, *r.launch, d.mark_after,
+                                          d.marks ? &d.mark_start : nullptr, s.opts.record_ops != 0);
+}
+
 }  // namespace
 
 void prepare(psc_sched &s) {
@@ -602,11 +718,6 @@ void prepare(psc_sched &s) {
   d->streams.assign(dev_mode ? 1 : s.plan.total_streams, nullptr);
   for (auto &st : d->streams) PSC_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
   const bool aql_mode = !dev_mode && s.opts.dispatch == PSC_DISPATCH_AQL;
-  d->op_ev.assign(s.plan.ops.size(), nullptr);
-  if (!dev_mode && !aql_mode)
-    for (size_t i = 0; i < s.plan.ops.size(); ++i)
-      if (s.plan.ops[i].recorded || (s.plan.dynamic && s.plan.ops[i].type == PSC_OP_H2D))
-        PSC_HIP(hipEventCreateWithFlags(&d->op_ev[i], hipEventDisableTiming));
   d->join_ev.assign(d->streams.size(), nullptr);
   for (auto &e : d->join_ev) PSC_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   PSC_HIP(hipEventCreate(&d->start));
@@ -635,16 +746,29 @@ void prepare(psc_sched &s) {
     else
       (void)hipGetLastError();
   }
+  const int32_t nt = s.opts.host_threads > 0 ? s.opts.host_threads : s.plan.total_streams;
   if (dev_mode) {
     prepare_executor(g, s.plan, s.opts.exec_per_cu, *d);
-  } else if (s.plan.dynamic) {
-    d->dyn = std::make_unique<DynState>();
+  } else if (groups_launches(s)) {
+    for (int copies = 0; copies < 2; ++copies) d->grouped[copies] = make_grouped(s, *d, copies != 0);
+    std::shared_ptr<AqlQueues> queues;
+    if (aql_mode) {
+      queues = std::make_shared<AqlQueues>(
+          d->device, std::vector<const SchedPlan *>{d->grouped[0]->plan, d->grouped[1]->plan}, false);
+    }
+    for (auto &r : d->grouped) finish_runner(s, *d, *r, queues);
+    d->grouped[1]->disp_plan = 1;
+    d->disp = std::make_unique<Dispatcher>(std::vector<const SchedPlan *>{d->grouped[0]->plan, d->grouped[1]->plan}, nt);
   } else {
-    const int32_t nt = s.opts.host_threads > 0 ? s.opts.host_threads : s.plan.total_streams;
-    d->disp = std::make_unique<Dispatcher>(s.plan, nt);
+    if (s.plan.dynamic) d->dyn = std::make_unique<DynState>();
+    d->plain = std::make_unique<Runner>();
+    d->plain->plan = &s.plan;
+    d->plain->launch = &d->launch;
+    std::shared_ptr<AqlQueues> queues;
     if (aql_mode)
-      d->aql = std::make_unique<AqlSchedule>(d->device, s.plan, d->launch, d->mark_after,
-                                             d->marks ? &d->mark_start : nullptr, s.opts.record_ops != 0);
+      queues = std::make_shared<AqlQueues>(d->device, std::vector<const SchedPlan *>{&s.plan}, s.opts.record_ops != 0);
+    finish_runner(s, *d, *d->plain, queues);
+    if (!s.plan.dynamic) d->disp = std::make_unique<Dispatcher>(s.plan, nt);
   }
   s.dev = std::move(d);
 }
@@ -709,23 +833,23 @@ void do_copy(const CopyDesc &c, hipStream_t st) {
 }
 
 struct HipBackend final : Backend {
-  psc_sched &s;
   Device &d;
-  const std::vector<CopyDesc> &cd;
+  const Runner &r;
+  const std::vector<CopyDesc> &cd;  // per op of the runner's plan
   bool timed;
-  HipBackend(psc_sched &s_, const std::vector<CopyDesc> &cd_, bool timed_)
-      : s(s_), d(*s_.dev), cd(cd_), timed(timed_) {}
-  hipStream_t st(int32_t op) const { return d.streams[s.plan.ops[op].stream]; }
-  void wait(int32_t op, int32_t awaited) override { PSC_HIP(hipStreamWaitEvent(st(op), d.op_ev[awaited], 0)); }
+  HipBackend(Device &d_, const Runner &r_, const std::vector<CopyDesc> &cd_, bool timed_)
+      : d(d_), r(r_), cd(cd_), timed(timed_) {}
+  hipStream_t st(int32_t op) const { return d.streams[r.plan->ops[op].stream]; }
+  void wait(int32_t op, int32_t awaited) override { PSC_HIP(hipStreamWaitEvent(st(op), r.op_ev[awaited], 0)); }
   void exec(int32_t o) override {
-    const Op &op = s.plan.ops[o];
+    const Op &op = r.plan->ops[o];
     if (timed) PSC_HIP(hipEventRecord(d.t0[o], st(o)));
-    if (op.type == PSC_OP_KERNEL) launch(d.launch[op.kernel], st(o));
+    if (op.type == PSC_OP_KERNEL) launch((*r.launch)[op.kernel], st(o));
     else do_copy(cd[o], st(o));
     if (timed) PSC_HIP(hipEventRecord(d.t1[o], st(o)));
     if (op.type == PSC_OP_KERNEL && d.marks && d.mark_after[op.kernel].func) launch(d.mark_after[op.kernel], st(o));
   }
-  void record(int32_t o) override { PSC_HIP(hipEventRecord(d.op_ev[o], st(o))); }
+  void record(int32_t o) override { PSC_HIP(hipEventRecord(r.op_ev[o], st(o))); }
   void stream_done(int32_t stream) override {
     if (stream != 0) PSC_HIP(hipEventRecord(d.join_ev[stream], d.streams[stream]));
   }
@@ -816,7 +940,7 @@ namespace {
 [[noreturn]] void run_fault_prefix(psc_sched &s, const std::vector<CopyDesc> &cd) {
   Device &d = *s.dev;
   const int32_t k = s.opts.fault_inject_op - 1;
-  HipBackend backend(s, cd, false);
+  HipBackend backend(d, *d.plain, cd, false);
   PSC_HIP(hipEventRecord(d.start, d.streams[0]));
   fork_streams(d, d.start);
   for (int32_t o = 0; o < k; ++o) {
@@ -956,11 +1080,11 @@ void run_dynamic(psc_sched &s, const std::vector<CopyDesc> &cd, bool timed) {
           if (uo < 0) continue;
           if (up_stream[uo] < 0) {
             timed_op(uo, hs, [&] { do_copy(cd[uo], hs); });
-            PSC_HIP(hipEventRecord(d.op_ev[uo], hs));
+            PSC_HIP(hipEventRecord(d.plain->op_ev[uo], hs));
             up_stream[uo] = q;
             new_stream[uo] = q, new_pos[uo] = pos[q]++, new_order[uo] = order++;
           } else if (up_stream[uo] != q) {
-            PSC_HIP(hipStreamWaitEvent(hs, d.op_ev[uo], 0));
+            PSC_HIP(hipStreamWaitEvent(hs, d.plain->op_ev[uo], 0));
             new_waits[kop].push_back(uo);
           }
         }
@@ -1012,7 +1136,7 @@ void run(psc_sched &s, const psc_host_io *io, int32_t n_io, psc_run_stats *stats
   Device &d = *s.dev;
   PSC_HIP(hipSetDevice(d.device));
   if (d.in_flight) {  // the previous run timed out: its work must end before buffers are reused
-    if (d.aql) (void)d.aql->wait_end(0);
+    if (d.aql_run) (void)d.aql_run->wait_end(0);
     else PSC_HIP(hipEventSynchronize(d.end));
     d.in_flight = false;
   }
@@ -1021,6 +1145,18 @@ void run(psc_sched &s, const psc_host_io *io, int32_t n_io, psc_run_stats *stats
   const bool timed = s.opts.record_ops != 0;
   hipStream_t s0 = d.streams[0];
   double host_ms = 0;
+  // the plan this run takes, and its copies
+  Runner *r = d.plain.get();
+  std::vector<CopyDesc> own_cd;
+  const std::vector<CopyDesc> *rcd = &cd;
+  if (d.grouped[0]) {
+    bool any = false;
+    for (const CopyDesc &c : cd) any = any || c.active;
+    r = d.grouped[any ? 1 : 0].get();
+    for (int32_t o : r->op_of) own_cd.push_back(cd[o]);
+    rcd = &own_cd;
+  }
+  d.aql_run = r ? r->aql.get() : nullptr;
   if (s.plan.device) {
     const auto h0 = std::chrono::steady_clock::now();
     // The executor runs each upload and read-back whose host memory the device can address
@@ -1079,25 +1215,25 @@ void run(psc_sched &s, const psc_host_io *io, int32_t n_io, psc_run_stats *stats
     const auto h0 = std::chrono::steady_clock::now();
     run_dynamic(s, cd, timed);
     host_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - h0).count();
-  } else if (d.aql) {
-    std::vector<AqlCopy> ac(cd.size());
-    for (size_t o = 0; o < cd.size(); ++o) {
-      const CopyDesc &c = cd[o];
+  } else if (d.aql_run) {
+    std::vector<AqlCopy> ac(rcd->size());
+    for (size_t o = 0; o < rcd->size(); ++o) {
+      const CopyDesc &c = (*rcd)[o];
       ac[o] = AqlCopy{c.active, c.kind == hipMemcpyHostToDevice, c.dst, c.src, c.dpitch, c.spitch, c.width, c.height};
     }
     const auto h0 = std::chrono::steady_clock::now();
-    d.aql->begin(ac);
-    AqlBackend backend(*d.aql);
+    d.aql_run->begin(ac);
+    AqlBackend backend(*d.aql_run);
     try {
-      d.disp->run(backend);
+      d.disp->run(backend, r->disp_plan);
     } catch (...) {
       // nothing may wait forever on an op that was never enqueued: complete those, join, drain
-      d.aql->release_undispatched();
-      d.aql->end();
-      (void)d.aql->wait_end(0);
+      d.aql_run->release_undispatched();
+      d.aql_run->end();
+      (void)d.aql_run->wait_end(0);
       throw;
     }
-    d.aql->end();
+    d.aql_run->end();
     host_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - h0).count();
   } else if (s.opts.use_graph) {
     std::vector<const void *> key;
@@ -1118,20 +1254,20 @@ void run(psc_sched &s, const psc_host_io *io, int32_t n_io, psc_run_stats *stats
     if (d.marks) launch(d.mark_start, s0);
     PSC_HIP(hipEventRecord(d.start, s0));
     fork_streams(d, d.start);
-    HipBackend backend(s, cd, timed);
-    d.disp->run(backend);
+    HipBackend backend(d, *r, *rcd, timed);
+    d.disp->run(backend, r->disp_plan);
     join_streams(d);
     PSC_HIP(hipEventRecord(d.end, s0));
     host_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - h0).count();
   }
   float ms = 0;
-  if (d.aql) {
-    if (!d.aql->wait_end(s.opts.timeout_ms)) {
+  if (d.aql_run) {
+    if (!d.aql_run->wait_end(s.opts.timeout_ms)) {
       d.in_flight = true;
       fail(PSC_ERR_TIMEOUT, "run not finished within timeout_ms = " + std::to_string(s.opts.timeout_ms) +
                                 " (still executing; the next psc_run or psc_sched_destroy waits for it)");
     }
-    ms = float(d.aql->makespan_ms());
+    ms = float(d.aql_run->makespan_ms());
   } else {
     wait_end(s);
     PSC_HIP(hipEventElapsedTime(&ms, d.start, d.end));
@@ -1170,9 +1306,9 @@ void run(psc_sched &s, const psc_host_io *io, int32_t n_io, psc_run_stats *stats
       }
     }
     d.have_times = true;
-  } else if (timed && d.aql) {
+  } else if (timed && d.aql_run) {
     std::vector<float> a, b;
-    d.aql->op_times(a, b);
+    d.aql_run->op_times(a, b);
     d.times.resize(s.plan.ops.size());
     d.active.assign(s.plan.ops.size(), 0);
     for (size_t o = 0; o < s.plan.ops.size(); ++o) {
@@ -1207,7 +1343,7 @@ void run(psc_sched &s, const psc_host_io *io, int32_t n_io, psc_run_stats *stats
     }
     stats->n_streams = s.plan.total_streams;
     stats->graph = s.opts.use_graph != 0;
-    stats->aql_packets = d.aql ? d.aql->packets_last_run() : 0;
+    stats->aql_packets = d.aql_run ? d.aql_run->packets_last_run() : 0;
   }
 }
 

@@ -106,10 +106,17 @@ void map_eft(const Dag &g, int32_t S, CostModel &cost, std::vector<int32_t> &ord
     // myopic: a model that has learned how much a kernel stretches beside busy streams would
     // make every kernel wait for a free stream -- serialise -- without counting what waiting
     // costs the rest of the schedule.)  The chosen stream then stays busy for the contended time.
-    int32_t best = 0;
+    // Only the stream of the predecessor that finishes last starts without a cross-stream wait for
+    // it; and kernels of a level that lie on one stream share launches, which chains kept on their
+    // streams preserve.
+    constexpr double kWaitUs = 3.0;
+    int32_t best = 0, last_pred = -1;
+    for (int32_t p : g.pred[k])
+      if (last_pred < 0 || finish[p] > finish[last_pred]) last_pred = p;
     double best_st = 1e300, best_f = 1e300;
     for (int32_t s = 0; s < S; ++s) {
-      const double st = std::max(avail[s] + up, dep_ready);
+      const bool follows = last_pred < 0 || stream_of[last_pred] == s;
+      const double st = std::max(avail[s] + up, dep_ready + (follows ? 0.0 : kWaitUs));
       int32_t busy = 0;
       for (int32_t q = 0; q < S; ++q) busy += q != s && avail[q] > st;
       const double f = st + w(k, busy);
@@ -252,6 +259,40 @@ SchedPlan build_dynamic_plan(const Dag &g, int policy, const psc_sched_opts &o) 
   return plan;
 }
 
+void assign_waits(SchedPlan &plan, const std::vector<std::vector<int32_t>> &deps) {
+  const int32_t T = plan.total_streams;
+  const size_t n = plan.ops.size();
+  std::vector<int32_t> pos(T, 0);
+  for (Op &op : plan.ops) op.pos = pos[op.stream]++;
+  // waits: vector clocks over streams; vc[i][t] = last position on stream t known to precede op i
+  std::vector<int32_t> vc(n * T, -1);
+  std::vector<int32_t> last_on(T, -1);
+  std::vector<int32_t> cur(T);
+  for (size_t i = 0; i < n; ++i) {
+    Op &op = plan.ops[i];
+    const int32_t prev = last_on[op.stream];
+    if (prev >= 0)
+      std::copy(vc.begin() + prev * T, vc.begin() + (prev + 1) * T, cur.begin());
+    else
+      std::fill(cur.begin(), cur.end(), -1);
+    std::vector<int32_t> d = deps[i];
+    std::sort(d.begin(), d.end(), std::greater<int32_t>());  // later ops first
+    d.erase(std::unique(d.begin(), d.end()), d.end());
+    for (int32_t dep : d) {
+      const Op &p = plan.ops[dep];
+      if (p.stream == op.stream) continue;  // stream order covers it
+      if (cur[p.stream] >= p.pos) continue;  // implied by an earlier wait
+      op.waits.push_back(dep);
+      plan.ops[dep].recorded = true;
+      for (int32_t t = 0; t < T; ++t) cur[t] = std::max(cur[t], vc[dep * T + t]);
+    }
+    std::sort(op.waits.begin(), op.waits.end());
+    cur[op.stream] = op.pos;
+    std::copy(cur.begin(), cur.end(), vc.begin() + i * T);
+    last_on[op.stream] = static_cast<int32_t>(i);
+  }
+}
+
 SchedPlan build_plan(const Dag &g, int policy, const psc_sched_opts &o) {
   if (policy == PSC_DEVICE) return build_device_plan(g, o.copy_roots != 0);
   if (policy == PSC_EAGER || policy == PSC_HEFT) return build_dynamic_plan(g, policy, o);
@@ -333,11 +374,9 @@ SchedPlan build_plan(const Dag &g, int policy, const psc_sched_opts &o) {
     for (int32_t b : g.iso_out[k]) emit(PSC_OP_D2H, -1, b, read_s >= 0 ? read_s : s, {kop});
   }
 
-  const int32_t T = plan.total_streams;
-  const size_t n = plan.ops.size();
   if (ooo) {
     // stream order implies nothing: every direct precedence is a wait
-    for (size_t i = 0; i < n; ++i) {
+    for (size_t i = 0; i < plan.ops.size(); ++i) {
       std::vector<int32_t> d = deps[i];
       std::sort(d.begin(), d.end());
       d.erase(std::unique(d.begin(), d.end()), d.end());
@@ -346,33 +385,7 @@ SchedPlan build_plan(const Dag &g, int policy, const psc_sched_opts &o) {
     }
     return plan;
   }
-  // waits: vector clocks over streams; vc[i][t] = last position on stream t known to precede op i
-  std::vector<int32_t> vc(n * T, -1);
-  std::vector<int32_t> last_on(T, -1);
-  std::vector<int32_t> cur(T);
-  for (size_t i = 0; i < n; ++i) {
-    Op &op = plan.ops[i];
-    const int32_t prev = last_on[op.stream];
-    if (prev >= 0)
-      std::copy(vc.begin() + prev * T, vc.begin() + (prev + 1) * T, cur.begin());
-    else
-      std::fill(cur.begin(), cur.end(), -1);
-    std::vector<int32_t> d = deps[i];
-    std::sort(d.begin(), d.end(), std::greater<int32_t>());  // later ops first
-    d.erase(std::unique(d.begin(), d.end()), d.end());
-    for (int32_t dep : d) {
-      const Op &p = plan.ops[dep];
-      if (p.stream == op.stream) continue;  // stream order covers it
-      if (cur[p.stream] >= p.pos) continue;  // implied by an earlier wait
-      op.waits.push_back(dep);
-      plan.ops[dep].recorded = true;
-      for (int32_t t = 0; t < T; ++t) cur[t] = std::max(cur[t], vc[dep * T + t]);
-    }
-    std::sort(op.waits.begin(), op.waits.end());
-    cur[op.stream] = op.pos;
-    std::copy(cur.begin(), cur.end(), vc.begin() + i * T);
-    last_on[op.stream] = static_cast<int32_t>(i);
-  }
+  assign_waits(plan, deps);
   return plan;
 }
 
