@@ -282,22 +282,73 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, int bid, unsign
     }
 }
 
+// Eight consecutive bf16 at p[0..8), element e only if ok_e(e), packed into one uint4.
+template <typename F>
+__device__ __forceinline__ uint4 pack8_guarded(const uint16_t *p, F ok_e) {
+  uint32_t w[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t lo = ok_e(2 * q) ? uint32_t(p[2 * q]) : 0u;
+    const uint32_t hi = ok_e(2 * q + 1) ? uint32_t(p[2 * q + 1]) : 0u;
+    w[q] = lo | (hi << 16);
+  }
+  return uint4{w[0], w[1], w[2], w[3]};
+}
+
+// ---------------------------------------------------------------------------------------------
+// BF16 operands in LDS.  A lies as in memory, rows of k (pitch kAPitch elements); so does B, rows
+// of n, written with 16-byte stores.  The matrix core needs eight consecutive k of one B column per
+// lane, and gfx950's transposing LDS read (ds_read_b64_tr_b16) delivers them: within each aligned
+// group of 16 lanes, the lanes' 4-wide reads form a 16 x 4 matrix M and lane j receives
+// M[j/4 + 4e][j%4], e < 4.  So when lane r of the group reads the four columns 4 (r%4) .. + 3 of B
+// row k0 + r/4, lane j gets B[k0 + e][j]; two such reads (k0 and k0 + 4) give the eight.
+// B transposed on the way into LDS instead took 64 four-byte stores per lane and 64-deep chunk of a
+// 64-wide tile, each a 4-way bank conflict, as many byte permutes, and registers (64 x 64 K-split
+// tile: 316 against 220, one wavefront per SIMD against two).  Measured: 4-layer 1024 BF16
+// attention 622 -> 485 us on queues and 916 -> 777 us on the device executor, a batch of sixteen
+// BF16 DAGs 1.58 -> 1.25 ms.
+// Pitches: four rows of 16 columns, which 16 lanes read together, fall on distinct banks.
+// ---------------------------------------------------------------------------------------------
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+constexpr int kAPitch = 80;
+template <int TN>
+constexpr int b_pitch() {
+  return TN == 16 ? 24 : TN == 32 ? 48 : TN == 64 ? 72 : TN + 16;
+}
+// This lane's offset into a B region for the 16-column block at column 0 and the slice at row 0.
+template <int TN>
+__device__ __forceinline__ int b_frag_lane(int lane) {
+  return (8 * (lane >> 4) + ((lane & 15) >> 2)) * b_pitch<TN>() + 4 * (lane & 3);
+}
+template <int TN>
+__device__ __forceinline__ bf16x8 b_frag(const uint16_t *q) {
+  const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4 *)(q));
+  const shortx4 hi =
+      __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4 *)(q + 4 * b_pitch<TN>()));
+  const short v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  bf16x8 f;
+  memcpy(&f, v, 16);
+  return f;
+}
+
 template <int BM, int BN, int BK>
 constexpr int gemm_bf16_smem() {
-  return 2 * (BM + BN) * (BK + 8);
+  return 2 * (BM * kAPitch + BK * b_pitch<BN>());
 }
 
 template <int BM, int BN, int BK, int WM, int WN, bool OUT_BF16>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &p, int bid, unsigned char *smem) {
-  static_assert(BK % 32 == 0, "BK must be a multiple of the 32-deep matrix-core step");
+  static_assert(BK == 64, "a K step is 64 deep");
   static_assert(64 * (BM / WM) * (BN / WN) == 256, "four wavefronts per block");
   constexpr int NWN = BN / WN, NT = 64 * (BM / WM) * NWN;
   constexpr int FM = WM / 16, FN = WN / 16;
-  constexpr int KP = BK + 8;  // row pitch in bf16 elements: (KP/2) = 4 * odd dwords
-  constexpr int UA = BM * (BK / 8), UB = (BK / 2) * (BN / 8);
-  constexpr int NA = (UA + NT - 1) / NT, NB = (UB + NT - 1) / NT;
+  constexpr int KP = kAPitch, BP = b_pitch<BN>();
+  constexpr int UA = BM * (BK / 8), UB = BK * (BN / 8);  // units of 8 elements
+  static_assert(UA % NT == 0 && UB % NT == 0 && NT % (BK / 8) == 0 && NT % (BN / 8) == 0,
+                "whole units per thread, each thread in one column of units");
+  constexpr int NA = UA / NT, NB = UB / NT;
   uint16_t *As = reinterpret_cast<uint16_t *>(smem);  // As[m][k]
-  uint16_t *Bt = As + BM * KP;                         // Bt[n][k] (B transposed)
+  uint16_t *Bs = As + BM * KP;                         // Bs[k][n]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / NWN, wn = wave % NWN;
@@ -306,60 +357,34 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &p, int bid, unsig
   const uint16_t *A = static_cast<const uint16_t *>(p.A);
   const uint16_t *B = static_cast<const uint16_t *>(p.B);
 
-  uint4 ra[NA], rb0[NB], rb1[NB];
+  uint4 ra[NA], rb[NB];
   const bool n_whole = n0 + BN <= p.N;
+  const int ac = (tid % (BK / 8)) * 8, ar = tid / (BK / 8), br = tid / (BN / 8);
   const int bc = n0 + (tid % (BN / 8)) * 8, bs = max(0, min(bc, p.N - 8)), b_bits = min(16 * (bc - bs), 112);
   bool raw = false;
-  const uint16_t *pa[NA], *const pb = B + int64_t(2 * (tid / (BN / 8))) * p.ldb + bs;
+  const uint16_t *pa[NA], *const pb = B + int64_t(br) * p.ldb + bs;
 #pragma unroll
-  for (int j = 0; j < NA; ++j)
-    pa[j] = A + int64_t(min(m0 + (tid + NT * j) / (BK / 8), p.M - 1)) * p.lda + (tid % (BK / 8)) * 8;
-  static_assert(NT % (BK / 8) == 0 && NT % (BN / 8) == 0, "a thread keeps its column in every unit");
+  for (int j = 0; j < NA; ++j) pa[j] = A + int64_t(min(m0 + ar + j * (NT / (BK / 8)), p.M - 1)) * p.lda + ac;
   auto load = [&](int k0) {
-    raw = UA % NT == 0 && UB % NT == 0 && p.N >= 8 && k0 + BK <= p.K;  // see "Unguarded loads" above
+    raw = p.N >= 8 && k0 + BK <= p.K;  // see "Unguarded loads" above
     if (raw) {
 #pragma unroll
       for (int j = 0; j < NA; ++j) ra[j] = load_as<uint4>(pa[j] + k0);
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const uint16_t *q = pb + int64_t(k0 + j * (2 * NT / (BN / 8))) * p.ldb;
-        rb0[j] = load_as<uint4>(q);
-        rb1[j] = load_as<uint4>(q + p.ldb);
-      }
+      for (int j = 0; j < NB; ++j) rb[j] = load_as<uint4>(pb + int64_t(k0 + j * (NT / (BN / 8))) * p.ldb);
       return;
     }
-    // A: units of 8 consecutive k in one row
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
-      const int u = tid + NT * j, r = u / (BK / 8), c = (u % (BK / 8)) * 8;
-      const int gr = m0 + r, gc = k0 + c;
-      if (u < UA && gr < p.M && gc + 7 < p.K) {
-        ra[j] = load_as<uint4>(A + int64_t(gr) * p.lda + gc);
-      } else {
-        uint16_t v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (u < UA && gr < p.M && gc + e < p.K) ? A[int64_t(gr) * p.lda + gc + e] : 0;
-        memcpy(&ra[j], v, 16);
-      }
+      const int gr = m0 + ar + j * (NT / (BK / 8)), gc = k0 + ac;
+      if (gr < p.M && gc + 7 < p.K) ra[j] = load_as<uint4>(A + int64_t(gr) * p.lda + gc);
+      else ra[j] = pack8_guarded(A + int64_t(gr) * p.lda + gc, [&](int e) { return gr < p.M && gc + e < p.K; });
     }
-    // B: units of two consecutive k rows x 8 consecutive n, stored transposed as (k, k+1) pairs
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int u = tid + NT * j, kp = u / (BN / 8), c = (u % (BN / 8)) * 8;
-      const int gk = k0 + 2 * kp, gc = n0 + c;
-      if (u < UB && gk + 1 < p.K && gc + 7 < p.N) {
-        rb0[j] = load_as<uint4>(B + int64_t(gk) * p.ldb + gc);
-        rb1[j] = load_as<uint4>(B + int64_t(gk + 1) * p.ldb + gc);
-      } else {
-        uint16_t lo[8], hi[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          lo[e] = (u < UB && gk < p.K && gc + e < p.N) ? B[int64_t(gk) * p.ldb + gc + e] : 0;
-          hi[e] = (u < UB && gk + 1 < p.K && gc + e < p.N) ? B[int64_t(gk + 1) * p.ldb + gc + e] : 0;
-        }
-        memcpy(&rb0[j], lo, 16);
-        memcpy(&rb1[j], hi, 16);
-      }
+      const int gk = k0 + br + j * (NT / (BN / 8));
+      if (gk < p.K && bc + 7 < p.N) rb[j] = load_as<uint4>(B + int64_t(gk) * p.ldb + bc);
+      else rb[j] = pack8_guarded(B + int64_t(gk) * p.ldb + bc, [&](int e) { return gk < p.K && bc + e < p.N; });
     }
   };
 
@@ -369,41 +394,26 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &p, int bid, unsig
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+  const uint16_t *const a_frag = As + (wm * WM + (lane & 15)) * KP + 8 * (lane >> 4);
+  const uint16_t *const b_lane = Bs + b_frag_lane<BN>(lane) + wn * WN;
   load(0);
   for (int k0 = 0; k0 < p.K; k0 += BK) {
 #pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      const int u = tid + NT * j, r = u / (BK / 8), c = (u % (BK / 8)) * 8;
-      if (u < UA) *reinterpret_cast<uint4 *>(&As[r * KP + c]) = ra[j];
-    }
+    for (int j = 0; j < NA; ++j) *reinterpret_cast<uint4 *>(&As[(ar + j * (NT / (BK / 8))) * KP + ac]) = ra[j];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int u = tid + NT * j, kp = u / (BN / 8), c = (u % (BN / 8)) * 8;
-      if (raw && !n_whole) {
-        rb0[j] = shift_down(rb0[j], b_bits);
-        rb1[j] = shift_down(rb1[j], b_bits);
-      }
-      if (u < UB) {
-        uint16_t lo[8], hi[8];
-        memcpy(lo, &rb0[j], 16);
-        memcpy(hi, &rb1[j], 16);
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          *reinterpret_cast<uint32_t *>(&Bt[(c + e) * KP + 2 * kp]) = uint32_t(lo[e]) | (uint32_t(hi[e]) << 16);
-      }
+      if (raw && !n_whole) rb[j] = shift_down(rb[j], b_bits);
+      *reinterpret_cast<uint4 *>(&Bs[(br + j * (NT / (BN / 8))) * BP + bc - n0]) = rb[j];
     }
     __syncthreads();
     if (k0 + BK < p.K) load(k0 + BK);  // in flight while this tile is multiplied
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 32) {
-      const int kq = kk + 8 * (lane >> 4);
       bf16x8 a[FM], b[FN];
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
-        a[i] = *reinterpret_cast<const bf16x8 *>(&As[(wm * WM + i * 16 + (lane & 15)) * KP + kq]);
+      for (int i = 0; i < FM; ++i) a[i] = *reinterpret_cast<const bf16x8 *>(a_frag + i * 16 * KP + kk);
 #pragma unroll
-      for (int j = 0; j < FN; ++j)
-        b[j] = *reinterpret_cast<const bf16x8 *>(&Bt[(wn * WN + j * 16 + (lane & 15)) * KP + kq]);
+      for (int j = 0; j < FN; ++j) b[j] = b_frag<BN>(b_lane + kk * BP + j * 16);
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -567,7 +577,8 @@ __device__ __forceinline__ void gemm_f32_splitk_tile(const GemmArgs &p, int bid,
 
 template <int TM, int TN>
 constexpr int gemm_bf16_splitk_smem() {
-  return 4 * (TM + TN) * 72 * 2 > 4 * TM * TN * 4 ? 4 * (TM + TN) * 72 * 2 : 4 * TM * TN * 4;
+  constexpr int stage = 4 * 2 * (TM * kAPitch + 64 * b_pitch<TN>()), red = 4 * TM * TN * 4;
+  return stage > red ? stage : red;
 }
 
 // PREFETCH = false loads each chunk just before staging it instead of during the previous
@@ -577,13 +588,12 @@ constexpr int gemm_bf16_splitk_smem() {
 // has only a few chunks.
 template <int TM, int TN, bool OUT_BF16, bool PREFETCH = true>
 __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid, unsigned char *smem) {
-  constexpr int BK = 64, KP = BK + 8, FM = TM / 16, FN = TN / 16;
-  constexpr int UA = TM * (BK / 8) / 64;        // uint4 (8 x bf16) loads per lane
-  constexpr int UB = (BK / 2) * (TN / 8) / 64;  // (k, k+1) x 8-column units per lane
+  constexpr int BK = 64, KP = kAPitch, BP = b_pitch<TN>(), FM = TM / 16, FN = TN / 16;
+  constexpr int UA = TM * (BK / 8) / 64, UB = BK * (TN / 8) / 64;  // 8-element loads per lane
   static_assert(UA >= 1 && UB >= 1, "tile too small for one load per lane");
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   uint16_t *As = reinterpret_cast<uint16_t *>(smem) + w * TM * KP;
-  uint16_t *Bt = reinterpret_cast<uint16_t *>(smem) + 4 * TM * KP + w * TN * KP;
+  uint16_t *Bs = reinterpret_cast<uint16_t *>(smem) + 4 * TM * KP + w * BK * BP;
   const int tm = bid / p.tiles_n, tn = bid % p.tiles_n;
   const int m0 = tm * TM, n0 = tn * TN;
   const uint16_t *A = static_cast<const uint16_t *>(p.A);
@@ -591,14 +601,15 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
   const int nchunks = (p.K + BK - 1) / BK;
   const int iters = (nchunks + 3) / 4;
 
-  uint4 ra[UA], rb0[UB], rb1[UB];
+  uint4 ra[UA], rb[UB];
   const bool n_whole = n0 + TN <= p.N;
+  const int ac = (lane % (BK / 8)) * 8, ar = lane / (BK / 8), br = lane / (TN / 8);
   const int bc = n0 + (lane % (TN / 8)) * 8, bs = max(0, min(bc, p.N - 8)), b_bits = min(16 * (bc - bs), 112);
   bool raw = false;
-  const uint16_t *pa[UA], *const pb = B + int64_t(2 * (lane / (TN / 8))) * p.ldb + bs;
+  const uint16_t *pa[UA], *const pb = B + int64_t(br) * p.ldb + bs;
 #pragma unroll
-  for (int j = 0; j < UA; ++j)
-    pa[j] = A + int64_t(min(m0 + (lane + 64 * j) / (BK / 8), p.M - 1)) * p.lda + (lane % (BK / 8)) * 8;
+  for (int j = 0; j < UA; ++j) pa[j] = A + int64_t(min(m0 + ar + 8 * j, p.M - 1)) * p.lda + ac;
+  constexpr int BR = 64 / (TN / 8);  // B rows one load of the wavefront covers
   auto load = [&](int chunk) {
     const int k0 = chunk * BK;
     raw = p.N >= 8 && k0 + BK <= p.K;  // see "Unguarded loads" above
@@ -606,43 +617,20 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
 #pragma unroll
       for (int j = 0; j < UA; ++j) ra[j] = load_as<uint4>(pa[j] + k0);
 #pragma unroll
-      for (int j = 0; j < UB; ++j) {
-        const uint16_t *q = pb + int64_t(k0 + j * (2 * 64 / (TN / 8))) * p.ldb;
-        rb0[j] = load_as<uint4>(q);
-        rb1[j] = load_as<uint4>(q + p.ldb);
-      }
+      for (int j = 0; j < UB; ++j) rb[j] = load_as<uint4>(pb + int64_t(k0 + j * BR) * p.ldb);
       return;
     }
 #pragma unroll
     for (int j = 0; j < UA; ++j) {
-      const int u = lane + 64 * j, r = u / (BK / 8), c = (u % (BK / 8)) * 8;
-      const int gr = m0 + r, gc = k0 + c;
-      if (gr < p.M && gc + 7 < p.K) {
-        ra[j] = load_as<uint4>(A + int64_t(gr) * p.lda + gc);
-      } else {
-        uint16_t v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (gr < p.M && gc + e < p.K) ? A[int64_t(gr) * p.lda + gc + e] : 0;
-        memcpy(&ra[j], v, 16);
-      }
+      const int gr = m0 + ar + 8 * j, gc = k0 + ac;
+      if (gr < p.M && gc + 7 < p.K) ra[j] = load_as<uint4>(A + int64_t(gr) * p.lda + gc);
+      else ra[j] = pack8_guarded(A + int64_t(gr) * p.lda + gc, [&](int e) { return gr < p.M && gc + e < p.K; });
     }
 #pragma unroll
     for (int j = 0; j < UB; ++j) {
-      const int u = lane + 64 * j, kp = u / (TN / 8), c = (u % (TN / 8)) * 8;
-      const int gk = k0 + 2 * kp, gc = n0 + c;
-      if (gk + 1 < p.K && gc + 7 < p.N) {
-        rb0[j] = load_as<uint4>(B + int64_t(gk) * p.ldb + gc);
-        rb1[j] = load_as<uint4>(B + int64_t(gk + 1) * p.ldb + gc);
-      } else {
-        uint16_t lo[8], hi[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          lo[e] = (gk < p.K && gc + e < p.N) ? B[int64_t(gk) * p.ldb + gc + e] : 0;
-          hi[e] = (gk + 1 < p.K && gc + e < p.N) ? B[int64_t(gk + 1) * p.ldb + gc + e] : 0;
-        }
-        memcpy(&rb0[j], lo, 16);
-        memcpy(&rb1[j], hi, 16);
-      }
+      const int gk = k0 + br + j * BR;
+      if (gk < p.K && bc + 7 < p.N) rb[j] = load_as<uint4>(B + int64_t(gk) * p.ldb + bc);
+      else rb[j] = pack8_guarded(B + int64_t(gk) * p.ldb + bc, [&](int e) { return gk < p.K && bc + e < p.N; });
     }
   };
 
@@ -652,45 +640,39 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+  const uint16_t *const a_frag = As + (lane & 15) * KP + 8 * (lane >> 4);
+  const uint16_t *const b_lane = Bs + b_frag_lane<TN>(lane);
   if (PREFETCH) load(w);
   for (int it = 0; it < iters; ++it) {
     // no block barrier in this loop: each wavefront stages and reads only its own LDS region,
     // and one wavefront's LDS operations take effect in program order
     if (!PREFETCH) load(it * 4 + w);
 #pragma unroll
-    for (int j = 0; j < UA; ++j) {
-      const int u = lane + 64 * j, r = u / (BK / 8), c = (u % (BK / 8)) * 8;
-      *reinterpret_cast<uint4 *>(&As[r * KP + c]) = ra[j];
-    }
+    for (int j = 0; j < UA; ++j) *reinterpret_cast<uint4 *>(&As[(ar + 8 * j) * KP + ac]) = ra[j];
 #pragma unroll
     for (int j = 0; j < UB; ++j) {
-      const int u = lane + 64 * j, kp = u / (TN / 8), c = (u % (TN / 8)) * 8;
-      if (raw && !n_whole) {
-        rb0[j] = shift_down(rb0[j], b_bits);
-        rb1[j] = shift_down(rb1[j], b_bits);
-      }
-      uint16_t lo[8], hi[8];
-      memcpy(lo, &rb0[j], 16);
-      memcpy(hi, &rb1[j], 16);
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        *reinterpret_cast<uint32_t *>(&Bt[(c + e) * KP + 2 * kp]) = uint32_t(lo[e]) | (uint32_t(hi[e]) << 16);
+      if (raw && !n_whole) rb[j] = shift_down(rb[j], b_bits);
+      *reinterpret_cast<uint4 *>(&Bs[(br + j * BR) * BP + bc - n0]) = rb[j];
     }
     if (PREFETCH && it + 1 < iters) load((it + 1) * 4 + w);
+    // (the fence keeps the compiler from moving the transposing reads above the stores)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 32) {
-      const int kq = kk + 8 * (lane >> 4);
       bf16x8 a[FM], b[FN];
 #pragma unroll
-      for (int i = 0; i < FM; ++i) a[i] = *reinterpret_cast<const bf16x8 *>(&As[(i * 16 + (lane & 15)) * KP + kq]);
+      for (int i = 0; i < FM; ++i) a[i] = *reinterpret_cast<const bf16x8 *>(a_frag + i * 16 * KP + kk);
 #pragma unroll
-      for (int j = 0; j < FN; ++j) b[j] = *reinterpret_cast<const bf16x8 *>(&Bt[(j * 16 + (lane & 15)) * KP + kq]);
+      for (int j = 0; j < FN; ++j) b[j] = b_frag<TN>(b_lane + kk * BP + j * 16);
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
   float *red = reinterpret_cast<float *>(smem);
@@ -847,19 +829,6 @@ __device__ __forceinline__ void gemm_bf16_deep_tile(const GemmArgs &p, int bid, 
   }
 }
 
-// Eight consecutive bf16 at p[0..8), element e only if ok_e(e), packed into one uint4.
-template <typename F>
-__device__ __forceinline__ uint4 pack8_guarded(const uint16_t *p, F ok_e) {
-  uint32_t w[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t lo = ok_e(2 * q) ? uint32_t(p[2 * q]) : 0u;
-    const uint32_t hi = ok_e(2 * q + 1) ? uint32_t(p[2 * q + 1]) : 0u;
-    w[q] = lo | (hi << 16);
-  }
-  return uint4{w[0], w[1], w[2], w[3]};
-}
-
 // ---------------------------------------------------------------------------------------------
 // Large BF16 GEMM tile: 256 x 256 outputs per 512-thread block, K step 64, eight wavefronts
 // (2 along M x 4 along N) each owning a 128 x 64 sub-tile (8 x 4 blocks of
@@ -879,8 +848,6 @@ __device__ __forceinline__ uint4 pack8_guarded(const uint16_t *p, F ok_e) {
 // ---------------------------------------------------------------------------------------------
 constexpr int kBigKP = 80, kBigBP = 280;
 constexpr int gemm_bf16_big_smem() { return 2 * (256 * kBigKP + 64 * kBigBP) * 2; }
-
-typedef short shortx4 __attribute__((ext_vector_type(4)));
 
 // Requires M % 256 == 0, N % 256 == 0, K % 64 == 0, 16-byte aligned operands and leading
 // dimensions that are multiples of 8 (the launch factory checks; other shapes use tile 4).
