@@ -439,7 +439,9 @@ psc_status psc_sched_prepare(psc_sched *sched);
  * all their workgroups, placed where the first of them stands: the precedences, the buffers and
  * the results are those of one launch per kernel, and psc_sched_export keeps describing the plan
  * kernel by kernel.  GEMMs with an automatic tile take one that suits the launch, among those that
- * sum in the same order.  Every kernel keeps its own launch under record_ops, mark_components,
+ * sum in the same order.  The streams are carried by as many hardware queues as a prediction of the
+ * run finds fastest, stream s by queue s mod that count (runs with host copies on kernel streams
+ * keep one queue per stream).  Every kernel keeps its own launch and stream under record_ops, mark_components,
  * use_graph, fault_inject_op and out_of_order, and under every other policy.
  * Errors: PSC_ERR_NAME (io names no isolated write or read), PSC_ERR_ARG (byte count), PSC_ERR_HIP. */
 psc_status psc_run(psc_sched *sched, const psc_host_io *io, int32_t n_io, psc_run_stats *stats);

@@ -18,7 +18,8 @@ constexpr auto kIdleSpin = std::chrono::milliseconds(20);  // spin before parkin
 }  // namespace
 
 Dispatcher::Dispatcher(const std::vector<const SchedPlan *> &plans, int32_t n_threads)
-    : n_threads_(std::max<int32_t>(1, std::min(n_threads, plans[0]->total_streams))) {
+    : n_threads_(1) {
+  for (const SchedPlan *plan : plans) n_threads_ = std::max(n_threads_, std::min(n_threads, plan->total_streams));
   for (const SchedPlan *plan : plans) {
     Plan p;
     p.plan = plan;
@@ -104,6 +105,16 @@ void Dispatcher::worker_main(int32_t t) {
 }
 
 void Dispatcher::run(Backend &b, int32_t plan) {
+  if (plans_[plan].plan->total_streams == 1) {  // one stream: the caller alone, the others stay idle
+    const std::vector<Op> &ops = plans_[plan].plan->ops;
+    for (size_t o = 0; o < ops.size(); ++o) {
+      for (int32_t w : ops[o].waits) b.wait(int32_t(o), w);  // (out-of-order queues)
+      b.exec(int32_t(o));
+      if (ops[o].recorded) b.record(int32_t(o));
+    }
+    b.stream_done(0);
+    return;
+  }
   backend_ = &b;
   now_ = &plans_[plan];
   abort_.store(false);

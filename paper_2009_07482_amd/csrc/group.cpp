@@ -8,10 +8,12 @@
 namespace psc {
 
 GroupedPlan group_plan(const Dag &g, const SchedPlan &plan, const std::vector<int32_t> &key,
-                       const std::vector<int64_t> &blocks, int64_t max_blocks, bool copies, bool copy_roots) {
+                       const std::vector<int64_t> &blocks, int64_t max_blocks, bool copies, bool copy_roots,
+                       int32_t queues) {
   GroupedPlan gp;
-  gp.plan.n_streams = plan.n_streams;
-  gp.plan.total_streams = plan.total_streams;
+  gp.plan.n_streams = queues;
+  gp.plan.total_streams = queues + (plan.total_streams - plan.n_streams);
+  auto queue_of = [&](int32_t s) { return s < plan.n_streams ? s % queues : s - plan.n_streams + queues; };
   const size_t n = plan.ops.size(), nk = g.kers.size();
   const std::vector<int32_t> upload_as = upload_buffers(g, copy_roots);
   std::vector<int32_t> h2d_op(g.bufs.size(), -1);
@@ -49,7 +51,7 @@ GroupedPlan group_plan(const Dag &g, const SchedPlan &plan, const std::vector<in
     x.type = op.type;
     x.kernel = kernel;
     x.buffer = op.buffer;
-    x.stream = op.stream;
+    x.stream = queue_of(op.stream);
     x.pos = 0;
     x.host_order = int32_t(gp.plan.ops.size());
     gp.plan.ops.push_back(std::move(x));
@@ -71,7 +73,7 @@ GroupedPlan group_plan(const Dag &g, const SchedPlan &plan, const std::vector<in
     int32_t x = -1;
     const int32_t ky = key[op.kernel];
     if (ky >= 0) {
-      auto it = open.find({op.stream, level[op.kernel], ky});
+      auto it = open.find({queue_of(op.stream), level[op.kernel], ky});
       if (it != open.end() && last < int32_t(it->second.first) && it->second.blocks < max_blocks) {
         x = it->second.op;
         it->second.blocks += blocks[op.kernel];
@@ -82,12 +84,62 @@ GroupedPlan group_plan(const Dag &g, const SchedPlan &plan, const std::vector<in
     if (x < 0) {
       gp.units.push_back({op.kernel});
       x = emit(op, o, int32_t(gp.units.size()) - 1);
-      if (ky >= 0) open[{op.stream, level[op.kernel], ky}] = Open{x, o, blocks[op.kernel]};
+      if (ky >= 0) open[{queue_of(op.stream), level[op.kernel], ky}] = Open{x, o, blocks[op.kernel]};
     }
     for (int32_t w : d) deps[x].push_back(new_of[w]);
   }
   assign_waits(gp.plan, deps);
   return gp;
+}
+
+double predict_plan_us(const GroupedPlan &gp, const std::vector<UnitCost> &cost, double gap_us, double wait_us) {
+  const std::vector<Op> &ops = gp.plan.ops;
+  const int32_t T = gp.plan.total_streams;
+  std::vector<std::vector<int32_t>> queue(T);
+  for (size_t o = 0; o < ops.size(); ++o) queue[ops[o].stream].push_back(int32_t(o));
+  std::vector<double> end(ops.size(), -1), left(T, 0), from(T, 0);  // `from`: the queue's next start by its own order
+  std::vector<size_t> at(T, 0);
+  std::vector<char> running(T, 0);
+  for (int32_t q = 1; q < T; ++q) from[q] = wait_us;
+  double now = 0, finish = 0;
+  for (;;) {
+    // start what can start; otherwise the time at which the next one may
+    double next = 1e300, asked = 0;
+    bool any = false;
+    for (int32_t q = 0; q < T; ++q) {
+      if (!running[q] && at[q] < queue[q].size()) {
+        any = true;
+        const int32_t o = queue[q][at[q]];
+        double start = from[q];
+        for (int32_t w : ops[o].waits) start = end[w] < 0 ? 1e300 : std::max(start, end[w] + wait_us);
+        if (start <= now + 1e-9) {
+          running[q] = 1;
+          left[q] = cost[ops[o].kernel].us;
+        } else {
+          next = std::min(next, start);
+        }
+      }
+      if (running[q]) {
+        any = true;
+        asked += cost[ops[queue[q][at[q]]].kernel].share;
+      }
+    }
+    if (!any) return finish;
+    const double slow = std::max(1.0, asked);
+    for (int32_t q = 0; q < T; ++q)
+      if (running[q]) next = std::min(next, now + left[q] * slow);
+    if (next > 1e299) return 1e300;  // (not reached: the plan's waits name earlier ops)
+    for (int32_t q = 0; q < T; ++q) {
+      if (!running[q]) continue;
+      left[q] -= (next - now) / slow;
+      if (left[q] > 1e-9) continue;
+      running[q] = 0;
+      end[queue[q][at[q]++]] = next;
+      from[q] = next + gap_us;
+      finish = std::max(finish, next + (q ? wait_us : 0.0));
+    }
+    now = next;
+  }
 }
 
 }  // namespace psc

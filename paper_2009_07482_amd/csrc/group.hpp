@@ -30,8 +30,22 @@ struct GroupedPlan {
 // kernel's place, where everything any of its kernels depends on has been enqueued: the order
 // stays topological, so no wait can close a cycle, and no two kernels of a launch depend on each
 // other.  copies = false leaves the uploads and read-backs out (a run without host memory), so
-// that a kernel is not held back by an upload that is skipped.
+// that a kernel is not held back by an upload that is skipped.  queues (1 .. plan.n_streams): the
+// kernel streams are carried by this many, stream s by s mod queues in host order; copy streams
+// follow them.
 GroupedPlan group_plan(const Dag &g, const SchedPlan &plan, const std::vector<int32_t> &key,
-                       const std::vector<int64_t> &blocks, int64_t max_blocks, bool copies, bool copy_roots);
+                       const std::vector<int64_t> &blocks, int64_t max_blocks, bool copies, bool copy_roots,
+                       int32_t queues);
+
+// What one launch needs, for the prediction below: microseconds alone on the GPU and the share of
+// the GPU it then fills (0, 1].
+struct UnitCost {
+  double us = 0, share = 1;
+};
+// Predicted microseconds of a grouped plan without copies: each queue runs its launches one after
+// the other `gap_us` apart, a wait for another queue's launch (the run's start and end among them)
+// takes wait_us, and launches in flight together that ask for more than the whole GPU slow each
+// other down in proportion.
+double predict_plan_us(const GroupedPlan &gp, const std::vector<UnitCost> &cost, double gap_us, double wait_us);
 
 }  // namespace psc

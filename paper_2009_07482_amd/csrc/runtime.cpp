@@ -103,6 +103,8 @@ struct Runner {
   const SchedPlan *plan = nullptr;    // &own, or the schedule's plan
   const std::vector<Launch> *launch = nullptr;
   std::vector<Launch> own_launch;
+  std::vector<std::vector<Launch>> members;  // until upload_groups: per launch its kernels' launches
+  size_t table_bytes = 0;
   std::vector<int32_t> op_of;         // per op: the op of the schedule's plan (grouped plans)
   std::vector<hipEvent_t> op_ev;      // per op that another stream waits for
   void *table = nullptr;              // device memory: the launch groups' argument lists and maps
@@ -609,9 +611,37 @@ bool groups_launches(const psc_sched &s) {
 // waits for the launch's first kernels does not wait for a longer one.
 constexpr int64_t kGroupMaxBlocks = 2048;
 
+// What a launch that follows another on its queue, and one that waits for another queue's, start
+// late (us).  A HIP precedence is an event record, a wait and the barrier packets they become.
+constexpr double kGapUs = 2.0, kWaitAql = 8.0, kWaitHip = 20.0;
+
+// Microseconds a launch takes alone and the share of the GPU it fills, from the rates such launches
+// reach when they fill it (BF16 350, FP32 60 TFLOP/s, 4 TB/s) and what one costs however small.
+UnitCost unit_cost(const Dag &g, const std::vector<int32_t> &kernels, const Launch &L) {
+  // a launch alone loses a fifth of the GPU to the unevenness of its last blocks
+  constexpr double kLaunchUs = 3.0, kFullBlocks = 384, kAlone = 0.8;
+  double us = 0;
+  for (int32_t k : kernels) {
+    const Kernel &ker = g.kers[k];
+    const Buffer &a = g.bufs[ker.ins[0]], &o = g.bufs[ker.outs[0]];
+    double bytes = double(o.rows) * o.cols * elem_size(o.dtype);
+    for (int32_t b : ker.ins) bytes += double(g.bufs[b].rows) * g.bufs[b].cols * elem_size(g.bufs[b].dtype);
+    const double flops = ker.kind == PSC_GEMM ? 2.0 * double(o.rows) * double(o.cols) * double(a.cols) : 0.0;
+    us += std::max(flops / (a.dtype == PSC_BF16 ? 3.5e14 : 6.0e13), bytes / 4.0e12) * 1e6;
+  }
+  UnitCost c;
+  c.share = std::min(kAlone, std::max(1.0, double(L.grid.x)) / kFullBlocks);
+  c.us = L.empty ? 0.1 : kLaunchUs + us / c.share;
+  return c;
+}
+
 // The grouped plan of a schedule with its launches.  GEMMs whose tile is automatic are grouped by
 // summation order and take the tile that suits the group; everything else by kernel function.
-std::unique_ptr<Runner> make_grouped(const psc_sched &s, const Device &d, bool copies) {
+struct GroupedRunner {
+  std::unique_ptr<Runner> runner;
+  double us = 0;  // predicted
+};
+GroupedRunner make_grouped(const psc_sched &s, const Device &d, bool copies, int32_t queues) {
   const Dag &g = s.dag->g;
   const size_t nk = g.kers.size();
   std::vector<int32_t> key(nk, -1);
@@ -633,7 +663,8 @@ std::unique_ptr<Runner> make_grouped(const psc_sched &s, const Device &d, bool c
     }
     key[k] = ids.emplace(v, int32_t(ids.size())).first->second;
   }
-  GroupedPlan gp = group_plan(g, s.plan, key, blocks, kGroupMaxBlocks, copies, s.opts.copy_roots != 0);
+  GroupedPlan gp = group_plan(g, s.plan, key, blocks, kGroupMaxBlocks, copies, s.opts.copy_roots != 0,
+                              queues);
   auto r = std::make_unique<Runner>();
   std::vector<std::vector<Launch>> members(gp.units.size());
   size_t bytes = 0;
@@ -652,26 +683,69 @@ std::unique_ptr<Runner> make_grouped(const psc_sched &s, const Device &d, bool c
     }
     bytes += group_table_bytes(members[u]);
   }
-  std::vector<unsigned char> host(bytes);
-  if (bytes) {
-    hipError_t e = hipMalloc(&r->table, bytes);
-    if (e != hipSuccess) fail(PSC_ERR_OOM, std::string("hipMalloc (launch groups): ") + hipGetErrorString(e));
+  GroupedRunner out;
+  std::vector<UnitCost> cost(members.size());
+  for (size_t u = 0; u < members.size(); ++u) {
+    Launch all = members[u][0];
+    all.grid.x = 0;
+    for (const Launch &L : members[u]) all.grid.x += L.grid.x;
+    cost[u] = unit_cost(g, gp.units[u], all);
   }
-  size_t off = 0;
-  for (const std::vector<Launch> &m : members) {
-    if (m.size() < 2) {
-      r->own_launch.push_back(m[0]);
-      continue;
-    }
-    r->own_launch.push_back(group_launch(m, host.data() + off, static_cast<char *>(r->table) + off));
-    off += group_table_bytes(m);
-  }
-  if (bytes) PSC_HIP(hipMemcpy(r->table, host.data(), bytes, hipMemcpyHostToDevice));
+  if (!copies) out.us = predict_plan_us(gp, cost, kGapUs, s.opts.dispatch == PSC_DISPATCH_AQL ? kWaitAql : kWaitHip);
+  r->members = std::move(members);
+  r->table_bytes = bytes;
   r->own = std::move(gp.plan);
   r->op_of = std::move(gp.op_of);
   r->plan = &r->own;
   r->launch = &r->own_launch;
-  return r;
+  out.runner = std::move(r);
+  return out;
+}
+
+// The grouped launches' argument lists and maps in device memory, and the launches.
+void upload_groups(Runner &r) {
+  std::vector<unsigned char> host(r.table_bytes);
+  if (r.table_bytes) {
+    hipError_t e = hipMalloc(&r.table, r.table_bytes);
+    if (e != hipSuccess) fail(PSC_ERR_OOM, std::string("hipMalloc (launch groups): ") + hipGetErrorString(e));
+  }
+  size_t off = 0;
+  for (const std::vector<Launch> &m : r.members) {
+    if (m.size() < 2) {
+      r.own_launch.push_back(m[0]);
+      continue;
+    }
+    r.own_launch.push_back(group_launch(m, host.data() + off, static_cast<char *>(r.table) + off));
+    off += group_table_bytes(m);
+  }
+  if (r.table_bytes) PSC_HIP(hipMemcpy(r.table, host.data(), r.table_bytes, hipMemcpyHostToDevice));
+  r.members.clear();
+}
+
+// How many queues carry the plan's streams: the count with the shortest predicted run.  A wait
+// between queues costs more than a small launch, and launches that fill the GPU gain nothing from
+// running beside each other; kernels of unlike functions and sizes do.  Measured on 1 / 2 / 3 / 4
+// queues (us, the chosen count in brackets): fork-join of 256 FP32 on HIP streams [24] / 74 / 77 / 90;
+// 512 FP32 attention on AQL queues [77] / 83 / 92 / 97; 4-layer 1024 BF16 attention on AQL queues
+// 461 / [430] / 470 / 476; random DAG of 60 kernels on HIP streams [220] / 251 / 235 / 290; batch of
+// sixteen uneven BF16 DAGs on HIP streams 1656 / 1299 / [1213] / 1233.
+std::unique_ptr<Runner> best_grouped(const psc_sched &s, const Device &d, bool copies, int32_t *queues) {
+  if (copies) return make_grouped(s, d, true, *queues).runner;
+  GroupedRunner best;
+  for (int32_t q = 1; q <= std::min(s.plan.n_streams, 4); ++q) {
+    GroupedRunner r = make_grouped(s, d, false, q);
+    if (best.runner && r.us >= best.us) continue;
+    best = std::move(r);
+    *queues = q;
+  }
+  if (s.plan.n_streams > 4) {
+    GroupedRunner r = make_grouped(s, d, false, s.plan.n_streams);
+    if (r.us < best.us) {
+      best = std::move(r);
+      *queues = s.plan.n_streams;
+    }
+  }
+  return std::move(best.runner);
 }
 
 // Events, or AQL signals and records, of a plan.
@@ -750,13 +824,18 @@ void prepare(psc_sched &s) {
   if (dev_mode) {
     prepare_executor(g, s.plan, s.opts.exec_per_cu, *d);
   } else if (groups_launches(s)) {
-    for (int copies = 0; copies < 2; ++copies) d->grouped[copies] = make_grouped(s, *d, copies != 0);
-    std::shared_ptr<AqlQueues> queues;
-    if (aql_mode) {
-      queues = std::make_shared<AqlQueues>(
+    // uploads on their kernels' streams (no copy stream) overlap kernels of other streams: runs
+    // with copies then keep every stream
+    int32_t queues = s.plan.n_streams;
+    d->grouped[0] = best_grouped(s, *d, false, &queues);
+    if (s.plan.total_streams == s.plan.n_streams) queues = s.plan.n_streams;
+    d->grouped[1] = best_grouped(s, *d, true, &queues);
+    for (auto &r : d->grouped) upload_groups(*r);
+    std::shared_ptr<AqlQueues> aql_queues;
+    if (aql_mode)
+      aql_queues = std::make_shared<AqlQueues>(
           d->device, std::vector<const SchedPlan *>{d->grouped[0]->plan, d->grouped[1]->plan}, false);
-    }
-    for (auto &r : d->grouped) finish_runner(s, *d, *r, queues);
+    for (auto &r : d->grouped) finish_runner(s, *d, *r, aql_queues);
     d->grouped[1]->disp_plan = 1;
     d->disp = std::make_unique<Dispatcher>(std::vector<const SchedPlan *>{d->grouped[0]->plan, d->grouped[1]->plan}, nt);
   } else {
@@ -866,12 +945,13 @@ struct AqlBackend final : Backend {
   void stream_done(int32_t) override {}
 };
 
-void fork_streams(Device &d, hipEvent_t ev) {
-  for (size_t i = 1; i < d.streams.size(); ++i) PSC_HIP(hipStreamWaitEvent(d.streams[i], ev, 0));
+// the first n streams, those the run uses
+void fork_streams(Device &d, hipEvent_t ev, int32_t n) {
+  for (int32_t i = 1; i < n; ++i) PSC_HIP(hipStreamWaitEvent(d.streams[i], ev, 0));
 }
 
-void join_streams(Device &d) {  // join events were recorded by the dispatch threads
-  for (size_t i = 1; i < d.streams.size(); ++i) PSC_HIP(hipStreamWaitEvent(d.streams[0], d.join_ev[i], 0));
+void join_streams(Device &d, int32_t n) {  // join events were recorded by the dispatch threads
+  for (int32_t i = 1; i < n; ++i) PSC_HIP(hipStreamWaitEvent(d.streams[0], d.join_ev[i], 0));
 }
 
 }  // namespace
@@ -942,7 +1022,7 @@ namespace {
   const int32_t k = s.opts.fault_inject_op - 1;
   HipBackend backend(d, *d.plain, cd, false);
   PSC_HIP(hipEventRecord(d.start, d.streams[0]));
-  fork_streams(d, d.start);
+  fork_streams(d, d.start, s.plan.total_streams);
   for (int32_t o = 0; o < k; ++o) {
     const Op &op = s.plan.ops[o];
     for (int32_t w : op.waits) backend.wait(o, w);
@@ -1039,7 +1119,7 @@ void run_dynamic(psc_sched &s, const std::vector<CopyDesc> &cd, bool timed) {
   int32_t order = 0;
   hipStream_t s0 = d.streams[0];
   PSC_HIP(hipEventRecord(d.start, s0));
-  fork_streams(d, d.start);
+  fork_streams(d, d.start, S);
   const auto t0 = std::chrono::steady_clock::now();
   auto now_us = [&] { return std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count(); };
   auto timed_op = [&](int32_t o, hipStream_t q, auto &&body) {
@@ -1115,7 +1195,7 @@ void run_dynamic(psc_sched &s, const std::vector<CopyDesc> &cd, bool timed) {
     throw;
   }
   for (int32_t x = 1; x < S; ++x) PSC_HIP(hipEventRecord(d.join_ev[x], d.streams[x]));
-  join_streams(d);
+  join_streams(d, S);
   PSC_HIP(hipEventRecord(d.end, s0));
   for (size_t o = 0; o < plan.ops.size(); ++o) {
     Op &op = plan.ops[o];
@@ -1253,10 +1333,10 @@ void run(psc_sched &s, const psc_host_io *io, int32_t n_io, psc_run_stats *stats
     const auto h0 = std::chrono::steady_clock::now();
     if (d.marks) launch(d.mark_start, s0);
     PSC_HIP(hipEventRecord(d.start, s0));
-    fork_streams(d, d.start);
+    fork_streams(d, d.start, r->plan->total_streams);
     HipBackend backend(d, *r, *rcd, timed);
     d.disp->run(backend, r->disp_plan);
-    join_streams(d);
+    join_streams(d, r->plan->total_streams);
     PSC_HIP(hipEventRecord(d.end, s0));
     host_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - h0).count();
   }

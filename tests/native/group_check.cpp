@@ -87,7 +87,9 @@ static void run_all() {
             o.copy_roots = roots;
             const SchedPlan plan = build_plan(g, PSC_FINE, o);
             const int64_t cap = 60;
-            const GroupedPlan gp = group_plan(g, plan, key, blocks, cap, copies != 0, roots != 0);
+            const int32_t queues = 1 + int32_t(r() % unsigned(o.n_streams));
+            auto queue_of = [&](int32_t st) { return st < o.n_streams ? st % queues : st - o.n_streams + queues; };
+            const GroupedPlan gp = group_plan(g, plan, key, blocks, cap, copies != 0, roots != 0, queues);
             const std::vector<Op> &ops = gp.plan.ops;
             const size_t n = ops.size();
             // every kernel once, on its stream; members alike and within the cap
@@ -101,7 +103,7 @@ static void run_all() {
               for (size_t m = 0; m < u.size(); ++m) {
                 check(at[u[m]] < 0, "kernel launched twice", seed);
                 at[u[m]] = int32_t(i);
-                check(plan.ops[size_t(plan.kernel_op[u[m]])].stream == ops[i].stream, "kernel on another stream", seed);
+                check(queue_of(plan.ops[size_t(plan.kernel_op[u[m]])].stream) == ops[i].stream, "kernel on another stream", seed);
                 check(u.size() == 1 || (key[u[m]] == key[u[0]] && key[u[m]] >= 0), "unlike kernels together", seed);
                 if (m + 1 < u.size()) before_last += blocks[u[m]];
               }
@@ -134,14 +136,25 @@ static void run_all() {
               if (ops[i].type == PSC_OP_KERNEL) continue;
               ++n_copies;
               const Op &orig = plan.ops[size_t(gp.op_of[i])];
-              check(orig.type == ops[i].type && orig.buffer == ops[i].buffer && orig.stream == ops[i].stream,
+              check(orig.type == ops[i].type && orig.buffer == ops[i].buffer && queue_of(orig.stream) == ops[i].stream,
                     "copy changed", seed);
               if (ops[i].type == PSC_OP_H2D) up[size_t(ops[i].buffer)] = int32_t(i);
             }
             size_t want = 0;
             for (const Op &op : plan.ops) want += op.type != PSC_OP_KERNEL;
             check(n_copies == (copies ? want : 0), "copies lost or added", seed);
-            if (!copies) continue;
+            if (!copies) {
+              // the prediction ends, and counts at least the longest launch and every queue's sum
+              std::vector<UnitCost> cost(gp.units.size());
+              std::vector<double> sum(size_t(queues), 0.0);
+              double least = 0;
+              for (size_t u = 0; u < cost.size(); ++u) cost[u] = UnitCost{1.0 + double(r() % 20), 0.1 * (1 + double(r() % 10))};
+              for (size_t i = 0; i < n; ++i) sum[size_t(ops[i].stream)] += cost[size_t(ops[i].kernel)].us;
+              for (double x : sum) least = std::max(least, x);
+              const double us = predict_plan_us(gp, cost, 1.0, 3.0);
+              check(us >= least - 1e-6 && us < 1e6, "prediction out of bounds", seed);
+              continue;
+            }
             for (int32_t k = 0; k < nk; ++k)
               for (int32_t b : g.iso_in[k])
                 check(past[size_t(at[k])].count(up[size_t(as[size_t(b)])]) == 1, "kernel not after its upload", seed);
