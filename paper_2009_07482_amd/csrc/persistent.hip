@@ -63,16 +63,16 @@ __device__ __forceinline__ void copy_task(const CopyArgs &c, int tile) {
   if (v16) {
     const int64_t upr = c.width / 16, n = nr * upr;
     for (int64_t base = threadIdx.x; base < n; base += 256 * 8) {
-      uint4 v[8];
+      u32x4 v[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int64_t u = base + 256 * j;
-        if (u < n) v[j] = *reinterpret_cast<const uint4 *>(src + (u / upr) * c.spitch + (u % upr) * 16);
+        if (u < n) v[j] = load16(src + (u / upr) * c.spitch + (u % upr) * 16);
       }
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int64_t u = base + 256 * j;
-        if (u < n) *reinterpret_cast<uint4 *>(dst + (u / upr) * c.dpitch + (u % upr) * 16) = v[j];
+        if (u < n) store16(dst + (u / upr) * c.dpitch + (u % upr) * 16, v[j]);
       }
     }
   } else {
@@ -82,12 +82,12 @@ __device__ __forceinline__ void copy_task(const CopyArgs &c, int tile) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int64_t u = base + 256 * j;
-        if (u < n) v[j] = *reinterpret_cast<const uint16_t *>(src + (u / upr) * c.spitch + (u % upr) * 2);
+        if (u < n) v[j] = load1(reinterpret_cast<const uint16_t *>(src + (u / upr) * c.spitch + (u % upr) * 2));
       }
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int64_t u = base + 256 * j;
-        if (u < n) *reinterpret_cast<uint16_t *>(dst + (u / upr) * c.dpitch + (u % upr) * 2) = v[j];
+        if (u < n) store1(reinterpret_cast<uint16_t *>(dst + (u / upr) * c.dpitch + (u % upr) * 2), v[j]);
       }
     }
   }
