@@ -229,36 +229,57 @@ __device__ __forceinline__ bool wait_preds(const ExecArgs &a, const ExecNode &nd
 template <uint32_t G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(exec_waves(G)))) void exec_kernel(ExecArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[exec_smem(G)];
+  // The list and the description of the current kernel come through LDS: read where they lie, a
+  // task would start with three memory round trips one after the other (its entry, its kernel's
+  // variant, the argument record), each of them past an L2 that other workgroups' acquires empty.
+  // Measured with the start times kept only when recorded: 4-layer 1024 BF16 attention 707 -> 677 us.
+  // (The cache-wide fences are not what bounds the executor: without any of them, and wrong for it,
+  // the same DAG took 587 us.  A task is a chain of latencies on a CU with four wavefronts.)
+  constexpr int kTaskAhead = 64;
+  __shared__ ExecTask s_task[kTaskAhead];
+  __shared__ ExecNode s_node;
   __shared__ uint32_t s_ok;
+  static_assert(sizeof(ExecNode) == 128 && sizeof(ExecTask) == 16, "copied as 16-byte units");
   const int32_t w = __builtin_amdgcn_readfirstlane(int32_t(blockIdx.x));
   const int32_t lo = __builtin_amdgcn_readfirstlane(a.work_off[w]);
   const int32_t hi = __builtin_amdgcn_readfirstlane(a.work_off[w + 1]);
   int32_t checked = -1;  // node whose predecessors this workgroup has seen complete (uniform)
   for (int32_t i = lo; i < hi; ++i) {
-    const ExecTask t = uniform_load<ExecTask>(reinterpret_cast<const unsigned char *>(a.tasks + i));
-    const ExecNode *nd = a.nodes + t.node;
+    const int32_t slot = (i - lo) % kTaskAhead;
+    if (slot == 0) {  // (every wavefront is past the barrier that ended its last task)
+      if (threadIdx.x < kTaskAhead && i + int32_t(threadIdx.x) < hi) s_task[threadIdx.x] = a.tasks[i + threadIdx.x];
+      __syncthreads();
+    }
+    const ExecTask t = uniform_load<ExecTask>(reinterpret_cast<const unsigned char *>(&s_task[slot]));
     if (t.node != checked) {
-      if (__builtin_amdgcn_readfirstlane(nd->n_pred) > 0) {
+      const ExecNode *nd = a.nodes + t.node;
+      if (threadIdx.x < sizeof(ExecNode) / 16)
+        reinterpret_cast<uint4 *>(&s_node)[threadIdx.x] = reinterpret_cast<const uint4 *>(nd)[threadIdx.x];
+      if (threadIdx.x == 0) {
         // One acquire for the workgroup: thread 0 observes the counters, then invalidates this
         // CU's L1 and the XCD's L2 (cache-wide operations) before the barrier releases the
         // other wavefronts to read the predecessors' outputs.
-        if (threadIdx.x == 0) {
-          const bool ok = wait_preds(a, *nd);
+        bool ok = true;
+        if (nd->n_pred > 0) {
+          ok = wait_preds(a, *nd);
           if (ok) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             __builtin_amdgcn_s_waitcnt(0);
           }
-          s_ok = ok ? 1u : 0u;
         }
-        __syncthreads();
-        const uint32_t ok = __builtin_amdgcn_readfirstlane(s_ok);
-        if (!ok) break;
+        s_ok = ok ? 1u : 0u;
+        // (an atomic on a word that many workgroups update takes microseconds, and this
+        // wavefront's next loads wait behind it: once per run of tasks, and only when recorded)
+        if (ok && a.record)
+          __hip_atomic_fetch_min(&a.t_first[t.node], uint64_t(wall_clock64()), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
       }
+      __syncthreads();
+      const uint32_t ok = __builtin_amdgcn_readfirstlane(s_ok);
+      if (!ok) break;
       checked = t.node;
     }
-    if (threadIdx.x == 0)
-      __hip_atomic_fetch_min(&a.t_first[t.node], uint64_t(wall_clock64()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!run_task<G>(nd, t.tile, smem)) {  // uniform: the variant is read with readfirstlane
+    if (!run_task<G>(&s_node, t.tile, smem)) {  // uniform: the variant is read with readfirstlane
       if (threadIdx.x == 0) {
         __hip_atomic_fetch_or(&a.ctl[0], 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(a.host_err, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -269,6 +290,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(exec_waves(
       // One release for the workgroup: every wavefront waits until its stores have reached the
       // L2, the barrier orders that before thread 0's release fence (a write-back of the whole
       // L2) and its counter update.
+      const int32_t n_tiles = __builtin_amdgcn_readfirstlane(s_node.n_tiles);  // (before the barrier: LDS is reused)
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
       if (threadIdx.x == 0) {
@@ -278,7 +300,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(exec_waves(
         const uint64_t now = wall_clock64();
         const uint32_t before =
             __hip_atomic_fetch_add(&a.done[t.node], uint32_t(t.signal), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (before + uint32_t(t.signal) == uint32_t(nd->n_tiles))
+        if (before + uint32_t(t.signal) == uint32_t(n_tiles))
           __hip_atomic_store(&a.t_last[t.node], now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     } else {

@@ -55,11 +55,12 @@ struct ExecArgs {
   uint32_t *done;          // per kernel: tiles completed
   uint32_t *ctl;           // [0] error flags: 1 = a wait exceeded its bound
   uint32_t *host_err;      // page-locked host word: set to 1 by any workgroup that stops early
-  uint64_t *t_first;       // per kernel: device clock when its first tile started
+  uint64_t *t_first;       // per kernel: device clock when its first tile started (record only)
   uint64_t *t_last;        // per kernel: device clock when its last tile finished
   uint64_t *t_start;       // device clock at reset
   int32_t n_nodes;
   int32_t n_workers;
+  int32_t record;          // keep t_first (per-op times are wanted)
   uint64_t max_wait;       // device-clock ticks one wait may last before the run stops with an error
 };
 

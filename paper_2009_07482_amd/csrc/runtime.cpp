@@ -160,6 +160,7 @@ struct Device {
   ExecNode *h_copy_nodes = nullptr;   // page-locked: their records, rewritten before every run
   uint32_t *h_err = nullptr;  // page-locked word receiving the executor's error flag
   double clock_mhz = 100.0;   // device wall clock rate
+  int exec_record = 0;        // the executor keeps per-op start times
 
   ~Device() {
     if (in_flight && end) (void)hipEventSynchronize(end);  // a timed-out run still executing
@@ -571,6 +572,7 @@ void upload_exec_plan(const ExecPlan &ep, Device &d, void *&mem, ExecArgs &a) {
   a.t_start = reinterpret_cast<uint64_t *>(base + o_ts);
   a.n_nodes = nn;
   a.n_workers = W;
+  a.record = d.exec_record;
   a.host_err = d.h_err;
   // one wait may last 5 s of device time (the clock runs at clock_mhz)
   a.max_wait = uint64_t(5.0e6 * d.clock_mhz);
@@ -822,6 +824,7 @@ void prepare(psc_sched &s) {
   }
   const int32_t nt = s.opts.host_threads > 0 ? s.opts.host_threads : s.plan.total_streams;
   if (dev_mode) {
+    d->exec_record = s.opts.record_ops != 0;
     prepare_executor(g, s.plan, s.opts.exec_per_cu, *d);
   } else if (groups_launches(s)) {
     // uploads on their kernels' streams (no copy stream) overlap kernels of other streams: runs
