@@ -47,6 +47,35 @@ def test_gemm_windows_exact(dt, tile):
             np.testing.assert_array_equal(out["C"], a.astype(np.float64) @ b.astype(np.float64))
 
 
+@pytest.mark.parametrize("out_dt", ["f32", "bf16"])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("policy,tile", [("coarse", t) for t in range(psc.psc_gemm_tile_count())] + [("device", 0)])
+def test_gemm_stores_stay_in_their_columns(policy, tile, dt, out_dt):
+    """Products into neighbouring column windows of one matrix, of every width modulo the four
+    columns that a lane stores: exact, so no store reaches into the window to its right."""
+    g = np.random.default_rng(70 + tile)
+    m, k, widths = 37, 9, (67, 1, 66, 2, 65, 3, 4)    # sums of nine ternary products: exact in bf16
+    spec = {"buffers": [{"name": "A", "dtype": dt, "rows": m, "cols": k, "view_of": None, "row_off": 0, "col_off": 0},
+                        {"name": "C", "dtype": out_dt, "rows": m, "cols": sum(widths), "view_of": None, "row_off": 0,
+                         "col_off": 0}],
+            "kernels": [], "edges": [], "component": [0] * len(widths)}
+    a = g.integers(-1, 2, (m, k)).astype(np.float32)
+    inp, at = {"A": a}, 0
+    for i, n in enumerate(widths):
+        spec["buffers"] += [{"name": f"B{i}", "dtype": dt, "rows": k, "cols": n, "view_of": None, "row_off": 0,
+                             "col_off": 0},
+                            {"name": f"C{i}", "dtype": out_dt, "rows": m, "cols": n, "view_of": "C", "row_off": 0,
+                             "col_off": at}]
+        spec["kernels"].append({"name": f"k{i}", "kind": "gemm", "inputs": ["A", f"B{i}"], "outputs": [f"C{i}"],
+                                "alpha": 1.0, "tile": tile})
+        inp[f"B{i}"] = g.integers(-1, 2, (k, n)).astype(np.float32)
+        at += n
+    print(f"gemm {dt} -> {out_dt} tile {tile} {policy}", flush=True)
+    out, _ = psc.run_spec(spec, inp, policy)
+    for i in range(len(widths)):
+        np.testing.assert_array_equal(out[f"C{i}"], a.astype(np.float64) @ inp[f"B{i}"].astype(np.float64))
+
+
 @pytest.mark.parametrize("policy", ["coarse", "device"])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("r,c,pad", [(3, 1, 1), (65, 7, 3), (9, 257, 1), (66, 515, 3), (5, 1001, 1), (4, 2047, 3)])
