@@ -141,6 +141,8 @@ __device__ __forceinline__ bool run_task(const ExecNode *ndp, int tile, unsigned
     PSC_TASK(163, gemm_direct_tile<4, false, true, 8>(uniform_load<GemmArgs>(nd.args), tile, smem));
     PSC_TASK(210, gemm_bf16_tile<64, 64, 64, 32, 32, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
     PSC_TASK(211, gemm_bf16_tile<64, 64, 64, 32, 32, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(206, gemm_bf16_tile<128, 128, 64, 64, 64, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(207, gemm_bf16_tile<128, 128, 64, 64, 64, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
     PSC_TASK(266, gemm_bf16_splitk_tile<64, 64, false, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
     PSC_TASK(267, gemm_bf16_splitk_tile<64, 64, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
     PSC_TASK(254, gemm_direct_tile<1, true, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
@@ -318,7 +320,7 @@ constexpr uint32_t kInstances[] = {
     kGElem | (1u << 3) | (1u << 4) | (1u << 5),                 // FP32: aligned direct-load tiles
     kGElem | (1u << 10) | (1u << 11) | (1u << 12),              // BF16: aligned direct-load tiles
     kGElem | (1u << 0) | (1u << 3) | (1u << 4) | (1u << 5),     // FP32 attention: + 64 x 64 tile
-    kGElem | (1u << 6) | (1u << 10) | (1u << 11) | (1u << 12),  // BF16 attention: + 64 x 64 tile
+    kGElem | (3u << 6) | (1u << 10) | (1u << 11) | (1u << 12),  // BF16 attention: + 64 x 64, 128 x 128 tiles
     kGF32All,                                                  // every FP32 tile function
     kGBf16All,                                                 // every BF16 tile function
     kGAll};                                                    // everything
@@ -334,7 +336,7 @@ const void *exec_fn(int i) { return instance_fn(i, std::make_integer_sequence<in
 struct PCfg {
   int cfg, bm, bn;
 };
-constexpr PCfg kPersistentGemm[] = {{2, 64, 64}, {16, 64, 64}, {13, 16, 16}, {14, 16, 32}, {15, 16, 64}};
+constexpr PCfg kPersistentGemm[] = {{1, 128, 128}, {2, 64, 64}, {16, 64, 64}, {13, 16, 16}, {14, 16, 32}, {15, 16, 64}};
 
 }  // namespace
 
@@ -349,7 +351,7 @@ ExecNode make_exec_node(int kind, const unsigned char *args, int in_dtype, int o
       // so a task should carry more work than the standalone kernels' small tiles (made to fill
       // the GPU with one kernel).  `want` is the number of workgroups this kernel can expect:
       // take the largest tile that still gives at least `want` tasks, else the smallest.
-      // Candidates, largest first: 64 x 64 (LDS staged), then 16 x 64 / 16 x 32 / 16 x 16
+      // Candidates, largest first: 128 x 128 and 64 x 64 (LDS staged), then 16 x 64 / 16 x 32 / 16 x 16
       // direct-load tiles -- one memory round trip per wavefront for its share of K, where an
       // LDS-staged 32 x 32 tile pays one per K step (measured: the 512 x 512 x 512 output
       // projection of the attention DAG in 256 tasks, 3.6% shorter makespan).  A 16-row task
@@ -359,12 +361,16 @@ ExecNode make_exec_node(int kind, const unsigned char *args, int in_dtype, int o
       // each wavefront multiplies the whole 64 x 64 block over its own quarter of K, one 64-deep
       // chunk at a time, and the four partial blocks are summed through LDS): the staged tile
       // steps through K one 64-deep slice per block barrier, a memory round trip each, sixteen
-      // for K = 1024 against four.  (`tile`, the standalone choice, is unused.)
+      // for K = 1024 against four.  A BF16 product with K < 256, which is one to three of the staged
+      // tile's steps, takes 128 x 128 tiles where there are enough of them: such a task is a round
+      // trip for its operands whatever it multiplies, so the 1024 x 64 x 1024 scores of a 16-head
+      // attention layer take four per workgroup instead of sixteen (4-layer 1024 BF16 attention 650
+      // -> 608 us).  (`tile`, the standalone choice, is unused.)
       (void)tile;
       int cfg = -1;
-      static constexpr int c0[] = {2, 15, 14, 13};
+      static constexpr int c0[] = {1, 2, 15, 14, 13};
       constexpr int nc = sizeof(c0) / sizeof(c0[0]);
-      for (int i = 0; i < nc && cfg < 0; ++i) {
+      for (int i = in_dtype == 1 && g.K < 256 ? 0 : 1; i < nc && cfg < 0; ++i) {
         int bm = 16, bn = 16;
         for (const PCfg &c : kPersistentGemm)
           if (c.cfg == c0[i]) { bm = c.bm; bn = c.bn; }

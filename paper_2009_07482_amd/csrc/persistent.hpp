@@ -71,7 +71,8 @@ ExecNode make_exec_node(int kind, const unsigned char *args, int in_dtype, int o
 
 // Tile-function groups: the group bit of a node variant (0 for the empty variant 0).  Groups 0
 // and 3-5: FP32 GEMM tiles (64 x 64 staged through LDS, direct-load with 1, 2 and 4 column
-// blocks); 6 and 10-12: the BF16 ones; 13: softmax, transpose, add and the host copies; 14: the
+// blocks); 6 and 10-12: the BF16 ones; 7: the BF16 128 x 128
+// staged tile; 13: softmax, transpose, add and the host copies; 14: the
 // BF16 64 x 64 K-split tile (its registers alone exceed what two workgroups per CU leave, so only
 // the one-per-CU instances hold it).
 constexpr uint32_t kGElem = 1u << 13;
@@ -80,6 +81,7 @@ __host__ __device__ constexpr uint32_t exec_variant_group(int v) {
        : v == 154 || v == 155 ? 1u << 3
        : v == 158 || v == 159 ? 1u << 4
        : v == 162 || v == 163 ? 1u << 5
+       : v == 206 || v == 207 ? 1u << 7
        : v == 210 || v == 211 ? 1u << 6
        : v == 254 || v == 255 ? 1u << 10
        : v == 258 || v == 259 ? 1u << 11

@@ -97,3 +97,29 @@ def test_elementwise_windows(policy, dt, r, c, pad):
     np.testing.assert_array_equal(out["T"], np.asarray(a, np.float64).T)
     # FP32 exponentials and sums (~1e-7 each), and for BF16 output the rare rounding they flip
     assert normwise(out["P"], oracle_outputs(spec, inp, emulate=True)["P"]) < (1e-5 if dt == "f32" else 1e-3)
+
+
+@pytest.mark.parametrize("out_dt", ["f32", "bf16"])
+@pytest.mark.parametrize("m,n,k", [(128, 128, 64), (129, 127, 1), (257, 130, 65), (64, 300, 255), (130, 1, 128),
+                                   (256, 384, 200)])
+def test_executor_short_products_exact(m, n, k, out_dt):
+    """Products of K < 256 on the device executor, in DAGs narrow and wide enough that its tiles are
+    the smallest and the largest: exact."""
+    g = np.random.default_rng(90)
+    for width in (1, 96):
+        spec = {"buffers": [], "kernels": [], "edges": [], "component": list(range(width))}
+        inp, want = {}, {}
+        for i in range(width):
+            pad = i % 2
+            spec["buffers"] += _window(f"A{i}", "bf16", m, k, pad) + _window(f"B{i}", "bf16", k, n, pad) + \
+                _window(f"C{i}", out_dt, m, n, pad)
+            spec["kernels"].append({"name": f"k{i}", "kind": "gemm", "inputs": [f"A{i}", f"B{i}"],
+                                    "outputs": [f"C{i}"], "alpha": 1.0, "tile": 0})
+            a = g.integers(-1, 2, (m, k)).astype(np.float32)
+            b = g.integers(-1, 2, (k, n)).astype(np.float32)
+            inp[f"A{i}r"], inp[f"B{i}r"] = _embed(a, spec, f"A{i}"), _embed(b, spec, f"B{i}")
+            want[f"C{i}"] = a.astype(np.float64) @ b.astype(np.float64)   # |sums| <= 255: exact in bf16
+        print(f"executor {m}x{n}x{k} -> {out_dt}, {width} kernels", flush=True)
+        out, _ = psc.run_spec(spec, inp, "device")
+        for name, w in want.items():
+            np.testing.assert_array_equal(out[name], w)
