@@ -623,12 +623,7 @@ constexpr int gemm_bf16_splitk_smem() {
   return stage > red ? stage : red;
 }
 
-// PREFETCH = false loads each chunk just before staging it instead of during the previous
-// chunk's products: no staging registers live beside the fragments and accumulators (for the
-// 64 x 64 tile, whose 64 accumulator registers per lane would otherwise push a two-wavefront-per-
-// SIMD kernel into spills), at the price of the overlap, which matters little when a wavefront
-// has only a few chunks.
-template <int TM, int TN, bool OUT_BF16, bool PREFETCH = true>
+template <int TM, int TN, bool OUT_BF16>
 __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid, unsigned char *smem) {
   constexpr int BK = 64, KP = kAPitch, BP = b_pitch<TN>(), FM = TM / 16, FN = TN / 16;
   constexpr int UA = TM * (BK / 8) / 64, UB = BK * (TN / 8) / 64;  // 8-element loads per lane
@@ -684,11 +679,10 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
 
   const uint16_t *const a_frag = As + (lane & 15) * KP + 8 * (lane >> 4);
   const uint16_t *const b_lane = Bs + b_frag_lane<TN>(lane);
-  if (PREFETCH) load(w);
+  load(w);
   for (int it = 0; it < iters; ++it) {
     // no block barrier in this loop: each wavefront stages and reads only its own LDS region,
     // and one wavefront's LDS operations take effect in program order
-    if (!PREFETCH) load(it * 4 + w);
 #pragma unroll
     for (int j = 0; j < UA; ++j) *reinterpret_cast<uint4 *>(&As[(ar + 8 * j) * KP + ac]) = ra[j];
 #pragma unroll
@@ -696,7 +690,7 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
       if (raw && !n_whole) rb[j] = shift_down(rb[j], b_bits);
       *reinterpret_cast<uint4 *>(&Bs[(br + j * BR) * BP + bc - n0]) = rb[j];
     }
-    if (PREFETCH && it + 1 < iters) load((it + 1) * 4 + w);
+    if (it + 1 < iters) load((it + 1) * 4 + w);
     // (the fence keeps the compiler from moving the transposing reads above the stores)
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
