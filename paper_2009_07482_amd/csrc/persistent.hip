@@ -297,6 +297,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(exec_waves(
       __syncthreads();
       if (threadIdx.x == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        // The write-back is only started by the fence's instruction: the fence's own wait comes
+        // after it, but the compiler drops that wait as done by the one above (every store of the
+        // wavefront has completed; it does not count the write-back).  Without this one the counter
+        // could be added to before the tiles were in memory, and another XCD read stale ones.
+        __builtin_amdgcn_s_waitcnt(0);
         // the end time is read before the add: a consumer may see the count complete (and stamp
         // its own start) while this returning add is still on its way back
         const uint64_t now = wall_clock64();
