@@ -1345,6 +1345,59 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// The rest of a row held in registers (chunk t of lane l starts at column (64 t + l) CW; -inf past
+// the last column): exponentials, sum, store.  m: the lane's own maximum.
+template <bool OUT_BF16, bool NT, int CW, int NC>
+__device__ __forceinline__ void softmax_finish(const SoftmaxArgs &p, int row, float (&v)[NC][CW], float m) {
+  const int lane = threadIdx.x & 63;
+  const int64_t yo = int64_t(row) * p.ldy;
+  const float ninf = -__builtin_huge_valf();
+  m = wave_max(m);
+  float s = 0.f;
+#pragma unroll
+  for (int t = 0; t < NC; ++t)
+#pragma unroll
+    for (int e = 0; e < CW; ++e) {
+      const float ex = (v[t][e] == ninf) ? 0.f : __expf(v[t][e] - m);
+      v[t][e] = ex;
+      s += ex;
+    }
+  s = wave_sum(s);
+  const float inv = 1.0f / s;
+#pragma unroll
+  for (int t = 0; t < NC; ++t) {
+    const int c = (t * 64 + lane) * CW;
+    if (c + CW - 1 < p.C) {
+#pragma unroll
+      for (int h = 0; h < CW / 4; ++h) {
+        const float *q = &v[t][4 * h];
+        if constexpr (OUT_BF16 && CW == 8) {
+          if (h == 0) {
+            const float *q8 = v[t];
+            u32x4 w;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              w[k] = uint32_t(f32_to_bf16(q8[2 * k] * inv)) | (uint32_t(f32_to_bf16(q8[2 * k + 1] * inv)) << 16);
+            store16<NT>(static_cast<uint16_t *>(p.Y) + yo + c, w);
+          }
+        } else if constexpr (OUT_BF16) {
+          const u32x2 w = {uint32_t(f32_to_bf16(q[0] * inv)) | (uint32_t(f32_to_bf16(q[1] * inv)) << 16),
+                           uint32_t(f32_to_bf16(q[2] * inv)) | (uint32_t(f32_to_bf16(q[3] * inv)) << 16)};
+          store8<NT>(static_cast<uint16_t *>(p.Y) + yo + c + 4 * h, w);
+        } else {
+          const u32x4 w = {__float_as_uint(q[0] * inv), __float_as_uint(q[1] * inv),
+                           __float_as_uint(q[2] * inv), __float_as_uint(q[3] * inv)};
+          store16<NT>(static_cast<float *>(p.Y) + yo + c + 4 * h, w);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < CW; ++e)
+        if (c + e < p.C) store_elem<OUT_BF16>(p.Y, yo + c + e, v[t][e] * inv);
+    }
+  }
+}
+
 template <int NV, bool IN_BF16, bool OUT_BF16, bool NT = false, int CW = 4>
 __device__ __forceinline__ void softmax_row(const SoftmaxArgs &p, int row) {
   const int lane = threadIdx.x & 63;
@@ -1384,50 +1437,7 @@ __device__ __forceinline__ void softmax_row(const SoftmaxArgs &p, int row) {
 #pragma unroll
       for (int e = 0; e < CW; ++e) m = fmaxf(m, v[t][e]);
     }
-    m = wave_max(m);
-    float s = 0.f;
-#pragma unroll
-    for (int t = 0; t < NC; ++t)
-#pragma unroll
-      for (int e = 0; e < CW; ++e) {
-        const float ex = (v[t][e] == ninf) ? 0.f : __expf(v[t][e] - m);
-        v[t][e] = ex;
-        s += ex;
-      }
-    s = wave_sum(s);
-    const float inv = 1.0f / s;
-#pragma unroll
-    for (int t = 0; t < NC; ++t) {
-      const int c = (t * 64 + lane) * CW;
-      if (c + CW - 1 < p.C) {
-#pragma unroll
-        for (int h = 0; h < CW / 4; ++h) {
-          const float *q = &v[t][4 * h];
-          if constexpr (OUT_BF16 && CW == 8) {
-            if (h == 0) {
-              const float *q8 = v[t];
-              u32x4 w;
-#pragma unroll
-              for (int k = 0; k < 4; ++k)
-                w[k] = uint32_t(f32_to_bf16(q8[2 * k] * inv)) | (uint32_t(f32_to_bf16(q8[2 * k + 1] * inv)) << 16);
-              store16<NT>(static_cast<uint16_t *>(p.Y) + yo + c, w);
-            }
-          } else if constexpr (OUT_BF16) {
-            const u32x2 w = {uint32_t(f32_to_bf16(q[0] * inv)) | (uint32_t(f32_to_bf16(q[1] * inv)) << 16),
-                             uint32_t(f32_to_bf16(q[2] * inv)) | (uint32_t(f32_to_bf16(q[3] * inv)) << 16)};
-            store8<NT>(static_cast<uint16_t *>(p.Y) + yo + c + 4 * h, w);
-          } else {
-            const u32x4 w = {__float_as_uint(q[0] * inv), __float_as_uint(q[1] * inv),
-                             __float_as_uint(q[2] * inv), __float_as_uint(q[3] * inv)};
-            store16<NT>(static_cast<float *>(p.Y) + yo + c + 4 * h, w);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < CW; ++e)
-          if (c + e < p.C) store_elem<OUT_BF16>(p.Y, yo + c + e, v[t][e] * inv);
-      }
-    }
+    softmax_finish<OUT_BF16, NT, CW>(p, row, v, m);
   } else {
     float m = ninf;
     for (int c = lane; c < p.C; c += 64) m = fmaxf(m, load_elem<IN_BF16>(p.X, xo + c));
@@ -1438,6 +1448,34 @@ __device__ __forceinline__ void softmax_row(const SoftmaxArgs &p, int row) {
     const float inv = 1.0f / s;
     for (int c = lane; c < p.C; c += 64)
       store_elem<OUT_BF16>(p.Y, yo + c, __expf(load_elem<IN_BF16>(p.X, xo + c) - m) * inv);
+  }
+}
+
+// NR rows of exactly 256 NV columns, `stride` rows apart: every load of all of them is issued, with
+// no check between, before the first row is reduced.
+template <int NR, int NV, bool IN_BF16, bool OUT_BF16>
+__device__ __forceinline__ void softmax_whole_rows(const SoftmaxArgs &p, int row, int stride) {
+  using V = typename std::conditional<IN_BF16, u32x2, u32x4>::type;  // four elements
+  const int lane = threadIdx.x & 63;
+  V raw[NR][NV];
+#pragma unroll
+  for (int j = 0; j < NR; ++j)
+#pragma unroll
+    for (int t = 0; t < NV; ++t)
+      raw[j][t] = load_as<V>(static_cast<const unsigned char *>(p.X) +
+                             (int64_t(row + j * stride) * p.ldx + (t * 64 + lane) * 4) * (IN_BF16 ? 2 : 4));
+#pragma unroll
+  for (int j = 0; j < NR; ++j) {
+    float v[NV][4], m = -__builtin_huge_valf();
+#pragma unroll
+    for (int t = 0; t < NV; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (IN_BF16) v[t][e] = __uint_as_float((e & 1) ? raw[j][t][e / 2] & 0xffff0000u : raw[j][t][e / 2] << 16);
+        else v[t][e] = __uint_as_float(raw[j][t][e]);
+        m = fmaxf(m, v[t][e]);
+      }
+    softmax_finish<OUT_BF16, false, 4>(p, row + j * stride, v, m);
   }
 }
 

@@ -123,3 +123,30 @@ def test_executor_short_products_exact(m, n, k, out_dt):
         out, _ = psc.run_spec(spec, inp, "device")
         for name, w in want.items():
             np.testing.assert_array_equal(out[name], w)
+
+
+@pytest.mark.parametrize("dt,out_dt", [("f32", "f32"), ("f32", "bf16"), ("bf16", "f32"), ("bf16", "bf16")])
+@pytest.mark.parametrize("c", [256, 512, 1024, 2048])
+def test_executor_softmax_of_whole_rows(c, dt, out_dt):
+    """Rows that fill the executor's registers exactly and rows one short of it, over whole and partial
+    tasks of 16 rows, with entries of -inf: the same as each row by itself (another matrix, whose
+    rows start elsewhere in their task)."""
+    for r in (16, 33):
+        for cols in (c, c - 1):
+            print(f"executor softmax {r}x{cols} {dt} -> {out_dt}", flush=True)
+            spec = {"buffers": [], "kernels": [], "edges": [], "component": [0, 1]}
+            x = uniform(91, (r, cols), -8, 8)
+            x[::3, 5] = -np.inf
+            inp = {}
+            for n, v in (("A", x), ("B", x[::-1])):
+                spec["buffers"] += _window(n, dt, r, cols, 1) + _window("P" + n, out_dt, r, cols, 3)
+                spec["kernels"].append({"name": "k" + n, "kind": "softmax", "inputs": [n], "outputs": ["P" + n],
+                                        "alpha": 1.0, "tile": 0})
+                inp[n + "r"] = _embed(v, spec, n)
+            out, _ = psc.run_spec(spec, inp, "device")
+            np.testing.assert_array_equal(out["PA"], out["PB"][::-1])
+            xr = (round_bf16(x) if dt == "bf16" else x).astype(np.float64)
+            e = np.exp(xr - xr.max(axis=1, keepdims=True))
+            # FP32 exponentials and a sum of up to 2048 terms; BF16 output: half a unit of 2^-8
+            err = np.abs(out["PA"] - e / e.sum(axis=1, keepdims=True)) / (e / e.sum(axis=1, keepdims=True)).max()
+            assert err.max() < (1e-5 if out_dt == "f32" else 2.0 ** -8)
