@@ -21,12 +21,12 @@ struct GroupedPlan {
   std::vector<int32_t> op_of;  // per op: the op of the original plan (a unit: its first kernel's)
 };
 
-// The launch groups of `plan` (an in-order PSC_FINE or PSC_COARSE plan of `g`).  Two kernels may
+// The launch groups of `plan` (an in-order PSC_FINE plan of `g`).  Two kernels may
 // share a launch if they lie on one stream, have the same key (>= 0; -1 = never) and the same level
 // (longest path from a root: a kernel of a later level would run ahead of what the plan puts before
 // it), and a launch takes no further kernel once its kernels have `max_blocks` workgroups
-// (`blocks`, per kernel).  A kernel joins the latest open launch of its stream, level and key if every op it depends on comes
-// before that launch's first kernel in host order.  Each launch then stands at its first
+// (`blocks`, per kernel).  A kernel joins the latest open launch of its stream, level and key if
+// every op it depends on comes before that launch's first kernel in host order.  Each launch then stands at its first
 // kernel's place, where everything any of its kernels depends on has been enqueued: the order
 // stays topological, so no wait can close a cycle, and no two kernels of a launch depend on each
 // other.  copies = false leaves the uploads and read-backs out (a run without host memory), so

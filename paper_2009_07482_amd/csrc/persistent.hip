@@ -245,8 +245,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(exec_waves(
   // task would start with three memory round trips one after the other (its entry, its kernel's
   // variant, the argument record), each of them past an L2 that other workgroups' acquires empty.
   // Measured with the start times kept only when recorded: 4-layer 1024 BF16 attention 707 -> 677 us.
-  // (The cache-wide fences are not what bounds the executor: without any of them, and wrong for it,
-  // the same DAG took 587 us.  A task is a chain of latencies on a CU with four wavefronts.)
+  // (The cache-wide fences are not what bounds the executor: of 655 us they took 70.  A task is a
+  // chain of latencies on a CU with four wavefronts.)
   constexpr int kTaskAhead = 64;
   __shared__ ExecTask s_task[kTaskAhead];
   __shared__ ExecNode s_node;

@@ -727,7 +727,7 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
 // share of K in flight at once.  Wavefront w owns the contiguous K chunks (64 deep) [w q, (w+1) q),
 // q = ceil(chunks / 4); it loads D of them into registers in one go -- for K up to 256 D one
 // memory round trip in all -- stages them in its own LDS region (A as rows, B as (k, k + 1) pairs
-// per column, as in the tile above), then multiplies them in order.  The four partial tiles are
+// per column), then multiplies them in order.  The four partial tiles are
 // summed through LDS in the order w = 0, 1, 2, 3.  Trip counts are uniform across wavefronts
 // (chunks past the end are zero-filled), so every __syncthreads is reached by all of them.
 // For the attention projections (1024 x 64 x 1024: few output tiles, a long K) the staged tile
