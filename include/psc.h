@@ -439,7 +439,9 @@ psc_status psc_sched_prepare(psc_sched *sched);
  * all their workgroups, placed where the first of them stands: the precedences, the buffers and
  * the results are those of one launch per kernel, and psc_sched_export keeps describing the plan
  * kernel by kernel.  GEMMs with an automatic tile take one that suits the launch, among those that
- * sum in the same order.  The streams are carried by as many hardware queues as a prediction of the
+ * sum in the order of the size heuristic's tile.  (Once a tile of another order is in the tile cache
+ * for one of the two kinds of launch, their results may differ in rounding; within one schedule all
+ * kernels of a shape sum in one order.)  The streams are carried by as many hardware queues as a prediction of the
  * run finds fastest, stream s by queue s mod that count (runs with host copies on kernel streams
  * keep one queue per stream).  Every kernel keeps its own launch and stream under record_ops, mark_components,
  * use_graph, fault_inject_op and out_of_order, and under every other policy.
@@ -643,18 +645,21 @@ psc_status psc_sched_device_tasks(const psc_sched *sched, int32_t workers, int32
  * leading dimensions that are multiples of 8, else they run as tile 4; with FP32 operands they
  * run as tile 1.  A GEMM whose params leave tile at
  * 0 takes the process-wide cache entry for its (M, N, K, operand dtype, output dtype) when there
- * is one, and a size heuristic otherwise; the choice is made when a schedule is prepared.  The
- * cache is thread safe.  (The paper leaves autotuning to future work, Sec. VII.)
+ * is one, and a size heuristic otherwise; the choice is made when a schedule is prepared.  An entry
+ * holds a choice for launches of one kernel and one for launches of several (see psc_run), either
+ * of which may be missing: what suits a kernel alone leaves a shared launch slow and the other way
+ * round.  The cache is thread safe.  (The paper leaves autotuning to future work, Sec. VII.)
  * ------------------------------------------------------------------------------------------- */
 
 /* Number of tile configuration indices (valid configurations are 1 .. *n - 1). */
 psc_status psc_gemm_tile_count(int32_t *n);
 
-/* Sets (tile > 0) or removes (tile = 0) the cache entry for one GEMM shape and dtype pair. */
+/* Sets (tile > 0, for both kinds of launch) or removes (tile = 0) the cache entry for one GEMM shape
+ * and dtype pair. */
 psc_status psc_tile_cache_set(int32_t M, int32_t N, int32_t K, int32_t ab_dtype, int32_t c_dtype,
                               int32_t tile);
 
-/* Cache entry for a shape, 0 if none. */
+/* Cached choice for a launch of one kernel of this shape, 0 if none. */
 psc_status psc_tile_cache_get(int32_t M, int32_t N, int32_t K, int32_t ab_dtype, int32_t c_dtype,
                               int32_t *tile);
 
@@ -666,7 +671,8 @@ psc_status psc_tile_cache_clear(int32_t *n_removed);
  * bytes including the NUL; PSC_ERR_ARG if it does not fit. */
 psc_status psc_tile_cache_key(int32_t device, char *key, int32_t cap);
 /* Host-only: writes every cached tile choice to `path` (text: a header, the key, one line per
- * (M, N, K, operand dtype, output dtype, tile), a checksum line; written to path.tmp and renamed)
+ * choice, "entry" for launches of one kernel and "shared" for launches of several, with (M, N, K,
+ * operand dtype, output dtype, tile), a checksum line; written to path.tmp and renamed)
  * under `key` (a word without blanks, normally psc_tile_cache_key's).  PSC_ERR_IO if it cannot
  * be written. */
 psc_status psc_tile_cache_save(const char *path, const char *key);
@@ -674,7 +680,8 @@ psc_status psc_tile_cache_save(const char *path, const char *key);
  * cached one for its shape).  The file is checked whole before anything is merged: PSC_ERR_IO
  * if it is missing, malformed, altered (checksum) or names a tile outside 1 .. count-1;
  * PSC_ERR_STATE if it was saved under another key (another architecture, runtime or library
- * version: its timings do not apply).  *n_loaded (may be NULL) = entries merged. */
+ * version: its timings do not apply).  *n_loaded (may be NULL) = entries merged
+ * (shapes). */
 psc_status psc_tile_cache_load(const char *path, const char *key, int32_t *n_loaded);
 
 /* [GPU] Times every tile configuration for C (M x N) = A (M x K) * B (K x N) on zero-filled
@@ -683,7 +690,9 @@ psc_status psc_tile_cache_load(const char *path, const char *key, int32_t *n_loa
  * *best_us.  us_per_tile[t] for t < cap receives every configuration's time (index 0 unused);
  * a configuration that resolves to another for this shape and dtype (16-21 with FP32 operands,
  * 16, 20 and 21 on shapes that are not whole 256 x 256 tiles) is not timed and its entry is left
- * unchanged, so the cache always names the tile a launch uses.
+ * unchanged, so the cache always names the tile a launch uses.  The choice is the one for launches
+ * of one kernel; the shape's choice for shared launches, if any, is removed (the size heuristic
+ * serves them again).
  * Any output pointer may be NULL.  Errors: PSC_ERR_ARG, PSC_ERR_HIP, PSC_ERR_OOM. */
 psc_status psc_autotune_gemm(int32_t device, int32_t M, int32_t N, int32_t K, int32_t ab_dtype,
                              int32_t c_dtype, int32_t iters, int32_t *best_tile, float *best_us,
@@ -699,12 +708,14 @@ psc_status psc_autotune_dag(psc_dag *dag, int32_t device, int32_t iters, int32_t
  * by holding more LDS and registers).  For every GEMM shape class of the DAG (operand and output
  * dtype included; kernels with a fixed tile are left alone) this first runs psc_autotune_gemm,
  * then, for the max_classes heaviest classes (isolated time x kernels), heaviest first, schedules
- * the DAG with `policy` and `opts` once per candidate among the class's top_k isolated tiles (and,
- * under PSC_FINE, the 64-column tiles 2, 6 and 7, which suit kernels launched together) -- the
+ * the DAG with `policy` and `opts` once per candidate among the class's top_k isolated tiles -- the
  * other classes at their current choice -- and times `iters` device-resident runs on seeded
  * inputs; the tile with the lowest median makespan goes into the tile cache (lighter classes keep
- * the isolated winner).  *n_changed (may be NULL) = classes whose choice differs from the
- * isolated winner.  The DAG must be schedulable with these options. */
+ * the isolated winner).  A class whose kernels share launches in that schedule (see psc_run) is tuned
+ * for shared launches only: its candidates are also the size heuristic and the 64-column tiles 2, 6
+ * and 7, and its choice for launches of one kernel stays the isolated winner.  *n_changed (may be
+ * NULL) = classes whose choice in the schedule is not the isolated winner.  The DAG must be
+ * schedulable with these options. */
 psc_status psc_autotune_dag_in_schedule(psc_dag *dag, int32_t policy, const psc_sched_opts *opts, int32_t top_k,
                                         int32_t max_classes, int32_t iters, int32_t *n_changed);
 

@@ -15,6 +15,7 @@
 
 #include "core.hpp"
 #include "dispatch.hpp"
+#include "kernels.hpp"
 #include "mlp.hpp"
 #include "persist.hpp"
 
@@ -40,12 +41,8 @@ void device_info(int device, char *name, int name_cap, char *arch, int arch_cap,
 int autotune_gemm(int device, int M, int N, int K, int ab, int c, int iters, float *best_us, float *us_per_tile,
                   int cap);
 int sched_kernel_tile(const psc_sched &s, int32_t kernel);
+bool sched_shares_launches(const psc_sched &s, int M, int N, int K, int ab, int c);
 void sched_executor_info(const psc_sched &s, int32_t *workers, int32_t *per_cu, uint32_t *groups);
-void tile_cache_set(int M, int N, int K, int ab, int c, int tile);
-int tile_cache_get(int M, int N, int K, int ab, int c);
-void tile_cache_clear();
-size_t tile_cache_size();
-int gemm_num_tiles();
 psc_dag *dag_from_json(const char *json, const char *const *sym_names, const int64_t *sym_values, int32_t n_sym,
                        psc_spec_info *info);
 }  // namespace psc
@@ -760,14 +757,14 @@ psc_status psc_tile_cache_set(int32_t M, int32_t N, int32_t K, int32_t ab_dtype,
     need(tile >= 0 && tile < psc::gemm_num_tiles(), PSC_ERR_ARG, "tile out of range");
     need((ab_dtype == PSC_F32 || ab_dtype == PSC_BF16) && (c_dtype == PSC_F32 || c_dtype == PSC_BF16), PSC_ERR_ARG,
          "bad dtype");
-    psc::tile_cache_set(M, N, K, ab_dtype, c_dtype, tile);
+    psc::tile_cache_set(M, N, K, ab_dtype, c_dtype, tile, psc::TileUse::both);
   });
 }
 
 psc_status psc_tile_cache_get(int32_t M, int32_t N, int32_t K, int32_t ab_dtype, int32_t c_dtype, int32_t *tile) {
   return guard([&] {
     need(tile != nullptr, PSC_ERR_ARG, "NULL tile");
-    *tile = psc::tile_cache_get(M, N, K, ab_dtype, c_dtype);
+    *tile = psc::tile_cache_get(M, N, K, ab_dtype, c_dtype, psc::TileUse::alone);
   });
 }
 
@@ -853,6 +850,7 @@ psc_status psc_autotune_dag_in_schedule(psc_dag *dag, int32_t policy, const psc_
       std::tuple<int, int, int, int, int> key;
       double weight;               // isolated best time x kernels of the class
       std::vector<int> candidates; // tiles by isolated time, fastest first
+      std::vector<int> large;      // further candidates for kernels that share launches
     };
     std::vector<Cls> cls;
     const int nt = psc::gemm_num_tiles();
@@ -866,18 +864,21 @@ psc_status psc_autotune_dag_in_schedule(psc_dag *dag, int32_t policy, const psc_
         if (us[t] > 0) order.push_back(t);
       std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return us[x] < us[y]; });
       if (int(order.size()) > top_k) order.resize(top_k);
-      // kernels that share a launch fill the GPU together, with tiles too large for one alone
-      if (policy == PSC_FINE && kv.second > 1)
-        for (int t : {2, 6, 7})
-          if (us[t] > 0 && std::find(order.begin(), order.end(), t) == order.end()) order.push_back(t);
-      cls.push_back({kv.first, double(best_us) * kv.second, order});
+      std::vector<int> large;
+      for (int t : {2, 6, 7})
+        if (us[t] > 0 && std::find(order.begin(), order.end(), t) == order.end()) large.push_back(t);
+      cls.push_back({kv.first, double(best_us) * kv.second, order, large});
     }
     std::stable_sort(cls.begin(), cls.end(), [](const Cls &x, const Cls &y) { return x.weight > y.weight; });
     if (int32_t(cls.size()) > max_classes) cls.resize(max_classes);   // the rest keep the isolated choice
-    auto makespan = [&]() {
+    auto schedule = [&]() {
       psc_sched *s = nullptr;
       psc_status st = psc_schedule(dag, policy, opts, &s);
       if (st != PSC_OK) psc::fail(st, psc_last_error());
+      return s;
+    };
+    auto makespan = [&]() {
+      psc_sched *s = schedule();
       std::vector<double> mk;
       try {
         psc::fill_inputs(*s);
@@ -895,23 +896,49 @@ psc_status psc_autotune_dag_in_schedule(psc_dag *dag, int32_t policy, const psc_
       std::nth_element(mk.begin(), mk.begin() + mk.size() / 2, mk.end());
       return mk[mk.size() / 2];
     };
+    // Classes whose kernels share launches in this schedule are tuned for that, among their
+    // isolated best, the tiles too large for one kernel alone and the automatic choice (0); their
+    // choice for launches of one kernel stays the isolated winner, which every other schedule of
+    // the process takes.
+    std::vector<char> shared(cls.size(), 0);
+    {
+      psc_sched *s = schedule();
+      try {
+        psc::prepare(*s);
+        for (size_t i = 0; i < cls.size(); ++i) {
+          const auto &[M, N, K, ab, cd] = cls[i].key;
+          shared[i] = psc::sched_shares_launches(*s, M, N, K, ab, cd);
+        }
+      } catch (...) {
+        psc_sched_destroy(s);
+        throw;
+      }
+      psc_sched_destroy(s);
+    }
     int32_t changed = 0;
     // coordinate descent, heaviest class first: each class's candidates timed in the schedule
     // with every other class at its current choice
-    for (const Cls &c : cls) {
-      if (c.candidates.size() < 2) continue;
+    for (size_t i = 0; i < cls.size(); ++i) {
+      const Cls &c = cls[i];
       const auto &[M, N, K, ab, cd] = c.key;
-      int best_t = c.candidates[0];
+      const psc::TileUse use = shared[i] ? psc::TileUse::shared : psc::TileUse::alone;
+      std::vector<int> candidates = c.candidates;
+      if (shared[i]) {
+        candidates.insert(candidates.begin(), 0);
+        candidates.insert(candidates.end(), c.large.begin(), c.large.end());
+      }
+      if (candidates.size() < 2) continue;
+      int best_t = candidates[0];
       double best_ms = -1;
-      for (int t : c.candidates) {
-        psc::tile_cache_set(M, N, K, ab, cd, t);
+      for (int t : candidates) {
+        psc::tile_cache_set(M, N, K, ab, cd, t, use);
         const double ms = makespan();
         if (best_ms < 0 || ms < best_ms) {
           best_ms = ms;
           best_t = t;
         }
       }
-      psc::tile_cache_set(M, N, K, ab, cd, best_t);
+      psc::tile_cache_set(M, N, K, ab, cd, best_t, use);
       changed += best_t != c.candidates[0];
     }
     if (n_changed) *n_changed = changed;

@@ -89,11 +89,13 @@ void make_mark(Launch &L, uint64_t *slot);
 // one FP32 value per word, or (bf16) two bfloat16 values.  Timing operands for the autotuner
 // (the matrix cores' power, and with it the clock, depends on the data).
 void make_fill(Launch &L, void *p, int64_t bytes, int bf16, uint32_t seed);
-void tile_cache_set(int M, int N, int K, int ab, int c, int tile);
-int tile_cache_get(int M, int N, int K, int ab, int c);
+// The tile cache keeps two choices per shape: for a launch of one kernel and for one of several.
+enum class TileUse { alone, shared, both };
+void tile_cache_set(int M, int N, int K, int ab, int c, int tile, TileUse use);  // tile 0: none
+int tile_cache_get(int M, int N, int K, int ab, int c, TileUse use);             // alone or shared
 void tile_cache_clear();
 size_t tile_cache_size();
-std::vector<std::array<int, 6>> tile_cache_entries();   // (M, N, K, operand dtype, output dtype, tile)
+std::vector<std::array<int, 7>> tile_cache_entries();  // (M, N, K, operand dtype, output dtype, alone, shared)
 int gemm_auto_tile(int M, int N, int K, int dtype);
 
 }  // namespace psc

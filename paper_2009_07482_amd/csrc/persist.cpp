@@ -11,6 +11,7 @@
 #include <cstring>
 #include <fstream>
 #include <iterator>
+#include <map>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -136,7 +137,8 @@ MlpState mlp_file_read(const std::string &path) {
 }
 
 // ---- tile-cache file ------------------------------------------------------------------------
-// Text: "psc-tile-cache 1", "key <key>", one "entry M N K ab c tile" line per choice, then
+// Text: "psc-tile-cache 1", "key <key>", per shape an "entry M N K ab c tile" line for a launch of
+// one kernel, a "shared M N K ab c tile" line for a launch of several, or both, then
 // "checksum <16 hex digits>" of every preceding byte.
 
 std::string tile_cache_key(int device) {
@@ -160,7 +162,10 @@ void tile_cache_save(const std::string &path, const std::string &key) {
   std::ostringstream o;
   o << "psc-tile-cache 1\nkey " << key << "\n";
   for (const auto &e : tile_cache_entries())
-    o << "entry " << e[0] << " " << e[1] << " " << e[2] << " " << e[3] << " " << e[4] << " " << e[5] << "\n";
+    for (int use : {5, 6})
+      if (e[use] > 0)
+        o << (use == 5 ? "entry " : "shared ") << e[0] << " " << e[1] << " " << e[2] << " " << e[3] << " " << e[4] << " "
+          << e[use] << "\n";
   std::string body = o.str();
   char sum[32];
   std::snprintf(sum, sizeof(sum), "%016llx", static_cast<unsigned long long>(fnv1a64(body.data(), body.size())));
@@ -185,21 +190,26 @@ int tile_cache_load(const std::string &path, const std::string &key) {
   if (!std::getline(in, line) || line.rfind("key ", 0) != 0) fail(PSC_ERR_IO, path + ": no key line");
   if (line.substr(4) != key)
     fail(PSC_ERR_STATE, path + ": made for " + line.substr(4) + ", not for " + key + " (nothing loaded)");
-  std::vector<std::array<int, 6>> got;
+  std::map<std::array<int, 5>, std::array<int, 2>> got;  // shape: alone, shared
   while (std::getline(in, line)) {
     std::istringstream ls(line);
     std::string w;
     std::array<int, 6> e{};
-    if (!(ls >> w) || w != "entry") fail(PSC_ERR_IO, path + ": unexpected line '" + line + "'");
+    if (!(ls >> w) || (w != "entry" && w != "shared")) fail(PSC_ERR_IO, path + ": unexpected line '" + line + "'");
+    const bool shared = w == "shared";
     for (int &v : e)
       if (!(ls >> v)) fail(PSC_ERR_IO, path + ": short entry '" + line + "'");
     if (ls >> w) fail(PSC_ERR_IO, path + ": long entry '" + line + "'");
     if (e[0] < 0 || e[1] < 0 || e[2] < 0 || (e[3] != PSC_F32 && e[3] != PSC_BF16) ||
         (e[4] != PSC_F32 && e[4] != PSC_BF16) || e[5] < 1 || e[5] >= gemm_num_tiles())
       fail(PSC_ERR_IO, path + ": entry out of range '" + line + "'");
-    got.push_back(e);
+    got[{e[0], e[1], e[2], e[3], e[4]}][shared] = e[5];
   }
-  for (const auto &e : got) tile_cache_set(e[0], e[1], e[2], e[3], e[4], e[5]);
+  for (const auto &kv : got) {
+    const auto &k = kv.first;
+    tile_cache_set(k[0], k[1], k[2], k[3], k[4], kv.second[0], TileUse::alone);
+    tile_cache_set(k[0], k[1], k[2], k[3], k[4], kv.second[1], TileUse::shared);
+  }
   return int(got.size());
 }
 

@@ -19,7 +19,9 @@
 #include <cstring>
 #include <map>
 #include <queue>
+#include <set>
 #include <string>
+#include <tuple>
 
 #include "aql.hpp"
 #include "core.hpp"
@@ -96,6 +98,8 @@ struct ExecCopy {
   int64_t width = 0;  // bytes per row
 };
 
+using GemmShape = std::tuple<int, int, int, int, int>;  // M, N, K, operand dtype, output dtype
+
 // One of the plans a schedule runs: its launches (per op.kernel), events and dispatchers.  A
 // PSC_FINE schedule has two when it groups launches, for runs without and with host copies.
 struct Runner {
@@ -103,6 +107,7 @@ struct Runner {
   const SchedPlan *plan = nullptr;    // &own, or the schedule's plan
   const std::vector<Launch> *launch = nullptr;
   std::vector<Launch> own_launch;
+  std::vector<std::vector<int32_t>> units;   // until upload_groups: per launch its kernels
   std::vector<std::vector<Launch>> members;  // until upload_groups: per launch its kernels' launches
   size_t table_bytes = 0;
   std::vector<int32_t> op_of;         // per op: the op of the schedule's plan (grouped plans)
@@ -145,6 +150,7 @@ struct Device {
   bool have_marks = false;
   std::unique_ptr<Runner> plain;     // the schedule's plan as it is, or with launch groups:
   std::unique_ptr<Runner> grouped[2];  // [1] for runs with host copies, [0] without
+  std::set<GemmShape> shared_shapes;   // GEMMs of automatic tile that share a launch in either
   std::unique_ptr<Dispatcher> disp;  // enqueueing threads, for every plan
   AqlSchedule *aql_run = nullptr;    // the AQL plan of the last run
   std::unique_ptr<struct DynState> dyn;  // PSC_EAGER / PSC_HEFT: the run-time scheduler's state
@@ -637,44 +643,68 @@ UnitCost unit_cost(const Dag &g, const std::vector<int32_t> &kernels, const Laun
   return c;
 }
 
-// The grouped plan of a schedule with its launches.  GEMMs whose tile is automatic are grouped by
-// summation order and take the tile that suits the group; everything else by kernel function.
-struct GroupedRunner {
-  std::unique_ptr<Runner> runner;
-  double us = 0;  // predicted
+// What a kernel runs as where it shares a launch.  A GEMM whose params leave the tile open takes the
+// cache's choice for shared launches or else the size heuristic's tile, which a group may replace by
+// another of its summation order; the cache's choice for a launch of one kernel says nothing here.
+// Such GEMMs are grouped by summation order, everything else by kernel function.
+struct Grouping {
+  std::vector<Launch> launch;   // per kernel
+  std::vector<char> open;       // the tile is not fixed by the kernel's params
+  std::vector<char> automatic;  // ... nor by the cache
+  std::vector<GemmShape> shape;  // of the open ones
+  std::vector<int32_t> key;
+  std::vector<int64_t> blocks;
 };
-GroupedRunner make_grouped(const psc_sched &s, const Device &d, bool copies, int32_t queues) {
-  const Dag &g = s.dag->g;
+Grouping grouping_of(const Dag &g, const Device &d) {
   const size_t nk = g.kers.size();
-  std::vector<int32_t> key(nk, -1);
-  std::vector<int64_t> blocks(nk, 0);
-  std::vector<char> automatic(nk, 0);
+  Grouping gr;
+  gr.launch = d.launch;
+  gr.open.assign(nk, 0);
+  gr.automatic.assign(nk, 0);
+  gr.shape.assign(nk, GemmShape{});
+  gr.key.assign(nk, -1);
+  gr.blocks.assign(nk, 0);
   std::map<std::vector<int64_t>, int32_t> ids;
   for (size_t k = 0; k < nk; ++k) {
-    const Launch &L = d.launch[k];
+    Launch &L = gr.launch[k];
     const Kernel &ker = g.kers[k];
-    blocks[k] = L.grid.x;
-    if (!groupable(L)) continue;
-    std::vector<int64_t> v{L.kind, int64_t(reinterpret_cast<intptr_t>(L.func))};
     if (ker.kind == PSC_GEMM && ker.tile <= 0) {
       GemmArgs a;
       memcpy(&a, L.args, sizeof(a));
       const int ab = g.bufs[ker.ins[0]].dtype, c = g.bufs[ker.outs[0]].dtype;
-      automatic[k] = tile_cache_get(a.M, a.N, a.K, ab, c) == 0;
-      if (automatic[k]) v = {-1, ab, c, gemm_sum_order(L.tile)};
+      const int t = tile_cache_get(a.M, a.N, a.K, ab, c, TileUse::shared);
+      gr.open[k] = 1;
+      gr.automatic[k] = t == 0;
+      gr.shape[k] = {a.M, a.N, a.K, ab, c};
+      if (!make_gemm(L, a, ab, c, t > 0 ? t : gemm_auto_tile(a.M, a.N, a.K, ab)))
+        fail(PSC_ERR_UNSUPPORTED, "no kernel instance for '" + ker.name + "'");
     }
-    key[k] = ids.emplace(v, int32_t(ids.size())).first->second;
+    gr.blocks[k] = L.grid.x;
+    if (!groupable(L)) continue;
+    std::vector<int64_t> v{L.kind, int64_t(reinterpret_cast<intptr_t>(L.func))};
+    if (gr.automatic[k]) v = {-1, std::get<3>(gr.shape[k]), std::get<4>(gr.shape[k]), gemm_sum_order(L.tile)};
+    gr.key[k] = ids.emplace(v, int32_t(ids.size())).first->second;
   }
-  GroupedPlan gp = group_plan(g, s.plan, key, blocks, kGroupMaxBlocks, copies, s.opts.copy_roots != 0,
+  return gr;
+}
+
+// The grouped plan of a schedule with its launches.
+struct GroupedRunner {
+  std::unique_ptr<Runner> runner;
+  double us = 0;  // predicted
+};
+GroupedRunner make_grouped(const psc_sched &s, const Device &d, const Grouping &gr, bool copies, int32_t queues) {
+  const Dag &g = s.dag->g;
+  GroupedPlan gp = group_plan(g, s.plan, gr.key, gr.blocks, kGroupMaxBlocks, copies, s.opts.copy_roots != 0,
                               queues);
   auto r = std::make_unique<Runner>();
   std::vector<std::vector<Launch>> members(gp.units.size());
   size_t bytes = 0;
   for (size_t u = 0; u < gp.units.size(); ++u) {
     const std::vector<int32_t> &ks = gp.units[u];
-    for (int32_t k : ks) members[u].push_back(d.launch[k]);
+    for (int32_t k : ks) members[u].push_back(ks.size() < 2 ? d.launch[k] : gr.launch[k]);
     if (ks.size() < 2) continue;
-    if (automatic[ks[0]]) {
+    if (gr.automatic[ks[0]]) {
       std::vector<GemmArgs> as(ks.size());
       for (size_t i = 0; i < ks.size(); ++i) memcpy(&as[i], members[u][i].args, sizeof(GemmArgs));
       const int t = gemm_group_tile(as, members[u][0].tile);
@@ -694,6 +724,7 @@ GroupedRunner make_grouped(const psc_sched &s, const Device &d, bool copies, int
     cost[u] = unit_cost(g, gp.units[u], all);
   }
   if (!copies) out.us = predict_plan_us(gp, cost, kGapUs, s.opts.dispatch == PSC_DISPATCH_AQL ? kWaitAql : kWaitHip);
+  r->units = std::move(gp.units);
   r->members = std::move(members);
   r->table_bytes = bytes;
   r->own = std::move(gp.plan);
@@ -721,7 +752,25 @@ void upload_groups(Runner &r) {
     off += group_table_bytes(m);
   }
   if (r.table_bytes) PSC_HIP(hipMemcpy(r.table, host.data(), r.table_bytes, hipMemcpyHostToDevice));
+  r.units.clear();
   r.members.clear();
+}
+
+// Kernels of one shape sum in one order in every run of a schedule, with and without copies: where
+// some of them share a launch, one that stands alone keeps its own tile only if the order is theirs.
+void settle_shared_shapes(Device &d, const Grouping &gr) {
+  for (const auto &r : d.grouped)
+    for (const std::vector<int32_t> &ks : r->units)
+      if (ks.size() > 1)
+        for (int32_t k : ks)
+          if (gr.open[k]) d.shared_shapes.insert(gr.shape[k]);
+  for (const auto &r : d.grouped)
+    for (size_t u = 0; u < r->units.size(); ++u) {
+      const int32_t k = r->units[u][0];
+      if (r->units[u].size() == 1 && gr.open[k] && d.shared_shapes.count(gr.shape[k]) &&
+          gemm_sum_order(d.launch[k].tile) != gemm_sum_order(gr.launch[k].tile))
+        r->members[u][0] = gr.launch[k];
+    }
 }
 
 // How many queues carry the plan's streams: the count with the shortest predicted run.  A wait
@@ -731,17 +780,18 @@ void upload_groups(Runner &r) {
 // 512 FP32 attention on AQL queues [77] / 83 / 92 / 97; 4-layer 1024 BF16 attention on AQL queues
 // 461 / [430] / 470 / 476; random DAG of 60 kernels on HIP streams [220] / 251 / 235 / 290; batch of
 // sixteen uneven BF16 DAGs on HIP streams 1656 / 1299 / [1213] / 1233.
-std::unique_ptr<Runner> best_grouped(const psc_sched &s, const Device &d, bool copies, int32_t *queues) {
-  if (copies) return make_grouped(s, d, true, *queues).runner;
+std::unique_ptr<Runner> best_grouped(const psc_sched &s, const Device &d, const Grouping &gr, bool copies,
+                                     int32_t *queues) {
+  if (copies) return make_grouped(s, d, gr, true, *queues).runner;
   GroupedRunner best;
   for (int32_t q = 1; q <= std::min(s.plan.n_streams, 4); ++q) {
-    GroupedRunner r = make_grouped(s, d, false, q);
+    GroupedRunner r = make_grouped(s, d, gr, false, q);
     if (best.runner && r.us >= best.us) continue;
     best = std::move(r);
     *queues = q;
   }
   if (s.plan.n_streams > 4) {
-    GroupedRunner r = make_grouped(s, d, false, s.plan.n_streams);
+    GroupedRunner r = make_grouped(s, d, gr, false, s.plan.n_streams);
     if (r.us < best.us) {
       best = std::move(r);
       *queues = s.plan.n_streams;
@@ -831,9 +881,11 @@ void prepare(psc_sched &s) {
     // with copies then keep every stream, up to the four queues that the GPU serves at once (4-layer
     // 1024 BF16 attention with host copies on 2 / 4 / 8 / 16 AQL queues: 0.69 / 0.67 / 1.11 / 1.86 ms)
     int32_t queues = s.plan.n_streams;
-    d->grouped[0] = best_grouped(s, *d, false, &queues);
+    const Grouping gr = grouping_of(g, *d);
+    d->grouped[0] = best_grouped(s, *d, gr, false, &queues);
     if (s.plan.total_streams == s.plan.n_streams) queues = std::min(s.plan.n_streams, 4);
-    d->grouped[1] = best_grouped(s, *d, true, &queues);
+    d->grouped[1] = best_grouped(s, *d, gr, true, &queues);
+    settle_shared_shapes(*d, gr);
     for (auto &r : d->grouped) upload_groups(*r);
     std::shared_ptr<AqlQueues> aql_queues;
     if (aql_mode)
@@ -1708,9 +1760,18 @@ int autotune_gemm(int device, int M, int N, int K, int ab, int c, int iters, flo
   }
   cleanup();
   if (us_per_tile && cap > 0) us_per_tile[0] = 0.f;
-  if (best) tile_cache_set(M, N, K, ab, c, best);
+  if (best) {
+    tile_cache_set(M, N, K, ab, c, best, TileUse::alone);
+    tile_cache_set(M, N, K, ab, c, 0, TileUse::shared);
+  }
   if (best_us) *best_us = best_t;
   return best;
+}
+
+// Whether kernels of this shape share a launch in any plan of a prepared schedule.
+bool sched_shares_launches(const psc_sched &s, int M, int N, int K, int ab, int c) {
+  if (!s.dev) fail(PSC_ERR_STATE, "schedule not prepared");
+  return s.dev->shared_shapes.count({M, N, K, ab, c}) != 0;
 }
 
 int sched_kernel_tile(const psc_sched &s, int32_t kernel) {
