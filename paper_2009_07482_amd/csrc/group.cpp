@@ -97,7 +97,8 @@ double predict_plan_us(const GroupedPlan &gp, const std::vector<UnitCost> &cost,
   const int32_t T = gp.plan.total_streams;
   std::vector<std::vector<int32_t>> queue(T);
   for (size_t o = 0; o < ops.size(); ++o) queue[ops[o].stream].push_back(int32_t(o));
-  std::vector<double> end(ops.size(), -1), left(T, 0), from(T, 0);  // `from`: the queue's next start by its own order
+  std::vector<double> end(ops.size(), -1), left(T, 0), until(T, 0);
+  std::vector<double> from(T, 0);  // the queue's next start by its own order
   std::vector<size_t> at(T, 0);
   std::vector<char> running(T, 0);
   for (int32_t q = 1; q < T; ++q) from[q] = wait_us;
@@ -126,13 +127,15 @@ double predict_plan_us(const GroupedPlan &gp, const std::vector<UnitCost> &cost,
     }
     if (!any) return finish;
     const double slow = std::max(1.0, asked);
+    // what ends by `next` is decided on the sums themselves: what is left after subtracting can
+    // round to a little more than nothing, less than `now` resolves, and time would stand still
     for (int32_t q = 0; q < T; ++q)
-      if (running[q]) next = std::min(next, now + left[q] * slow);
+      if (running[q]) next = std::min(next, until[q] = now + left[q] * slow);
     if (next > 1e299) return 1e300;  // (not reached: the plan's waits name earlier ops)
     for (int32_t q = 0; q < T; ++q) {
       if (!running[q]) continue;
       left[q] -= (next - now) / slow;
-      if (left[q] > 1e-9) continue;
+      if (until[q] > next && left[q] > 1e-9) continue;
       running[q] = 0;
       end[queue[q][at[q]++]] = next;
       from[q] = next + gap_us;
