@@ -474,19 +474,15 @@ AqlQueues::AqlQueues(int device, const std::vector<const SchedPlan *> &plans, bo
     if (queues_.size() < size_t(T)) queues_.resize(T, nullptr);
   }
   const int32_t T = int32_t(queues_.size());
-  // a queue for every stream holding a kernel (and stream 0, which holds the marks and the join);
-  // packets per queue per run, an upper bound: start, per op its barriers, dispatch and mark, join
+  // a queue for every stream holding a kernel (and stream 0, which holds the marks and the join)
   std::vector<char> has_kernel(T, 0);
   has_kernel[0] = 1;
   std::vector<uint64_t> size_for(T, 0);
   for (const SchedPlan *plan : plans) {
-    std::vector<uint64_t> need(T, 6);
-    need[0] += uint64_t(T) / 5 + 8;
-    for (const Op &op : plan->ops) {
+    for (const Op &op : plan->ops)
       if (op.type == PSC_OP_KERNEL) has_kernel[op.stream] = 1;
-      need[op.stream] += 3 + (op.waits.size() + 1 + 4) / 5;
-    }
-    for (int32_t s = 0; s < T; ++s) size_for[s] = std::max(size_for[s], need[s]);
+    const std::vector<uint64_t> need = queue_packets(*plan);
+    for (size_t s = 0; s < need.size(); ++s) size_for[s] = std::max(size_for[s], need[s]);
   }
   try {
     for (int32_t s = 0; s < T; ++s) {
@@ -505,6 +501,8 @@ AqlQueues::AqlQueues(int device, const std::vector<const SchedPlan *> &plans, bo
     throw;
   }
 }
+
+uint64_t aql_queue_capacity(int device) { return agent_for(device).queue_max; }
 
 AqlQueues::~AqlQueues() {
   if (abandoned_) return;

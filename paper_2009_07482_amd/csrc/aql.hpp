@@ -32,6 +32,9 @@ struct AqlCopy {
   size_t dpitch = 0, spitch = 0, width = 0, height = 0;
 };
 
+// Packets the largest queue of the device holds.
+uint64_t aql_queue_capacity(int device);
+
 // The queues of one schedule's streams, shared by the plans it may run (one run at a time).
 class AqlQueues {
  public:

@@ -139,6 +139,10 @@ SchedPlan build_plan(const Dag &g, int policy, const psc_sched_opts &o);
 // another wait implies it.
 void assign_waits(SchedPlan &plan, const std::vector<std::vector<int32_t>> &deps);
 
+// Packets each stream of a plan puts into its queue in one run under AQL dispatch, an upper bound:
+// start, per op its barriers, dispatch and mark, join.
+std::vector<uint64_t> queue_packets(const SchedPlan &plan);
+
 struct Device;  // HIP state, runtime.cpp
 
 }  // namespace psc

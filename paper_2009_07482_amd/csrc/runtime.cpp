@@ -780,22 +780,28 @@ void settle_shared_shapes(Device &d, const Grouping &gr) {
 // 512 FP32 attention on AQL queues [77] / 83 / 92 / 97; 4-layer 1024 BF16 attention on AQL queues
 // 461 / [430] / 470 / 476; random DAG of 60 kernels on HIP streams [220] / 251 / 235 / 290; batch of
 // sixteen uneven BF16 DAGs on HIP streams 1656 / 1299 / [1213] / 1233.
+// A count whose queues cannot hold a whole run (AQL packets) is passed over while a larger one is left.
 std::unique_ptr<Runner> best_grouped(const psc_sched &s, const Device &d, const Grouping &gr, bool copies,
                                      int32_t *queues) {
-  if (copies) return make_grouped(s, d, gr, true, *queues).runner;
+  const int32_t S = s.plan.n_streams;
+  const uint64_t capacity = s.opts.dispatch == PSC_DISPATCH_AQL ? aql_queue_capacity(d.device) : UINT64_MAX;
+  auto holds = [&](const Runner &r) {
+    const std::vector<uint64_t> n = queue_packets(*r.plan);
+    return *std::max_element(n.begin(), n.end()) <= capacity;
+  };
+  if (copies) {
+    for (;; ++*queues) {
+      GroupedRunner r = make_grouped(s, d, gr, true, *queues);
+      if (*queues == S || holds(*r.runner)) return std::move(r.runner);
+    }
+  }
   GroupedRunner best;
-  for (int32_t q = 1; q <= std::min(s.plan.n_streams, 4); ++q) {
+  for (int32_t q = 1; q <= S; q = q < 4 || q == S ? q + 1 : S) {
     GroupedRunner r = make_grouped(s, d, gr, false, q);
+    if ((q < S || best.runner) && !holds(*r.runner)) continue;
     if (best.runner && r.us >= best.us) continue;
     best = std::move(r);
     *queues = q;
-  }
-  if (s.plan.n_streams > 4) {
-    GroupedRunner r = make_grouped(s, d, gr, false, s.plan.n_streams);
-    if (r.us < best.us) {
-      best = std::move(r);
-      *queues = s.plan.n_streams;
-    }
   }
   return std::move(best.runner);
 }

@@ -259,6 +259,13 @@ SchedPlan build_dynamic_plan(const Dag &g, int policy, const psc_sched_opts &o) 
   return plan;
 }
 
+std::vector<uint64_t> queue_packets(const SchedPlan &plan) {
+  std::vector<uint64_t> need(plan.total_streams, 6);
+  need[0] += uint64_t(plan.total_streams) / 5 + 8;
+  for (const Op &op : plan.ops) need[op.stream] += 3 + (op.waits.size() + 1 + 4) / 5;
+  return need;
+}
+
 void assign_waits(SchedPlan &plan, const std::vector<std::vector<int32_t>> &deps) {
   const int32_t T = plan.total_streams;
   const size_t n = plan.ops.size();
