@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void transpose_rc_kernel(TransArgs p) {
 template <bool IN_BF16, bool OUT_BF16, bool NT = false>
 __global__ __launch_bounds__(256) void add_vec_kernel(AddArgs p) {
   const int bid = member_block(p, blockIdx.x);
-  add_block_vec<IN_BF16, OUT_BF16, NT>(p, bid);
+  add_block<IN_BF16, OUT_BF16, NT>(p, bid);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -523,7 +523,7 @@ bool make_add(Launch &L, AddArgs a, int in_dtype, int out_dtype) {
   // plain loads and stores: streaming hints measured slower for the two-input add
   L.func = ib ? (ob ? (const void *)&add_vec_kernel<true, true> : (const void *)&add_vec_kernel<true, false>)
               : (ob ? (const void *)&add_vec_kernel<false, true> : (const void *)&add_vec_kernel<false, false>);
-  L.grid = dim3(unsigned(int64_t((a.C + 2047) / 2048) * a.R), 1, 1);
+  L.grid = dim3(unsigned((int64_t(add_units(a.C)) * a.R + 255) / 256), 1, 1);
   L.block = dim3(256, 1, 1);
   L.shmem = 0;
   L.empty = a.R == 0 || a.C == 0;

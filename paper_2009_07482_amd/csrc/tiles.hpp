@@ -95,6 +95,29 @@ __device__ __forceinline__ V shift_down(V v, int bits) {
   return v;
 }
 
+// The 16 bytes at column c of a row of n >= 1 elements, in two steps: load_edge reads without a branch
+// that differs between lanes, a vector that would cross the row's end from the last place where it
+// fits (rows shorter than a vector: element by element, past the end the last one again); in_place
+// then shifts such a vector.  Every access lies in the row; what the result holds past the row's end
+// is unspecified.  A load behind a check of its own is waited for inside its branch, so the checked
+// edges of a kernel would pay a memory latency per element.
+template <typename T, bool NT = false>
+__device__ __forceinline__ u32x4 load_edge(const T *row, int c, int n) {
+  constexpr int V = 16 / int(sizeof(T));
+  if (n >= V) return load16<NT>(row + min(c, n - V));
+  T e[V];
+#pragma unroll
+  for (int j = 0; j < V; ++j) e[j] = load1(row + min(c + j, n - 1));
+  u32x4 v;
+  memcpy(&v, e, 16);
+  return v;
+}
+template <typename T>
+__device__ __forceinline__ u32x4 in_place(u32x4 v, int c, int n) {
+  constexpr int V = 16 / int(sizeof(T)), BITS = 8 * int(sizeof(T));
+  return n >= V && c > n - V ? shift_down(v, BITS * min(c - (n - V), V - 1)) : v;
+}
+
 // ---------------------------------------------------------------------------------------------
 // bfloat16 <-> float.  A bfloat16 is the upper 16 bits of an IEEE binary32; conversion from
 // float rounds to nearest, ties to even, on those 16 bits; NaN stays a (quiet) NaN.
@@ -1616,58 +1639,89 @@ __device__ __forceinline__ void transpose_rc_tile(const TransArgs &p, int bid, u
 }
 
 // ---------------------------------------------------------------------------------------------
-// Element-wise add in FP32, rounded once to the output type: each thread adds 8 consecutive
-// elements per row of a 2048-column chunk; a workgroup covers one chunk of one row.
+// Element-wise add in FP32, rounded once to the output type: each thread adds a unit of 8 consecutive
+// elements of a row (the last unit of a row may be shorter).
 // ---------------------------------------------------------------------------------------------
 template <bool IN_BF16, bool OUT_BF16, bool NT = false>
-__device__ __forceinline__ void add_block_vec(const AddArgs &p, int bid) {
-  const int nbx = (p.C + 2047) / 2048;
-  const int c = (bid % nbx) * 2048 + threadIdx.x * 8;
-  const int r = bid / nbx;
+__device__ __forceinline__ void add_unit(const AddArgs &p, int r, int c) {
   if (c >= p.C || r >= p.R) return;
-  const int64_t ia = int64_t(r) * p.lda + c, ib = int64_t(r) * p.ldb + c, ic = int64_t(r) * p.ldc + c;
+  const int64_t ra = int64_t(r) * p.lda, rb = int64_t(r) * p.ldb, rc = int64_t(r) * p.ldc;
+  // (all loads first; where no row has a short unit there is nothing to put in place)
+  constexpr int NV = IN_BF16 ? 1 : 2, V = 8 / NV;  // vectors of a unit and operand, their elements
+  using T = typename std::conditional<IN_BF16, uint16_t, float>::type;
+  u32x4 x[NV], y[NV];
+  const T *A = static_cast<const T *>(p.A) + ra, *B = static_cast<const T *>(p.B) + rb;
+  if (p.C % 8 == 0) {
+#pragma unroll
+    for (int h = 0; h < NV; ++h) x[h] = load16<NT>(A + c + V * h);
+#pragma unroll
+    for (int h = 0; h < NV; ++h) y[h] = load16<NT>(B + c + V * h);
+  } else {
+#pragma unroll
+    for (int h = 0; h < NV; ++h) x[h] = load_edge<T, NT>(A, c + V * h, p.C);
+#pragma unroll
+    for (int h = 0; h < NV; ++h) y[h] = load_edge<T, NT>(B, c + V * h, p.C);
+    if (c + 8 > p.C)
+#pragma unroll
+      for (int h = 0; h < NV; ++h) x[h] = in_place<T>(x[h], c + V * h, p.C), y[h] = in_place<T>(y[h], c + V * h, p.C);
+  }
   float a[8], b[8];
-  if (c + 8 <= p.C) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
     if constexpr (IN_BF16) {
-      const u32x4 x = load16<NT>(static_cast<const uint16_t *>(p.A) + ia);
-      const u32x4 y = load16<NT>(static_cast<const uint16_t *>(p.B) + ib);
-      const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        a[2 * q] = __uint_as_float(xs[q] << 16);
-        a[2 * q + 1] = __uint_as_float(xs[q] & 0xffff0000u);
-        b[2 * q] = __uint_as_float(ys[q] << 16);
-        b[2 * q + 1] = __uint_as_float(ys[q] & 0xffff0000u);
-      }
+      a[e] = __uint_as_float((e & 1) ? x[0][e / 2] & 0xffff0000u : x[0][e / 2] << 16);
+      b[e] = __uint_as_float((e & 1) ? y[0][e / 2] & 0xffff0000u : y[0][e / 2] << 16);
     } else {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const u32x4 x = load16<NT>(static_cast<const float *>(p.A) + ia + 4 * h);
-        const u32x4 y = load16<NT>(static_cast<const float *>(p.B) + ib + 4 * h);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          a[4 * h + e] = __uint_as_float(x[e]);
-          b[4 * h + e] = __uint_as_float(y[e]);
-        }
-      }
+      a[e] = __uint_as_float(x[e / 4][e % 4]);
+      b[e] = __uint_as_float(y[e / 4][e % 4]);
     }
+  }
+  if (c + 8 <= p.C) {
     if constexpr (OUT_BF16) {
       uint32_t w[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         w[q] = uint32_t(f32_to_bf16(a[2 * q] + b[2 * q])) | (uint32_t(f32_to_bf16(a[2 * q + 1] + b[2 * q + 1])) << 16);
-      store16<NT>(static_cast<uint16_t *>(p.Cp) + ic, u32x4{w[0], w[1], w[2], w[3]});
+      store16<NT>(static_cast<uint16_t *>(p.Cp) + rc + c, u32x4{w[0], w[1], w[2], w[3]});
     } else {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        store16<NT>(static_cast<float *>(p.Cp) + ic + 4 * h,
+        store16<NT>(static_cast<float *>(p.Cp) + rc + c + 4 * h,
                     u32x4{__float_as_uint(a[4 * h] + b[4 * h]), __float_as_uint(a[4 * h + 1] + b[4 * h + 1]),
                           __float_as_uint(a[4 * h + 2] + b[4 * h + 2]), __float_as_uint(a[4 * h + 3] + b[4 * h + 3])});
     }
   } else {
-    for (int e = 0; c + e < p.C; ++e)
-      store_elem<OUT_BF16>(p.Cp, ic + e, load_elem<IN_BF16>(p.A, ia + e) + load_elem<IN_BF16>(p.B, ib + e));
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (c + e < p.C) store_elem<OUT_BF16>(p.Cp, rc + c + e, a[e] + b[e]);
   }
+}
+
+// Block `bid` of a standalone add: units 256 bid .. 256 bid + 255 in row order, so a block is full
+// whatever the row length.  (A block per 2048 columns of a row: 6472 x 2171 FP32 32.9 us, half of the
+// blocks with 123 columns each, and 7240 x 12 BF16 4.8 us, two threads of each block at work.)
+inline __host__ __device__ int add_units(int C) { return (C + 7) / 8; }
+template <bool IN_BF16, bool OUT_BF16, bool NT = false>
+__device__ __forceinline__ void add_block(const AddArgs &p, int bid) {
+  const uint32_t units = add_units(p.C), tid = threadIdx.x;
+  // the row and unit of the block's first thread (the same for all of it)
+  uint32_t r, u;
+  if (bid < (1 << 24)) {
+    r = uint32_t(bid) * 256u / units;
+    u = uint32_t(bid) * 256u - r * units + tid;
+  } else {
+    const uint64_t first = uint64_t(bid) * 256u;
+    r = uint32_t(first / units);
+    u = uint32_t(first - uint64_t(r) * units) + tid;
+  }
+  if (units >= 256) {
+    if (u >= units) u -= units, ++r;
+  } else {
+    const uint32_t dr = u / units;
+    u -= dr * units;
+    r += dr;
+  }
+  add_unit<IN_BF16, OUT_BF16, NT>(p, int(r), int(u) * 8);
 }
 
 }  // namespace psc
