@@ -151,8 +151,8 @@ typedef struct psc_kernel_params {
   int32_t alpha_set;    /* nonzero: use alpha as given (so alpha = 0 is expressible) */
   int32_t tile;         /* GEMM tile configuration index, -1 or 0 = automatic; for a transpose
                            the tile of the input a block moves: 1 = 64 x 64, 2 = 64 x 128,
-                           3 = 128 x 64, 4 = 64 x 256 (rows x columns), 0 = automatic (4 for
-                           transposes of 256 MiB and more, else 1) */
+                           3 = 128 x 64, 4 = 64 x 256 (rows x columns), 0 = automatic (1
+                           below 256 MiB, from there by the matrix's shape and alignment) */
   int32_t reserved;
 } psc_kernel_params;
 

@@ -490,14 +490,21 @@ bool make_softmax(Launch &L, SoftmaxArgs a, int in_dtype, int out_dtype) {
 
 #define PSC_TRC(T, TR, TC) (nt ? (const void *)&transpose_rc_kernel<T, TR, TC, true> : (const void *)&transpose_rc_kernel<T, TR, TC, false>)
 
-// tile: 1 64 x 64, 2 64 x 128, 3 128 x 64, 4 64 x 256 (rows x columns of the input).  Automatic (0): 64 x 256 for streaming
-// sizes, 64 x 64 otherwise.  Measured on a 16384^2 transpose with streaming hints (HBM fraction,
-// FP32 / BF16): 64 x 256 70.2-70.5% / 71.2-72.1%; 128 x 256 (BF16) 71.2%; 64 x 128 66.9% / 67.9%;
-// 64 x 64 65.4% / 67.1%; 128 x 128 66.3% / 68.2%; 32 x 256 68.7-68.9% / 52.5%; 64 x 512 (BF16)
-// 68.3%; without the hints every shape 1.5-4 points lower.
+// tile: 1 64 x 64, 2 64 x 128, 3 128 x 64, 4 64 x 256 (rows x columns of the input).  Automatic (0),
+// 64 x 64 below kStreamBytes; from there, measured (us):
+//   - streaming hints only where every row of B starts on a cache line; elsewhere the lines shared
+//     by two tiles go to memory in pieces: 9001 x 9003 FP32 in 128 x 64 tiles 215 with, 190 without;
+//     13001 x 12003 BF16 288 / 211; 8192 x 8193 FP32 98 / 103; 16384^2 FP32 382 / 396
+//   - with them 64 x 256 (16384^2 FP32 382, 64 x 128 399, 128 x 64 404, 64 x 64 409), but not for
+//     matrices narrower than that, whose tiles would lie mostly outside (900000 x 100 FP32: 64 x 256
+//     169, 64 x 128 143, 64 x 64 175; 4500000 x 15: 515, 216, 102)
+//   - without them 128 x 64 (9001 x 9003 FP32 190, the others 207 to 219; 100 x 900000 139 / 235 to
+//     242), but not for matrices of few rows (15 x 4500000: 294, 64 x 64 101)
 bool make_transpose(Launch &L, TransArgs a, int dtype, int tile) {
-  const bool nt = int64_t(a.R) * a.C * (dtype == 1 ? 2 : 4) >= kStreamBytes;
-  if (tile < 1 || tile > 4) tile = nt ? 4 : 1;
+  const int es = dtype == 1 ? 2 : 4;
+  const bool large = int64_t(a.R) * a.C * es >= kStreamBytes;
+  const bool nt = large && reinterpret_cast<uintptr_t>(a.B) % 128 == 0 && a.ldb * es % 128 == 0;
+  if (tile < 1 || tile > 4) tile = !large ? 1 : nt ? (a.C >= 256 ? 4 : a.C > 64 ? 2 : 1) : a.R > 64 ? 3 : 1;
   int tr = 64, tcl = 64;
   if (tile == 1)
     L.func = dtype == 1 ? (nt ? (const void *)&transpose_vec_kernel<uint16_t, true> : (const void *)&transpose_vec_kernel<uint16_t, false>)
