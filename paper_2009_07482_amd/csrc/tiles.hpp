@@ -118,6 +118,29 @@ __device__ __forceinline__ u32x4 in_place(u32x4 v, int c, int n) {
   return n >= V && c > n - V ? shift_down(v, BITS * min(c - (n - V), V - 1)) : v;
 }
 
+// The same for the vectors the GEMM tiles hold; keep_first: zeros from element n on.
+template <typename V, typename T>
+__device__ __forceinline__ V load_edge_as(const T *row, int c, int n) {
+  const u32x4 w = load_edge(row, c, n);
+  V v;
+  memcpy(&v, &w, 16);
+  return v;
+}
+// A copy of a thread's index whose origin the compiler does not see: what the edge path computes from
+// it stays there.  Computed ahead of the loop instead, it held twenty registers in every tile (64 x 64
+// BF16: 104 against 84, four wavefronts per SIMD against five).
+__device__ __forceinline__ int here(int t) {
+  asm volatile("" : "+v"(t));
+  return t;
+}
+__device__ __forceinline__ float4 keep_first(float4 v, int n) {
+  return make_float4(n > 0 ? v.x : 0.f, n > 1 ? v.y : 0.f, n > 2 ? v.z : 0.f, n > 3 ? v.w : 0.f);
+}
+__device__ __forceinline__ uint4 keep_first(uint4 v, int n) {  // bf16 pairs
+  auto part = [](uint32_t w, int m) { return m > 1 ? w : m > 0 ? w & 0xffffu : 0u; };
+  return uint4{part(v.x, n), part(v.y, n - 2), part(v.z, n - 4), part(v.w, n - 6)};
+}
+
 // ---------------------------------------------------------------------------------------------
 // bfloat16 <-> float.  A bfloat16 is the upper 16 bits of an IEEE binary32; conversion from
 // float rounds to nearest, ties to even, on those 16 bits; NaN stays a (quiet) NaN.
@@ -181,12 +204,13 @@ __device__ __forceinline__ int group_tile(int t, int tiles_m, int tiles_n, int G
 // 4-layer 1024 BF16 attention on the device executor 675 -> 651 us, a 60-kernel random BF16 DAG 221
 // -> 213 us, 512 FP32 attention on queues 80 -> 78 us.
 //
-// Unguarded loads.  A K step that lies inside the matrix is loaded without a check per vector:
-// one wavefront-uniform test picks that path, so the loads of a step are issued back to back
-// instead of each behind its own branch.  Rows of A past the last one read the last row instead
-// (their products land in rows that are not stored).  A vector of B that crosses the last column
-// starts at the last place where it fits, and its elements are shifted into place on the way to
-// LDS (`raw`; only in the blocks of the last tile column, the only ones to pay for it).  With a
+// Unguarded loads.  Operands are loaded without a check per vector, so the loads of a step are issued
+// back to back instead of each behind its own branch.  Rows of A past the last one read the last row
+// instead (their products land in rows that are not stored).  A vector of B that crosses the last
+// column starts at the last place where it fits, and its elements are shifted into place on the way to
+// LDS (only in the blocks of the last tile column, the only ones to pay for it).  The last, partial K
+// step treats A's columns and B's rows the same way and then sets what lies past K to zero; its path
+// also serves matrices narrower than a vector, whose elements are loaded one by one.  With a
 // check per vector those blocks set the time of a ragged product: 1777 x 2050 x 1001 FP32, whose
 // last tile column is two wide, took 143 us reading element by element, 128 us with unguarded
 // vectors everywhere else, and takes 92 us.
@@ -259,49 +283,40 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, int bid, unsign
 
   float4 ra[NA], rb[NB];
   const bool n_whole = n0 + BN <= p.N;
-  const int bc = n0 + (tid % (BN / 4)) * 4, bs = max(0, min(bc, p.N - 4)), b_bits = min(32 * (bc - bs), 96);
-  bool raw = false;
-  const float *pa[NA], *const pb = B + int64_t(tid / (BN / 4)) * p.ldb + bs;
+  const int ac = (tid % (BK / 4)) * 4, br = tid / (BN / 4);
+  const int bc = n0 + (tid % (BN / 4)) * 4, bs = max(0, min(bc, p.N - 4));
+  const int b_bits = p.N >= 4 ? min(32 * (bc - bs), 96) : 0;
+  const float *pa[NA], *const pb = B + int64_t(br) * p.ldb + bs;
 #pragma unroll
-  for (int j = 0; j < NA; ++j)
-    pa[j] = A + int64_t(min(m0 + (tid + NT * j) / (BK / 4), p.M - 1)) * p.lda + (tid % (BK / 4)) * 4;
-  static_assert(NT % (BK / 4) == 0 && NT % (BN / 4) == 0, "a thread keeps its column in every unit");
+  for (int j = 0; j < NA; ++j) pa[j] = A + int64_t(min(m0 + (tid + NT * j) / (BK / 4), p.M - 1)) * p.lda + ac;
+  static_assert(UA % NT == 0 && UB % NT == 0 && NT % (BK / 4) == 0 && NT % (BN / 4) == 0,
+                "whole units per thread, each thread in one column of units");
   auto load = [&](int k0) {  // next tile into registers (zero outside the matrices)
-    raw = UA % NT == 0 && UB % NT == 0 && p.N >= 4 && k0 + BK <= p.K;  // see "Unguarded loads" above
-    if (raw) {
+    const int left = p.K - k0;  // see "Unguarded loads" above
+    if (left >= BK && p.N >= 4) {
 #pragma unroll
       for (int j = 0; j < NA; ++j) ra[j] = load_as<float4>(pa[j] + k0);
 #pragma unroll
       for (int j = 0; j < NB; ++j) rb[j] = load_as<float4>(pb + int64_t(k0 + j * (NT / (BN / 4))) * p.ldb);
       return;
     }
+    const int t = here(tid), eac = (t % (BK / 4)) * 4, ebr = t / (BN / 4), ebc = n0 + (t % (BN / 4)) * 4;
+    if (left > 0) {
 #pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      const int u = tid + NT * j, r = u / (BK / 4), c = (u % (BK / 4)) * 4;
-      const int gr = m0 + r, gc = k0 + c;
-      if (u < UA && gr < p.M && gc + 3 < p.K) {
-        ra[j] = load_as<float4>(A + int64_t(gr) * p.lda + gc);
-      } else {
-        float v[4];
+      for (int j = 0; j < NA; ++j) ra[j] = load_edge_as<float4>(pa[j] - eac, k0 + eac, p.K);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          v[e] = (u < UA && gr < p.M && gc + e < p.K) ? load1(A + int64_t(gr) * p.lda + gc + e) : 0.f;
-        ra[j] = make_float4(v[0], v[1], v[2], v[3]);
-      }
+      for (int j = 0; j < NB; ++j)
+        rb[j] = load_edge_as<float4>(B + int64_t(min(k0 + ebr + j * (NT / (BN / 4)), p.K - 1)) * p.ldb, ebc, p.N);
     }
+    if (left < BK) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int u = tid + NT * j, r = u / (BN / 4), c = (u % (BN / 4)) * 4;
-      const int gr = k0 + r, gc = n0 + c;
-      if (u < UB && gr < p.K && gc + 3 < p.N) {
-        rb[j] = load_as<float4>(B + int64_t(gr) * p.ldb + gc);
-      } else {
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          v[e] = (u < UB && gr < p.K && gc + e < p.N) ? load1(B + int64_t(gr) * p.ldb + gc + e) : 0.f;
-        rb[j] = make_float4(v[0], v[1], v[2], v[3]);
+      for (int j = 0; j < NA; ++j) {
+        if (p.K >= 4) ra[j] = shift_down(ra[j], 32 * min(max(eac + 4 - left, 0), 3));
+        ra[j] = keep_first(ra[j], left - eac);
       }
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        if (ebr + j * (NT / (BN / 4)) >= left) rb[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   };
 
@@ -315,19 +330,16 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, int bid, unsign
   for (int k0 = 0; k0 < p.K; k0 += BK) {
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
-      const int u = tid + NT * j, r = u / (BK / 4), c = (u % (BK / 4)) * 4;
-      if (u < UA) {
-        As[(c + 0) * SA + (r ^ swz(c + 0))] = ra[j].x;
-        As[(c + 1) * SA + (r ^ swz(c + 1))] = ra[j].y;
-        As[(c + 2) * SA + (r ^ swz(c + 2))] = ra[j].z;
-        As[(c + 3) * SA + (r ^ swz(c + 3))] = ra[j].w;
-      }
+      const int r = (tid + NT * j) / (BK / 4);
+      As[(ac + 0) * SA + (r ^ swz(ac + 0))] = ra[j].x;
+      As[(ac + 1) * SA + (r ^ swz(ac + 1))] = ra[j].y;
+      As[(ac + 2) * SA + (r ^ swz(ac + 2))] = ra[j].z;
+      As[(ac + 3) * SA + (r ^ swz(ac + 3))] = ra[j].w;
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int u = tid + NT * j, r = u / (BN / 4), c = (u % (BN / 4)) * 4;
-      if (raw && !n_whole) rb[j] = shift_down(rb[j], b_bits);
-      if (u < UB) *reinterpret_cast<float4 *>(&Bs[r * SB + c]) = rb[j];
+      if (!n_whole) rb[j] = shift_down(rb[j], b_bits);
+      *reinterpret_cast<float4 *>(&Bs[(br + j * (NT / (BN / 4))) * SB + bc - n0]) = rb[j];
     }
     __syncthreads();
     if (k0 + BK < p.K) load(k0 + BK);  // in flight while this tile is multiplied
@@ -434,31 +446,37 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &p, int bid, unsig
   uint4 ra[NA], rb[NB];
   const bool n_whole = n0 + BN <= p.N;
   const int ac = (tid % (BK / 8)) * 8, ar = tid / (BK / 8), br = tid / (BN / 8);
-  const int bc = n0 + (tid % (BN / 8)) * 8, bs = max(0, min(bc, p.N - 8)), b_bits = min(16 * (bc - bs), 112);
-  bool raw = false;
+  const int bc = n0 + (tid % (BN / 8)) * 8, bs = max(0, min(bc, p.N - 8));
+  const int b_bits = p.N >= 8 ? min(16 * (bc - bs), 112) : 0;
   const uint16_t *pa[NA], *const pb = B + int64_t(br) * p.ldb + bs;
 #pragma unroll
   for (int j = 0; j < NA; ++j) pa[j] = A + int64_t(min(m0 + ar + j * (NT / (BK / 8)), p.M - 1)) * p.lda + ac;
   auto load = [&](int k0) {
-    raw = p.N >= 8 && k0 + BK <= p.K;  // see "Unguarded loads" above
-    if (raw) {
+    const int left = p.K - k0;  // see "Unguarded loads" above
+    if (left >= BK && p.N >= 8) {
 #pragma unroll
       for (int j = 0; j < NA; ++j) ra[j] = load_as<uint4>(pa[j] + k0);
 #pragma unroll
       for (int j = 0; j < NB; ++j) rb[j] = load_as<uint4>(pb + int64_t(k0 + j * (NT / (BN / 8))) * p.ldb);
       return;
     }
+    const int t = here(tid), eac = (t % (BK / 8)) * 8, ebr = t / (BN / 8), ebc = n0 + (t % (BN / 8)) * 8;
+    if (left > 0) {
 #pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      const int gr = m0 + ar + j * (NT / (BK / 8)), gc = k0 + ac;
-      if (gr < p.M && gc + 7 < p.K) ra[j] = load_as<uint4>(A + int64_t(gr) * p.lda + gc);
-      else ra[j] = pack8_guarded(A + int64_t(gr) * p.lda + gc, [&](int e) { return gr < p.M && gc + e < p.K; });
+      for (int j = 0; j < NA; ++j) ra[j] = load_edge_as<uint4>(pa[j] - eac, k0 + eac, p.K);
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        rb[j] = load_edge_as<uint4>(B + int64_t(min(k0 + ebr + j * (NT / (BN / 8)), p.K - 1)) * p.ldb, ebc, p.N);
     }
+    if (left < BK) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int gk = k0 + br + j * (NT / (BN / 8));
-      if (gk < p.K && bc + 7 < p.N) rb[j] = load_as<uint4>(B + int64_t(gk) * p.ldb + bc);
-      else rb[j] = pack8_guarded(B + int64_t(gk) * p.ldb + bc, [&](int e) { return gk < p.K && bc + e < p.N; });
+      for (int j = 0; j < NA; ++j) {
+        if (p.K >= 8) ra[j] = shift_down(ra[j], 16 * min(max(eac + 8 - left, 0), 7));
+        ra[j] = keep_first(ra[j], left - eac);
+      }
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        if (ebr + j * (NT / (BN / 8)) >= left) rb[j] = uint4{0, 0, 0, 0};
     }
   };
 
@@ -476,7 +494,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &p, int bid, unsig
     for (int j = 0; j < NA; ++j) *reinterpret_cast<uint4 *>(&As[(ar + j * (NT / (BK / 8))) * KP + ac]) = ra[j];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      if (raw && !n_whole) rb[j] = shift_down(rb[j], b_bits);
+      if (!n_whole) rb[j] = shift_down(rb[j], b_bits);
       *reinterpret_cast<uint4 *>(&Bs[(br + j * (NT / (BN / 8))) * BP + bc - n0]) = rb[j];
     }
     __syncthreads();
@@ -544,47 +562,40 @@ __device__ __forceinline__ void gemm_f32_splitk_tile(const GemmArgs &p, int bid,
 
   float4 ra[UA], rb[UB];
   const bool n_whole = n0 + TN <= p.N;
-  const int bc = n0 + (lane % (TN / 4)) * 4, bs = max(0, min(bc, p.N - 4)), b_bits = min(32 * (bc - bs), 96);
-  bool raw = false;
-  const float *pa[UA], *const pb = B + int64_t(lane / (TN / 4)) * p.ldb + bs;
+  const int ac = (lane % (BK / 4)) * 4, br = lane / (TN / 4);
+  const int bc = n0 + (lane % (TN / 4)) * 4, bs = max(0, min(bc, p.N - 4));
+  const int b_bits = p.N >= 4 ? min(32 * (bc - bs), 96) : 0;
+  constexpr int BR = 64 / (TN / 4);  // B rows one load of the wavefront covers
+  const float *pa[UA], *const pb = B + int64_t(br) * p.ldb + bs;
 #pragma unroll
-  for (int j = 0; j < UA; ++j)
-    pa[j] = A + int64_t(min(m0 + (lane + 64 * j) / (BK / 4), p.M - 1)) * p.lda + (lane % (BK / 4)) * 4;
+  for (int j = 0; j < UA; ++j) pa[j] = A + int64_t(min(m0 + (lane + 64 * j) / (BK / 4), p.M - 1)) * p.lda + ac;
   auto load = [&](int chunk) {
     const int k0 = chunk * BK;
-    raw = p.N >= 4 && k0 + BK <= p.K;  // see "Unguarded loads" above
-    if (raw) {
+    const int left = p.K - k0;  // see "Unguarded loads" above
+    if (left >= BK && p.N >= 4) {
 #pragma unroll
       for (int j = 0; j < UA; ++j) ra[j] = load_as<float4>(pa[j] + k0);
 #pragma unroll
-      for (int j = 0; j < UB; ++j) rb[j] = load_as<float4>(pb + int64_t(k0 + j * (64 / (TN / 4))) * p.ldb);
+      for (int j = 0; j < UB; ++j) rb[j] = load_as<float4>(pb + int64_t(k0 + j * BR) * p.ldb);
       return;
     }
+    const int t = here(lane), eac = (t % (BK / 4)) * 4, ebr = t / (TN / 4), ebc = n0 + (t % (TN / 4)) * 4;
+    if (left > 0) {
 #pragma unroll
-    for (int j = 0; j < UA; ++j) {
-      const int u = lane + 64 * j, r = u / (BK / 4), c = (u % (BK / 4)) * 4;
-      const int gr = m0 + r, gc = k0 + c;
-      if (gr < p.M && gc + 3 < p.K) {
-        ra[j] = load_as<float4>(A + int64_t(gr) * p.lda + gc);
-      } else {
-        float v[4];
+      for (int j = 0; j < UA; ++j) ra[j] = load_edge_as<float4>(pa[j] - eac, k0 + eac, p.K);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (gr < p.M && gc + e < p.K) ? load1(A + int64_t(gr) * p.lda + gc + e) : 0.f;
-        ra[j] = make_float4(v[0], v[1], v[2], v[3]);
-      }
+      for (int j = 0; j < UB; ++j)
+        rb[j] = load_edge_as<float4>(B + int64_t(min(k0 + ebr + j * BR, p.K - 1)) * p.ldb, ebc, p.N);
     }
+    if (left < BK) {
 #pragma unroll
-    for (int j = 0; j < UB; ++j) {
-      const int u = lane + 64 * j, r = u / (TN / 4), c = (u % (TN / 4)) * 4;
-      const int gr = k0 + r, gc = n0 + c;
-      if (gr < p.K && gc + 3 < p.N) {
-        rb[j] = load_as<float4>(B + int64_t(gr) * p.ldb + gc);
-      } else {
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (gr < p.K && gc + e < p.N) ? load1(B + int64_t(gr) * p.ldb + gc + e) : 0.f;
-        rb[j] = make_float4(v[0], v[1], v[2], v[3]);
+      for (int j = 0; j < UA; ++j) {
+        if (p.K >= 4) ra[j] = shift_down(ra[j], 32 * min(max(eac + 4 - left, 0), 3));
+        ra[j] = keep_first(ra[j], left - eac);
       }
+#pragma unroll
+      for (int j = 0; j < UB; ++j)
+        if (ebr + j * BR >= left) rb[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   };
 
@@ -594,23 +605,22 @@ __device__ __forceinline__ void gemm_f32_splitk_tile(const GemmArgs &p, int bid,
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  load(w);  // chunk w; chunks >= nchunks load zeros
+  load(w);  // chunk w; chunks >= nchunks are zeros
   for (int it = 0; it < iters; ++it) {
     // no block barrier in this loop: each wavefront stages and reads only its own LDS region,
     // and one wavefront's LDS operations take effect in program order
 #pragma unroll
     for (int j = 0; j < UA; ++j) {
-      const int u = lane + 64 * j, r = u / (BK / 4), c = (u % (BK / 4)) * 4;
-      As[(c + 0) * SA + r] = ra[j].x;
-      As[(c + 1) * SA + r] = ra[j].y;
-      As[(c + 2) * SA + r] = ra[j].z;
-      As[(c + 3) * SA + r] = ra[j].w;
+      const int r = (lane + 64 * j) / (BK / 4);
+      As[(ac + 0) * SA + r] = ra[j].x;
+      As[(ac + 1) * SA + r] = ra[j].y;
+      As[(ac + 2) * SA + r] = ra[j].z;
+      As[(ac + 3) * SA + r] = ra[j].w;
     }
 #pragma unroll
     for (int j = 0; j < UB; ++j) {
-      const int u = lane + 64 * j, r = u / (TN / 4), c = (u % (TN / 4)) * 4;
-      if (raw && !n_whole) rb[j] = shift_down(rb[j], b_bits);
-      *reinterpret_cast<float4 *>(&Bs[r * SB + c]) = rb[j];
+      if (!n_whole) rb[j] = shift_down(rb[j], b_bits);
+      *reinterpret_cast<float4 *>(&Bs[(br + j * BR) * SB + bc - n0]) = rb[j];
     }
     if (it + 1 < iters) load((it + 1) * 4 + w);
 #pragma unroll
@@ -664,33 +674,39 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
   uint4 ra[UA], rb[UB];
   const bool n_whole = n0 + TN <= p.N;
   const int ac = (lane % (BK / 8)) * 8, ar = lane / (BK / 8), br = lane / (TN / 8);
-  const int bc = n0 + (lane % (TN / 8)) * 8, bs = max(0, min(bc, p.N - 8)), b_bits = min(16 * (bc - bs), 112);
-  bool raw = false;
+  const int bc = n0 + (lane % (TN / 8)) * 8, bs = max(0, min(bc, p.N - 8));
+  const int b_bits = p.N >= 8 ? min(16 * (bc - bs), 112) : 0;
   const uint16_t *pa[UA], *const pb = B + int64_t(br) * p.ldb + bs;
 #pragma unroll
   for (int j = 0; j < UA; ++j) pa[j] = A + int64_t(min(m0 + ar + 8 * j, p.M - 1)) * p.lda + ac;
   constexpr int BR = 64 / (TN / 8);  // B rows one load of the wavefront covers
   auto load = [&](int chunk) {
     const int k0 = chunk * BK;
-    raw = p.N >= 8 && k0 + BK <= p.K;  // see "Unguarded loads" above
-    if (raw) {
+    const int left = p.K - k0;  // see "Unguarded loads" above
+    if (left >= BK && p.N >= 8) {
 #pragma unroll
       for (int j = 0; j < UA; ++j) ra[j] = load_as<uint4>(pa[j] + k0);
 #pragma unroll
       for (int j = 0; j < UB; ++j) rb[j] = load_as<uint4>(pb + int64_t(k0 + j * BR) * p.ldb);
       return;
     }
+    const int t = here(lane), eac = (t % (BK / 8)) * 8, ebr = t / (TN / 8), ebc = n0 + (t % (TN / 8)) * 8;
+    if (left > 0) {
 #pragma unroll
-    for (int j = 0; j < UA; ++j) {
-      const int gr = m0 + ar + 8 * j, gc = k0 + ac;
-      if (gr < p.M && gc + 7 < p.K) ra[j] = load_as<uint4>(A + int64_t(gr) * p.lda + gc);
-      else ra[j] = pack8_guarded(A + int64_t(gr) * p.lda + gc, [&](int e) { return gr < p.M && gc + e < p.K; });
+      for (int j = 0; j < UA; ++j) ra[j] = load_edge_as<uint4>(pa[j] - eac, k0 + eac, p.K);
+#pragma unroll
+      for (int j = 0; j < UB; ++j)
+        rb[j] = load_edge_as<uint4>(B + int64_t(min(k0 + ebr + j * BR, p.K - 1)) * p.ldb, ebc, p.N);
     }
+    if (left < BK) {
 #pragma unroll
-    for (int j = 0; j < UB; ++j) {
-      const int gk = k0 + br + j * BR;
-      if (gk < p.K && bc + 7 < p.N) rb[j] = load_as<uint4>(B + int64_t(gk) * p.ldb + bc);
-      else rb[j] = pack8_guarded(B + int64_t(gk) * p.ldb + bc, [&](int e) { return gk < p.K && bc + e < p.N; });
+      for (int j = 0; j < UA; ++j) {
+        if (p.K >= 8) ra[j] = shift_down(ra[j], 16 * min(max(eac + 8 - left, 0), 7));
+        ra[j] = keep_first(ra[j], left - eac);
+      }
+#pragma unroll
+      for (int j = 0; j < UB; ++j)
+        if (ebr + j * BR >= left) rb[j] = uint4{0, 0, 0, 0};
     }
   };
 
@@ -710,7 +726,7 @@ __device__ __forceinline__ void gemm_bf16_splitk_tile(const GemmArgs &p, int bid
     for (int j = 0; j < UA; ++j) *reinterpret_cast<uint4 *>(&As[(ar + 8 * j) * KP + ac]) = ra[j];
 #pragma unroll
     for (int j = 0; j < UB; ++j) {
-      if (raw && !n_whole) rb[j] = shift_down(rb[j], b_bits);
+      if (!n_whole) rb[j] = shift_down(rb[j], b_bits);
       *reinterpret_cast<uint4 *>(&Bs[(br + j * BR) * BP + bc - n0]) = rb[j];
     }
     if (it + 1 < iters) load((it + 1) * 4 + w);
@@ -1575,7 +1591,7 @@ __device__ __forceinline__ void transpose_tile_vec(const TransArgs &p, int bid, 
   // columns, so the ones in flight together write different column ranges of B (with a
   // power-of-two leading dimension, equal column ranges of many rows share HBM channels)
   const int tc = bid % tiles_c, tr = (bid / tiles_c + tc) % tiles_r;
-  if ((tr + 1) * 64 <= p.R && (tc + 1) * 64 <= p.C) {
+  if (__builtin_expect((tr + 1) * 64 <= p.R && (tc + 1) * 64 <= p.C, 1)) {
     transpose_vec_load<T, false, NT>(p, tr, tc, tile);
     __syncthreads();
     transpose_vec_store<T, false, NT>(p, tr, tc, tile);
