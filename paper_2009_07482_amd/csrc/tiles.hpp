@@ -1599,6 +1599,7 @@ __device__ __forceinline__ void transpose_tile_vec(const TransArgs &p, int bid, 
     transpose_vec_load<T, true, NT>(p, tr, tc, tile);
     __syncthreads();
     transpose_vec_store<T, true, NT>(p, tr, tc, tile);
+    asm volatile("");  // (keeps the stores of the two paths apart: merged, whole tiles take a jump more)
   }
 }
 
