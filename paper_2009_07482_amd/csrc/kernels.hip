@@ -359,16 +359,19 @@ int gemm_sum_order(int tile) {
 }
 
 int gemm_group_tile(const std::vector<GemmArgs> &args, int tile) {
-  // The largest tile of the same order that still yields kGroupBlocks blocks over all kernels.
+  // The largest tile of the same order that still yields kGroupBlocks blocks over all kernels and is
+  // not wasteful for those that hold more than an eighth of them: one short instance of a batch does
+  // not set the tile of the long ones (lengths 1 and eight times 512, FP32: 0.535 ms, and 0.580 when
+  // it does; eight times 1 and of 512: 0.564 and 0.679).
   constexpr int64_t kGroupBlocks = 384;
   auto fits = [&](int t) {
-    int64_t n = 0;
-    bool waste = false;
+    int64_t n = 0, waste = 0;
     for (const GemmArgs &a : args) {
-      n += tiles_of(t, a.M, a.N);
-      waste = waste || wasteful(t, a.M, a.N);
+      const int64_t b = tiles_of(t, a.M, a.N);
+      n += b;
+      if (wasteful(t, a.M, a.N)) waste += b;
     }
-    return n >= kGroupBlocks && !waste;
+    return n >= kGroupBlocks && 8 * waste <= n;
   };
   if (gemm_sum_order(tile) == 1) {
     for (int t : kStaged)
