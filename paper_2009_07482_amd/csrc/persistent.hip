@@ -128,9 +128,8 @@ __device__ __forceinline__ T uniform_load(const unsigned char *p) {
 constexpr uint32_t kGAll = kGElem | (1u << 14) | 0x1FFFu, kGF32All = kGElem | 0x3Fu,
                    kGBf16All = kGElem | (1u << 14) | 0x1FC0u;
 // Wavefronts per SIMD each instance is compiled for, the most its tile functions fit without
-// spilling registers to memory: the element-wise instance three (three workgroups' LDS fill a
-// CU), the aligned direct-load and attention instances two, the instances with every FP32, every
-// BF16 or every tile function one.
+// spilling registers to memory: the element-wise instance three, the direct-load and attention
+// instances two, the instances with every FP32, every BF16 or every tile function one.
 constexpr int exec_waves(uint32_t g) {
   return g == kGElem ? 3 : (g == kGAll || g == kGF32All || g == kGBf16All) ? 1 : 2;
 }
@@ -196,10 +195,30 @@ __device__ __forceinline__ bool run_task(const ExecNode *ndp, int tile, unsigned
 
 #undef PSC_TASK
 
-// LDS per workgroup: the largest tile function's -- 48 KiB (FP32 K-split tiles), or the 64 x 64
-// BF16 K-split tile's 72 KiB in the instances holding group 14.
+// LDS of the largest tile function of each group, and per workgroup of an instance (besides the task
+// list): 16.3 KiB with the element-wise functions alone, 17 KiB with the FP32 tiles, 40 KiB with the BF16 ones,
+// 76 KiB with the 64 x 64 BF16 K-split tile.
+constexpr int exec_group_smem(int group) {
+  switch (group) {
+    case 0: return gemm_f32_smem<64, 64, 16>();
+    case 3: return gemm_direct_smem<1, false>();
+    case 4: return gemm_direct_smem<2, false>();
+    case 5: return gemm_direct_smem<4, false>();
+    case 6: return gemm_bf16_smem<64, 64, 64>();
+    case 7: return gemm_bf16_smem<128, 128, 64>();
+    case 10: return gemm_direct_smem<1, true>();
+    case 11: return gemm_direct_smem<2, true>();
+    case 12: return gemm_direct_smem<4, true>();
+    case 13: return 64 * 65 * 4;  // transpose
+    case 14: return gemm_bf16_splitk_smem<64, 64>();
+    default: return 0;
+  }
+}
 constexpr int exec_smem(uint32_t g) {
-  return (g & (1u << 14)) ? (gemm_bf16_splitk_smem<64, 64>() > 49152 ? gemm_bf16_splitk_smem<64, 64>() : 49152) : 49152;
+  int n = 0;
+  for (int i = 0; i < 15; ++i)
+    if ((g >> i & 1u) && exec_group_smem(i) > n) n = exec_group_smem(i);
+  return n;
 }
 
 __global__ __launch_bounds__(256) void exec_reset_kernel(ExecArgs a) {
@@ -333,8 +352,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(exec_waves(
 // workgroups per CU.  The all-groups instance comes last and covers any DAG.
 constexpr uint32_t kInstances[] = {
     kGElem,                                                    // element-wise kernels only
-    kGElem | (1u << 3) | (1u << 4) | (1u << 5),                 // FP32: aligned direct-load tiles
-    kGElem | (1u << 10) | (1u << 11) | (1u << 12),              // BF16: aligned direct-load tiles
+    kGElem | (1u << 3) | (1u << 4) | (1u << 5),                 // FP32: direct-load tiles
+    kGElem | (1u << 10) | (1u << 11) | (1u << 12),              // BF16: direct-load tiles
     kGElem | (1u << 0) | (1u << 3) | (1u << 4) | (1u << 5),     // FP32 attention: + 64 x 64 tile
     kGElem | (3u << 6) | (1u << 10) | (1u << 11) | (1u << 12),  // BF16 attention: + 64 x 64, 128 x 128 tiles
     kGF32All,                                                  // every FP32 tile function
