@@ -54,10 +54,12 @@ __device__ __forceinline__ void softmax_task(const SoftmaxArgs &p, int tile) {
 
 template <bool IN_BF16, bool OUT_BF16>
 __device__ __forceinline__ void add_task(const AddArgs &p, int tile) {
-  const int nbx = (p.C + 2047) / 2048;  // column chunks of a row
+  const uint32_t units = add_units(p.C);
 #pragma unroll 1
-  for (int j = 0; j < 8 * nbx; ++j)
-    add_unit<IN_BF16, OUT_BF16>(p, tile * 8 + j / nbx, (j % nbx) * 2048 + int(threadIdx.x) * 8);
+  for (uint32_t u = uint32_t(here(threadIdx.x)); u < 8 * units; u += 256) {
+    const uint32_t r = u / units;
+    add_unit<IN_BF16, OUT_BF16>(p, tile * 8 + int(r), int(u - r * units) * 8);
+  }
 }
 
 // Copies rows [tile rpt, (tile + 1) rpt) of a host copy, the region taken as units of 16 bytes
