@@ -252,8 +252,10 @@ typedef struct psc_run_stats {
                               the device clock of a start mark, which every stream waits for,
                               to that of an end mark, after every stream joined */
   double host_enqueue_ms;  /* host wall time spent enqueueing (graph launch only, in graph mode) */
+  /* the schedule as psc_sched_export gives it, kernel by kernel; a run that shares launches (see
+     psc_run) makes fewer launches and waits, on no more queues */
   int32_t n_ops, n_kernels, n_h2d, n_d2h, n_waits, n_streams, graph;
-  int32_t aql_packets;     /* AQL packets written (PSC_DISPATCH_AQL), else 0 */
+  int32_t aql_packets;     /* AQL packets the run wrote (PSC_DISPATCH_AQL), else 0 */
 } psc_run_stats;
 
 /* Per-op timing of the last psc_run with record_ops = 1, relative to the start event. */
@@ -442,8 +444,8 @@ psc_status psc_sched_prepare(psc_sched *sched);
  * sum in the order of the size heuristic's tile.  (Once a tile of another order is in the tile cache
  * for one of the two kinds of launch, their results may differ in rounding; within one schedule all
  * kernels of a shape sum in one order.)  The streams are carried by as many hardware queues as a prediction of the
- * run finds fastest, stream s by queue s mod that count (runs with host copies on kernel streams
- * keep one queue per stream).  Every kernel keeps its own launch and stream under record_ops, mark_components,
+ * run finds fastest, stream s by queue s mod that count (runs with host copies on kernel streams:
+ * by at most four).  Every kernel keeps its own launch and stream under record_ops, mark_components,
  * use_graph, fault_inject_op and out_of_order, and under every other policy.
  * Errors: PSC_ERR_NAME (io names no isolated write or read), PSC_ERR_ARG (byte count), PSC_ERR_HIP. */
 psc_status psc_run(psc_sched *sched, const psc_host_io *io, int32_t n_io, psc_run_stats *stats);

@@ -1,9 +1,10 @@
 // Launch groups of a fine schedule: mutually independent kernels of one stream that share a kernel
 // function run as one launch.  A queue runs one launch at a time, and the kernels of an attention
 // head or a small instance fill a fraction of the GPU for a few microseconds each, so their number
-// set a schedule's time.  Measured with groups (and the tiles they allow) against one launch per
-// kernel: 4-layer 1024 BF16 attention on four AQL queues 622 against 1092 us, 1-layer 512 FP32 104
-// against 161 us, a batch of sixteen BF16 DAGs on four HIP streams 1.58 against 3.70 ms.
+// set a schedule's time.  Measured when they came in, with groups (and the tiles they allow) against
+// one launch per kernel: 4-layer 1024 BF16 attention on AQL queues 622 against 1092 us (410 now, with
+// the kernels and queue counts since), 1-layer 512 FP32 104 against 161 us (64 now), a batch of
+// sixteen BF16 DAGs on HIP streams 1.58 against 3.70 ms (1.10 now).
 #pragma once
 
 #include <cstdint>

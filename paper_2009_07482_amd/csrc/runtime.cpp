@@ -776,10 +776,10 @@ void settle_shared_shapes(Device &d, const Grouping &gr) {
 // How many queues carry the plan's streams: the count with the shortest predicted run.  A wait
 // between queues costs more than a small launch, and launches that fill the GPU gain nothing from
 // running beside each other; kernels of unlike functions and sizes do.  Measured on 1 / 2 / 3 / 4
-// queues (us, the chosen count in brackets): fork-join of 256 FP32 on HIP streams [24] / 74 / 77 / 90;
-// 512 FP32 attention on AQL queues [77] / 83 / 92 / 97; 4-layer 1024 BF16 attention on AQL queues
-// 461 / [430] / 470 / 476; random DAG of 60 kernels on HIP streams [220] / 251 / 235 / 290; batch of
-// sixteen uneven BF16 DAGs on HIP streams 1656 / 1299 / [1213] / 1233.
+// queues (us of GPU time, the chosen count in brackets): fork-join of 256 FP32 on HIP streams [13] /
+// 53 / 43 / 45; 512 FP32 attention on AQL queues [64] / 70 / 73 / 85; 4-layer 1024 BF16 attention on
+// AQL queues 428 / [412] / 434 / 459; random DAG of 60 kernels on HIP streams [164] / 232 / 214 / 215;
+// batch of sixteen uneven BF16 DAGs on HIP streams 1441 / 1159 / [1104] / 1113.
 // A count whose queues cannot hold a whole run (AQL packets) is passed over while a larger one is left.
 std::unique_ptr<Runner> best_grouped(const psc_sched &s, const Device &d, const Grouping &gr, bool copies,
                                      int32_t *queues) {
@@ -884,8 +884,13 @@ void prepare(psc_sched &s) {
     prepare_executor(g, s.plan, s.opts.exec_per_cu, *d);
   } else if (groups_launches(s)) {
     // uploads on their kernels' streams (no copy stream) overlap kernels of other streams: runs
-    // with copies then keep every stream, up to the four queues that the GPU serves at once (4-layer
-    // 1024 BF16 attention with host copies on 2 / 4 / 8 / 16 AQL queues: 0.69 / 0.67 / 1.11 / 1.86 ms)
+    // with copies then keep every stream, up to the four queues that the GPU serves at once.  Steady
+    // runs of sixteen streams with host copies on 1 / 2 / 4 / 8 / 16 queues (us): 4-layer 1024 BF16
+    // attention on AQL queues 1401 / 1371 / 1415 / 2416 / 4086, on HIP streams 1441 / 1419 / 1435 /
+    // 1661 / 2120; random DAG of 60 kernels 1796 / 1713 / 1448 / 1896 / 2060 and 1948 / 1211 / 1243 /
+    // 1203 / 1287; batch of sixteen DAGs 2646 / 2095 / 1883 / 2448 / 2951 and 2708 / 1931 / 1805 /
+    // 1710 / 2138.  (The first runs with copies on new HIP streams take several times that, whatever
+    // the plan is.)
     int32_t queues = s.plan.n_streams;
     const Grouping gr = grouping_of(g, *d);
     d->grouped[0] = best_grouped(s, *d, gr, false, &queues);

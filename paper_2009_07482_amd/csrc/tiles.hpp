@@ -1,11 +1,11 @@
 // Device tile functions of the gfx950 kernel library: GEMM on the matrix cores (FP32 and BF16
 // operands, FP32 accumulation), row softmax with wavefront reductions, LDS-tiled transpose and
 // element-wise add.  Each function computes one block-sized piece of its kernel (a GEMM output
-// tile, one softmax row per wavefront, a 64 x 64 transpose tile, a 256-column row segment) with
-// 256 threads and caller-provided LDS, so the same code serves the standalone kernels
-// (kernels.hip, one piece per block) and the persistent DAG executor (persistent.hip, pieces
-// pulled from a device work queue).  Every function handles ragged shapes with bounds checks;
-// vector loads are used only where the host has checked alignment.
+// tile, one softmax row per wavefront, a transpose tile, 256 units of an add) with 256 threads and
+// caller-provided LDS, so the same code serves the standalone kernels (kernels.hip, one piece per
+// block) and the persistent DAG executor (persistent.hip, pieces from lists planned by the host).
+// Every function handles ragged shapes and operands of any alignment with 16-byte accesses; only
+// the 256 x 256 BF16 tiles ask for whole tiles and aligned operands, which the host checks.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,7 +28,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // bytes (odd matrix sizes, windows) are read with the same wide accesses as aligned ones, at the
 // cost of one more cache line where a wavefront's run of addresses crosses one.  Read element by
 // element, as they were before, a batch of sixteen attention DAGs of odd lengths (BF16, 1,824
-// kernels) took 6.77 ms; it takes 3.70 ms.  NT: with the non-temporal (streaming) hint, for operands far larger than the last-level
+// kernels) took 6.77 ms; wide accesses alone brought it to 3.70 ms.  NT: with the non-temporal (streaming) hint, for operands far larger than the last-level
 // cache, which are read or written once and would only evict data still to be used.
 // Every access names global memory: a pointer that itself was read from memory (the argument list of
 // a launch of several kernels, the executor's nodes) would otherwise be followed with flat
@@ -213,7 +213,7 @@ __device__ __forceinline__ int group_tile(int t, int tiles_m, int tiles_n, int G
 // also serves matrices narrower than a vector, whose elements are loaded one by one.  With a
 // check per vector those blocks set the time of a ragged product: 1777 x 2050 x 1001 FP32, whose
 // last tile column is two wide, took 143 us reading element by element, 128 us with unguarded
-// vectors everywhere else, and takes 92 us.
+// vectors everywhere else, and takes 95 us.
 // ---------------------------------------------------------------------------------------------
 template <bool OUT_BF16>
 __device__ __forceinline__ void store4_whole(const GemmArgs &p, int row, int col, floatx4 v) {
