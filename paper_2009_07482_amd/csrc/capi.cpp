@@ -901,7 +901,7 @@ psc_status psc_autotune_dag_in_schedule(psc_dag *dag, int32_t policy, const psc_
     // choice for launches of one kernel stays the isolated winner, which every other schedule of
     // the process takes.
     std::vector<char> shared(cls.size(), 0);
-    {
+    if (policy == PSC_FINE && !cls.empty()) {
       psc_sched *s = schedule();
       try {
         psc::prepare(*s);
