@@ -54,12 +54,13 @@ __device__ __forceinline__ void softmax_task(const SoftmaxArgs &p, int tile) {
 
 template <bool IN_BF16, bool OUT_BF16>
 __device__ __forceinline__ void add_task(const AddArgs &p, int tile) {
-  const uint32_t units = add_units(p.C);
+  // rows of up to 1024 columns share a step, each on as many threads as a power of two that holds it
+  const int units = add_units(p.C), nbx = (units + 255) / 256;
+  int lw = 8;
+  while (lw > 5 && (1 << (lw - 1)) >= units) --lw;
+  const int tid = threadIdx.x, r = tile * 8 + (tid >> lw), c = (tid & ((1 << lw) - 1)) * 8;
 #pragma unroll 1
-  for (uint32_t u = uint32_t(here(threadIdx.x)); u < 8 * units; u += 256) {
-    const uint32_t r = u / units;
-    add_unit<IN_BF16, OUT_BF16>(p, tile * 8 + int(r), int(u - r * units) * 8);
-  }
+  for (int j = 0; j < 8 * nbx; j += 256 >> lw) add_unit<IN_BF16, OUT_BF16>(p, r + j / nbx, (j % nbx) * 2048 + c);
 }
 
 // Copies rows [tile rpt, (tile + 1) rpt) of a host copy, the region taken as units of 16 bytes
