@@ -1560,11 +1560,12 @@ template <typename T, bool CHECK, bool NT>
 __device__ __forceinline__ void transpose_vec_store(const TransArgs &p, int tr, int tc, T (*tile)[65]) {
   constexpr int V = 16 / int(sizeof(T)), VPR = 64 / V, RPP = 256 / VPR, PASSES = 64 / RPP;
   T *B = static_cast<T *>(p.B);
-  if (CHECK && tr * 64 + 64 > p.R) {
-    // B's rows end in this tile: element by element, consecutive threads along a row and then down the
-    // rows, so that narrow ones (which lie one behind the other) are written as one run.  (By vectors
-    // where they fit: 15 x 4.5 million FP32 154 us, not 119.)
-    const uint32_t w = uint32_t(p.R - tr * 64), rows = uint32_t(min(64, p.C - tc * 64));
+  const int left = p.R - tr * 64;  // columns of B that the tile reaches
+  if (CHECK && left <= 32) {
+    // few of them: element by element, consecutive threads along a row and then down the rows, so that
+    // narrow ones (which lie one behind the other) are written as one run.  (By vectors where they
+    // fit: 15 x 4.5 million FP32 154 us, not 101.  42 x 3000: 2.84 and 3.06 us.)
+    const uint32_t w = uint32_t(left), rows = uint32_t(min(64, p.C - tc * 64));
 #pragma unroll 1
     for (uint32_t i = threadIdx.x; i < rows * w; i += 256) {
       const uint32_t oc = i / w, x = i - oc * w;
@@ -1580,9 +1581,15 @@ __device__ __forceinline__ void transpose_vec_store(const TransArgs &p, int tr, 
     T e[V];
 #pragma unroll
     for (int j = 0; j < V; ++j) e[j] = tile[vx * V + j][oc];
-    u32x4 w;
-    memcpy(&w, e, 16);
-    if (!CHECK || orow < p.C) store16<NT>(B + int64_t(orow) * p.ldb + ocol, w);
+    if (!CHECK || (orow < p.C && ocol + V <= p.R)) {
+      u32x4 w;
+      memcpy(&w, e, 16);
+      store16<NT>(B + int64_t(orow) * p.ldb + ocol, w);
+    } else if (orow < p.C) {
+#pragma unroll
+      for (int j = 0; j < V; ++j)
+        if (ocol + j < p.R) store1(B + int64_t(orow) * p.ldb + ocol + j, e[j]);
+    }
   }
 }
 
@@ -1683,7 +1690,7 @@ __device__ __forceinline__ void add_unit(const AddArgs &p, int r, int c) {
   using T = typename std::conditional<IN_BF16, uint16_t, float>::type;
   u32x4 x[NV], y[NV];
   const T *A = static_cast<const T *>(p.A) + ra, *B = static_cast<const T *>(p.B) + rb;
-  if (p.C % 8 == 0) {
+  if (c + 8 <= p.C) {
 #pragma unroll
     for (int h = 0; h < NV; ++h) x[h] = load16<NT>(A + c + V * h);
 #pragma unroll
@@ -1693,9 +1700,8 @@ __device__ __forceinline__ void add_unit(const AddArgs &p, int r, int c) {
     for (int h = 0; h < NV; ++h) x[h] = load_edge<T, NT>(A, c + V * h, p.C);
 #pragma unroll
     for (int h = 0; h < NV; ++h) y[h] = load_edge<T, NT>(B, c + V * h, p.C);
-    if (c + 8 > p.C)
 #pragma unroll
-      for (int h = 0; h < NV; ++h) x[h] = in_place<T>(x[h], c + V * h, p.C), y[h] = in_place<T>(y[h], c + V * h, p.C);
+    for (int h = 0; h < NV; ++h) x[h] = in_place<T>(x[h], c + V * h, p.C), y[h] = in_place<T>(y[h], c + V * h, p.C);
   }
   float a[8], b[8];
 #pragma unroll
