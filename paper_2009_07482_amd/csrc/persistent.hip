@@ -144,8 +144,8 @@ __device__ __forceinline__ bool run_task(const ExecNode *ndp, int tile, unsigned
   const ExecNode &nd = *ndp;
   const int v = __builtin_amdgcn_readfirstlane(nd.variant);
   switch (v) {
-    PSC_TASK(110, gemm_f32_tile<64, 64, 16, 32, 32, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
-    PSC_TASK(111, gemm_f32_tile<64, 64, 16, 32, 32, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(110, gemm_f32_tile<64, 64, 16, 32, 32, false, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
+    PSC_TASK(111, gemm_f32_tile<64, 64, 16, 32, 32, true, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
     PSC_TASK(154, gemm_direct_tile<1, false, false>(uniform_load<GemmArgs>(nd.args), tile, smem));
     PSC_TASK(155, gemm_direct_tile<1, false, true>(uniform_load<GemmArgs>(nd.args), tile, smem));
     PSC_TASK(158, gemm_direct_tile<2, false, false, 8>(uniform_load<GemmArgs>(nd.args), tile, smem));

@@ -28,8 +28,9 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // bytes (odd matrix sizes, windows) are read with the same wide accesses as aligned ones, at the
 // cost of one more cache line where a wavefront's run of addresses crosses one.  Read element by
 // element, as they were before, a batch of sixteen attention DAGs of odd lengths (BF16, 1,824
-// kernels) took 6.77 ms; wide accesses alone brought it to 3.70 ms.  NT: with the non-temporal (streaming) hint, for operands far larger than the last-level
-// cache, which are read or written once and would only evict data still to be used.
+// kernels) took 6.77 ms; wide accesses alone brought it to 3.70 ms.  NT: with the non-temporal
+// (streaming) hint, for operands far larger than the last-level cache, which are read or written once
+// and would only evict data still to be used.
 // Every access names global memory: a pointer that itself was read from memory (the argument list of
 // a launch of several kernels, the executor's nodes) would otherwise be followed with flat
 // instructions, which also occupy the LDS path and its wait counter.  Measured: softmax of
@@ -257,7 +258,14 @@ constexpr int gemm_f32_smem() {
   return 4 * BK * ((((BM + 63) / 64) * 64 + 16) + (((BN + 63) / 64) * 64 + 16));
 }
 
-template <int BM, int BN, int BK, int WM, int WN, bool OUT_BF16>
+// FOLD (the executor's task): K goes by parts, a quarter in whole steps and at most 128, each summed
+// from zero and then added to the parts before it, as the direct-load tile's four wavefronts sum.  One
+// chain over all of K rounds off further the longer K is: 1023 x 513 products of K = 777 and 4096 are
+// off by 2.1e-7 and 2.3e-7 of their norm, by 2.6e-7 and 5.8e-7 in four quarters, and a 60-kernel
+// random FP32 DAG by 4.0e-7, in one chain by 9.1e-7.  The loop over a part's steps is the one a single
+// chain has, and so is the time (that DAG 628 us, 638 in one chain; adding up behind a test in every
+// step cost 1 to 4%).
+template <int BM, int BN, int BK, int WM, int WN, bool OUT_BF16, bool FOLD = false>
 __device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, int bid, unsigned char *smem) {
   static_assert(64 * (BM / WM) * (BN / WN) == 256, "four wavefronts per block");
   constexpr int NWN = BN / WN, NT = 64 * (BM / WM) * NWN;
@@ -320,51 +328,65 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs &p, int bid, unsign
     }
   };
 
-  floatx4 acc[FM][FN];
+  floatx4 acc[FM][FN], sum[FM][FN];  // (sum: with FOLD only)
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < FN; ++j) acc[i][j] = sum[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+  const int part = FOLD ? min(((p.K + 3) / 4 + BK - 1) / BK * BK, 128) : p.K;
+  int k0 = 0;
   load(0);
-  for (int k0 = 0; k0 < p.K; k0 += BK) {
+  do {
+    const int end = FOLD ? min(k0 + part, p.K) : p.K;
+    for (; k0 < end; k0 += BK) {
 #pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      const int r = (tid + NT * j) / (BK / 4);
-      As[(ac + 0) * SA + (r ^ swz(ac + 0))] = ra[j].x;
-      As[(ac + 1) * SA + (r ^ swz(ac + 1))] = ra[j].y;
-      As[(ac + 2) * SA + (r ^ swz(ac + 2))] = ra[j].z;
-      As[(ac + 3) * SA + (r ^ swz(ac + 3))] = ra[j].w;
+      for (int j = 0; j < NA; ++j) {
+        const int r = (tid + NT * j) / (BK / 4);
+        As[(ac + 0) * SA + (r ^ swz(ac + 0))] = ra[j].x;
+        As[(ac + 1) * SA + (r ^ swz(ac + 1))] = ra[j].y;
+        As[(ac + 2) * SA + (r ^ swz(ac + 2))] = ra[j].z;
+        As[(ac + 3) * SA + (r ^ swz(ac + 3))] = ra[j].w;
+      }
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        if (!n_whole) rb[j] = shift_down(rb[j], b_bits);
+        *reinterpret_cast<float4 *>(&Bs[(br + j * (NT / (BN / 4))) * SB + bc - n0]) = rb[j];
+      }
+      __syncthreads();
+      if (k0 + BK < p.K) load(k0 + BK);  // in flight while this tile is multiplied
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += 4) {
+        const int k = kk + (lane >> 4);
+        float a[FM], b[FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) a[i] = As[k * SA + ((wm * WM + i * 16 + (lane & 15)) ^ swz(k))];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) b[j] = Bs[k * SB + wn * WN + j * 16 + (lane & 15)];
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j], a[i], acc[i][j], 0, 0, 0);
+      }
+      __syncthreads();
     }
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      if (!n_whole) rb[j] = shift_down(rb[j], b_bits);
-      *reinterpret_cast<float4 *>(&Bs[(br + j * (NT / (BN / 4))) * SB + bc - n0]) = rb[j];
-    }
-    __syncthreads();
-    if (k0 + BK < p.K) load(k0 + BK);  // in flight while this tile is multiplied
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      const int k = kk + (lane >> 4);
-      float a[FM], b[FN];
-#pragma unroll
-      for (int i = 0; i < FM; ++i) a[i] = As[k * SA + ((wm * WM + i * 16 + (lane & 15)) ^ swz(k))];
-#pragma unroll
-      for (int j = 0; j < FN; ++j) b[j] = Bs[k * SB + wn * WN + j * 16 + (lane & 15)];
+    if constexpr (FOLD) {
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j], a[i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < FN; ++j) {
+          sum[i][j] += acc[i][j];
+          acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
     }
-    __syncthreads();
-  }
+  } while (FOLD && k0 < p.K);
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
       const int row = m0 + wm * WM + i * 16 + (lane & 15), col = n0 + wn * WN + j * 16 + (lane >> 4) * 4;
-      store4<OUT_BF16>(p, row, col, p.alpha * acc[i][j]);
+      store4<OUT_BF16>(p, row, col, p.alpha * (FOLD ? sum[i][j] : acc[i][j]));
     }
 }
 
