@@ -81,7 +81,8 @@ __device__ __forceinline__ void read_all(TransArgs &p) {
   asm volatile("" : "+s"(p.A), "+s"(p.B), "+s"(p.lda), "+s"(p.ldb), "+s"(p.R), "+s"(p.C));
 }
 __device__ __forceinline__ void read_all(AddArgs &p) {
-  asm volatile("" : "+s"(p.A), "+s"(p.B), "+s"(p.Cp), "+s"(p.lda), "+s"(p.ldb), "+s"(p.ldc), "+s"(p.R), "+s"(p.C));
+  asm volatile("" : "+s"(p.A), "+s"(p.B), "+s"(p.Cp), "+s"(p.lda), "+s"(p.ldb), "+s"(p.ldc), "+s"(p.R), "+s"(p.C),
+               "+s"(p.inv));
 }
 
 #define PSC_CONSTANT __attribute__((address_space(4)))
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_direct_kernel(GemmArgs p) {
 template <int NV, bool IN_BF16, bool OUT_BF16, bool NT = false, int CW = 4>
 __global__ __launch_bounds__(256) void softmax_kernel(SoftmaxArgs p) {
   const int row = member_block(p, blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (row < p.R) softmax_row<NV, IN_BF16, OUT_BF16, NT, CW>(p, row);
+  if (row < p.R) softmax_row<NV, IN_BF16, OUT_BF16, NT, CW, true>(p, row);
 }
 
 template <typename T, bool NT>
@@ -533,7 +534,9 @@ bool make_add(Launch &L, AddArgs a, int in_dtype, int out_dtype) {
   // plain loads and stores: streaming hints measured slower for the two-input add
   L.func = ib ? (ob ? (const void *)&add_vec_kernel<true, true> : (const void *)&add_vec_kernel<true, false>)
               : (ob ? (const void *)&add_vec_kernel<false, true> : (const void *)&add_vec_kernel<false, false>);
-  L.grid = dim3(unsigned((int64_t(add_units(a.C)) * a.R + 255) / 256), 1, 1);
+  const int64_t units = add_units(a.C);
+  a.inv = units > 1 ? uint32_t((int64_t(1) << 32) / units) : ~0u;
+  L.grid = dim3(unsigned((units * a.R + 255) / 256), 1, 1);
   L.block = dim3(256, 1, 1);
   L.shmem = 0;
   L.empty = a.R == 0 || a.C == 0;

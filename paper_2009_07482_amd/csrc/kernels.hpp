@@ -48,6 +48,7 @@ struct AddArgs {            // Cp (R x C) = A + B
   void *Cp;
   int64_t lda, ldb, ldc;
   int32_t R, C;
+  uint32_t inv, unused;     // inv: 2^32 over the units of a row (make_add)
   const uint32_t *map;
   const AddArgs *list;
 };

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("policy", ["coarse", "device"])
 @pytest.mark.parametrize("dt,out_dt", [("f32", "f32"), ("f32", "bf16"), ("bf16", "f32"), ("bf16", "bf16")])
 @pytest.mark.parametrize("r,widths", [(1, (1, 3, 2)), (5, (7, 8, 9)), (300, (15, 17, 1)), (33, (2047, 2049, 5)),
-                                      (9, (2040, 2056, 2171)), (1000, (4, 6, 1)), (257, (248, 255, 256))])
+                                      (9, (2040, 2056, 2171)), (1000, (4, 6, 1)), (257, (248, 255, 256)),
+                                      (2011, (9, 100, 4104))])
 def test_sums_are_exact_and_stay_in_their_window(r, widths, dt, out_dt, policy):
     """Sums into neighbouring column windows of one matrix: a store beyond a row's end would land in
     the next window, and one that starts late would leave a gap."""
